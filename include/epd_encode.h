@@ -179,7 +179,7 @@ epd_status epd_preprocess(epd_handle h, const uint8_t* pixels, const int32_t* sr
  *          R_1 = 0x0F1E2D3C4B5A6978 mod P over the words s_0 .. s_{L-1} = byte length (low,
  *          high 32 bits), salt (low, high), then the input as 32-bit little-endian words (last
  *          one zero-padded):  H_k = sum_j (s_j + 1) * R_k^(L - j) mod P.
- *   pool   caller-owned device memory; the first 1 MiB is scratch for the hash, the rest an
+ *   pool   caller-owned device memory; the first 1 MiB is reserved, the rest an
  *          arena of contiguous, 256-byte aligned entries; an insert drops least-recently-used
  *          entries until a free range (first fit, lowest address) holds the new entry; a
  *          lookup that hits makes its entry the most recent.
@@ -208,7 +208,7 @@ epd_status epd_store_hash(epd_store_handle s, const void* device_data, const uin
  *   n                1 .. 32 ranges per call; more returns EPD_ERR_SHAPE with nothing launched
  *   keys_device_out  DEVICE uint64 [n, 2]: written by the second of the two kernels this call
  *                    enqueues on `stream`; valid once the stream has passed that kernel
- * The partial hashes live in a 512 KiB array the library holds statically on every GPU it is
+ * The partial hashes live in a 64 KiB array the library holds statically on every GPU it is
  * loaded on (one copy per GPU, for the life of the process): the call allocates and frees nothing,
  * copies nothing and waits for nothing.  All calls on one GPU share that array, so two calls whose
  * kernels may overlap on the same GPU (different streams) race: order them.  Calls on different
