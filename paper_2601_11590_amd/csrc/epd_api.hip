@@ -728,6 +728,8 @@ epd_status epd_encode_cached(epd_handle h, epd_store_handle s, uint64_t model_sa
   if (epd_status e = epd_store_hash(s, pixels, off.data(), salt.data(), n, keys.data(), stream)) {
     h->err = std::string("epd_store_hash: ") + epd_store_last_error(s); return e;
   }
+  CopyArgs cp{};
+  auto flush = [&]() { if (cp.n) launch_copies(cp, st); cp.n = 0; };
   if (keys_out) std::memcpy(keys_out, keys.data(), keys.size() * 8);
   // hits: copy out; misses: collect
   std::vector<int> miss;
@@ -738,8 +740,11 @@ epd_status epd_encode_cached(epd_handle h, epd_store_handle s, uint64_t model_sa
     const epd_status e = epd_store_lookup(s, &keys[2 * i], &p, &bytes);
     const bool hit = e == EPD_OK && bytes == want;
     if (hit_out) hit_out[i] = hit ? 1 : 0;
-    if (hit) EPD_HIP(h, hipMemcpyAsync((char*)out_visual_tokens + (size_t)mrg[i] * row_bytes, p, want, hipMemcpyDeviceToDevice, st));
-    else miss.push_back(i);
+    if (!hit) { miss.push_back(i); continue; }
+  flush();
+  EPD_HIP(h, hipGetLastError());
+    if (cp.n == kCopyItems) flush();
+    cp.item[cp.n++] = CopyItem{p, (char*)out_visual_tokens + (size_t)mrg[i] * row_bytes, nullptr, (long long)want};
   }
   if (miss.empty()) return EPD_OK;
   // misses: preprocess every run of neighbouring items into the compact batch, then encode it
@@ -764,11 +769,18 @@ epd_status epd_encode_cached(epd_handle h, epd_store_handle s, uint64_t model_sa
   for (size_t j = 0; j < miss.size(); ++j) {
     const int i = miss[j];
     const size_t bytes = (size_t)(mrg[i + 1] - mrg[i]) * row_bytes;
-    const char* src = (const char*)out_scratch + m0 * row_bytes;
-    EPD_HIP(h, hipMemcpyAsync((char*)out_visual_tokens + (size_t)mrg[i] * row_bytes, src, bytes, hipMemcpyDeviceToDevice, st));
+    char* const src = (char*)out_scratch + m0 * row_bytes;
+    if (cp.n == kCopyItems) flush();
     void* slot = nullptr;
-    if (epd_store_insert(s, &keys[2 * i], bytes, &slot) == EPD_OK)
-      EPD_HIP(h, hipMemcpyAsync(slot, src, bytes, hipMemcpyDeviceToDevice, st));
+    if (epd_store_insert(s, &keys[2 * i], bytes, &slot) != EPD_OK) slot = nullptr;
+    // an insert may have dropped an entry that this launch was to file: its range is taken over
+    for (int k = 0; slot && k < cp.n; ++k) {
+      CopyItem& o = cp.item[k];
+      if (o.dst2 && (char*)slot < (char*)o.dst2 + o.bytes && (char*)o.dst2 < (char*)slot + bytes) o.dst2 = nullptr;
+    }
+  flush();
+  EPD_HIP(h, hipGetLastError());
+    cp.item[cp.n++] = CopyItem{src, (char*)out_visual_tokens + (size_t)mrg[i] * row_bytes, slot, (long long)bytes};
     m0 += (size_t)(mrg[i + 1] - mrg[i]);
   }
   return EPD_OK;

@@ -149,7 +149,22 @@ struct PrepArgs {
   float a[kPrepChannels], b[kPrepChannels];    // value = pixel * a[c] + b[c]
   PrepItem item[kPrepItems];
 };
-void launch_preprocess(const PrepArgs& a, int tokens, hipStream_t s);   // patch <= 32 (block = patch/2 x patch)
+void launch_preprocess(PrepArgs& a, hipStream_t s);   // patch even, <= 32
+
+// ---------------------------------------------------------------- device-to-device copies
+constexpr int kCopyItems = 64;      // copies per launch (descriptors travel as kernel arguments)
+struct CopyItem {
+  const void* src;
+  void* dst;
+  void* dst2;            // second copy of the same bytes, or nullptr
+  long long bytes;
+};
+struct CopyArgs {
+  int n;
+  int first_block[kCopyItems];   // set by the launcher
+  CopyItem item[kCopyItems];
+};
+void launch_copies(CopyArgs& a, hipStream_t s);   // destinations of one launch must not overlap
 
 constexpr int kVtAlign = 128;   // segment starts in the transposed-V buffer are multiples of this
 
