@@ -675,21 +675,18 @@ epd_status epd_preprocess(epd_handle h, const uint8_t* pixels, const int32_t* sr
   int tok_off = 0;
   for (int i0 = 0; i0 < num_items; i0 += kPrepItems) {
     const int n = std::min(kPrepItems, num_items - i0);
-    long long blocks = 0;
     for (int j = 0; j < n; ++j) {
       const int i = i0 + j;
       PrepItem& d = a.item[j];
       d.t = grid_thw[3 * i]; d.h = grid_thw[3 * i + 1]; d.w = grid_thw[3 * i + 2];
       d.hs = src_hw[2 * i]; d.ws = src_hw[2 * i + 1];
-      d.src_off = src_off; d.tok_off = tok_off; d.blk_off = (int)blocks;
+      d.src_off = src_off; d.tok_off = tok_off;
       const long long tokens = (long long)d.t * d.h * d.w;
-      blocks += tokens;
       src_off += (long long)c.in_channels * d.t * c.temporal_patch * d.hs * d.ws;
       tok_off += (int)tokens;
     }
-    if (blocks > 0x7fffffffLL) { h->err = "internal: preprocess grid too large"; return EPD_ERR_SHAPE; }
     a.n_items = n;
-    launch_preprocess(a, (int)blocks, (hipStream_t)stream);
+    launch_preprocess(a, (hipStream_t)stream);
   }
   EPD_HIP(h, hipGetLastError());
   return EPD_OK;
@@ -728,11 +725,11 @@ epd_status epd_encode_cached(epd_handle h, epd_store_handle s, uint64_t model_sa
   if (epd_status e = epd_store_hash(s, pixels, off.data(), salt.data(), n, keys.data(), stream)) {
     h->err = std::string("epd_store_hash: ") + epd_store_last_error(s); return e;
   }
+  if (keys_out) std::memcpy(keys_out, keys.data(), keys.size() * 8);
+  // hits: copy out, all in one launch; misses: collect
+  std::vector<int> miss;
   CopyArgs cp{};
   auto flush = [&]() { if (cp.n) launch_copies(cp, st); cp.n = 0; };
-  if (keys_out) std::memcpy(keys_out, keys.data(), keys.size() * 8);
-  // hits: copy out; misses: collect
-  std::vector<int> miss;
   for (int i = 0; i < n; ++i) {
     void* p = nullptr;
     uint64_t bytes = 0;
@@ -741,11 +738,11 @@ epd_status epd_encode_cached(epd_handle h, epd_store_handle s, uint64_t model_sa
     const bool hit = e == EPD_OK && bytes == want;
     if (hit_out) hit_out[i] = hit ? 1 : 0;
     if (!hit) { miss.push_back(i); continue; }
-  flush();
-  EPD_HIP(h, hipGetLastError());
     if (cp.n == kCopyItems) flush();
     cp.item[cp.n++] = CopyItem{p, (char*)out_visual_tokens + (size_t)mrg[i] * row_bytes, nullptr, (long long)want};
   }
+  flush();
+  EPD_HIP(h, hipGetLastError());
   if (miss.empty()) return EPD_OK;
   // misses: preprocess every run of neighbouring items into the compact batch, then encode it
   std::vector<int32_t> cu(miss.size() + 1, 0), grid(miss.size() * 3);
@@ -778,11 +775,11 @@ epd_status epd_encode_cached(epd_handle h, epd_store_handle s, uint64_t model_sa
       CopyItem& o = cp.item[k];
       if (o.dst2 && (char*)slot < (char*)o.dst2 + o.bytes && (char*)o.dst2 < (char*)slot + bytes) o.dst2 = nullptr;
     }
-  flush();
-  EPD_HIP(h, hipGetLastError());
     cp.item[cp.n++] = CopyItem{src, (char*)out_visual_tokens + (size_t)mrg[i] * row_bytes, slot, (long long)bytes};
     m0 += (size_t)(mrg[i + 1] - mrg[i]);
   }
+  flush();
+  EPD_HIP(h, hipGetLastError());
   return EPD_OK;
 }
 

@@ -139,13 +139,18 @@ struct PrepItem {
   int hs, ws;            // source frame size
   int t, h, w;           // grid in patches
   int tok_off;           // first packed row of the item
-  int blk_off;           // first token of the item in this launch (blockIdx.x counts tokens)
+  int blk_off;           // first block of the item in this launch (set by the launcher)
+  int slice_blocks;      // blocks per temporal slice, and below: set by the launcher
+  float inv_h, inv_w;    // 1 / (2 * output size)
+  float inv_cols;        // 1 / w
 };
 struct PrepArgs {
   const uint8_t* pixels;
   void* out;             // [T, pdim] bf16 or fp32
   int out_bf16;
   int n_items, channels, patch, tp, pdim;
+  int block_tokens, per_token;              // tokens per block, threads per token (set by the launcher)
+  float inv_per_token, inv_per_row;         // 1 / threads per token, 1 / threads per patch row (set by the launcher)
   float a[kPrepChannels], b[kPrepChannels];    // value = pixel * a[c] + b[c]
   PrepItem item[kPrepItems];
 };

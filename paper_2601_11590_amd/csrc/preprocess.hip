@@ -8,100 +8,188 @@
 // (v / 255 - mean_c) / std_c, row layout (channel, frame in patch, row in patch, column in
 // patch), tokens in raster order over (t, h, w).
 //
-// Bound: HBM (1 byte in per source pixel, 2 or 4 bytes out per element).  One thread makes
-// two neighbouring elements of a patch row (one 4- or 8-byte store); the tap positions are
-// exact integer arithmetic, (2j + 1) * n_in - n_out over 2 * n_out, so that equal sizes copy
-// pixels untouched and the weights carry a single rounding.
+// Bound: HBM (1 byte in per source pixel, 2 or 4 bytes out per element) once enough loads are in
+// flight.  The tap positions are exact integer arithmetic, (2j + 1) * n_in - n_out over 2 * n_out,
+// so that equal sizes copy pixels untouched; the weights carry the rounding of one product.
 #include "epd_internal.h"
 
 namespace epd {
 
-struct Tap { int i0, i1; float w1; };
+struct Tap { int i0; float w1; };
 
-// taps of output sample j along an axis of n_in source and n_out output samples
-__device__ __forceinline__ Tap tap(int j, int n_in, int n_out) {
+// taps of output sample j along an axis of n_in source and n_out output samples: i0 and i0 + 1
+// (clamped by the caller), the second weighted w1.  inv = 1 / (2 n_out): the quotient of the float
+// product is off by at most one (it stays below 2^14), which the remainder shows.
+__device__ __forceinline__ Tap tap(int j, int n_in, int n_out, float inv) {
   const int num = max((2 * j + 1) * n_in - n_out, 0), den = 2 * n_out;
+  int q = (int)((float)num * inv), r = num - q * den;
+  if (r < 0) { --q; r += den; }
+  if (r >= den) { ++q; r -= den; }
   Tap t;
-  t.i0 = min(num / den, n_in - 1);
-  t.i1 = min(t.i0 + 1, n_in - 1);
-  t.w1 = (float)(num - (num / den) * den) / (float)den;
+  t.i0 = min(q, n_in - 1);
+  t.w1 = (float)r * inv;
   return t;
 }
 
-// One block = one token (one output row): thread (x, y) makes V neighbouring elements of row y
-// of each of the token's channel x frame slabs of patch x patch elements in turn, so every pass
-// writes patch * patch consecutive elements and nothing about an element's position has to be
-// divided out of a flat index.  V = 8 (one 16-byte bf16 store) when the patch size allows it,
-// else 2.  blockIdx.x counts the tokens of the (at most kPrepItems) items of this launch.
-template <int V>
+typedef uint16_t u16_any __attribute__((aligned(1)));
+
+// two neighbouring elements of the output
+template <bool BF16> __device__ __forceinline__ void store_pair(char* base, uint32_t off, float v0, float v1) {
+  if constexpr (BF16) {
+    typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+    bf16x2 w;
+    w[0] = (__bf16)v0; w[1] = (__bf16)v1;
+    __builtin_nontemporal_store(w, (bf16x2*)(base + off));     // a stream of output: 41 -> 38 us on the clips below
+  } else {
+    *(float2*)(base + off) = make_float2(v0, v1);
+  }
+}
+
+// channel and frame of the slab at hand; stays on the last one
+struct SlabWalk {
+  int c, dt, left;             // left = slabs still ahead of this one
+  __device__ __forceinline__ void next(int tp) {
+    if (left > 0) { --left; if (++dt == tp) { dt = 0; ++c; } }
+  }
+};
+
+// base + off with off widened next to the load, so that "scalar base + 32-bit lane offset" stays the
+// load's own addressing form
+__device__ __forceinline__ uint32_t pixels_at(const uint8_t* base, uint32_t off) {
+  asm volatile("" : "+v"(off));
+  return *(const u16_any*)(base + (size_t)off);
+}
+
+// A thread owns two neighbouring elements at one position of the patch and makes them for every
+// channel x frame slab of its token, so that positions and taps are worked out once per token; a
+// wave's store is a contiguous run of the output row.  A block takes as many whole tokens of one
+// temporal slice as fit 512 threads: frame and output bases are then scalars, and a load is one
+// instruction on a 32-bit lane offset.  Two elements per thread and not more, because the lanes of
+// one load instruction then cover few source rows: with four or eight per thread a wave touches 16
+// or 32 rows per load and the eight images below take 26 us.
+// Measured, whole calls on inputs that do not stay in the last-level cache, against one block of
+// patch x patch / 8 (or / 2) threads per token with divisions and byte loads per tap: eight images
+// of 224 x 224 ... 1080 x 1920 to 448 x 448 48 -> 13 us (the host needs as long to queue one); 2160 x
+// 3840 to 1056 x 1888 52 -> 14 us (2.7 TB/s); 64 frames at size, patch 14, 61 -> 38 us (3.1 TB/s; bound
+// by HBM and what a wave spends before its first load); the same from 360 x 640 135 -> 70 us (vector
+// arithmetic: about 490 instructions per token and position).
+template <bool BF16>
 __global__ __launch_bounds__(512) void preprocess_kernel(PrepArgs a) {
   // consecutive block ids go to different XCDs (8, each with its own L2): give every XCD a
-  // contiguous eighth of the tokens, so that the neighbouring patches that share a 128-byte line
+  // contiguous eighth of the blocks, so that the neighbouring patches that share a 128-byte line
   // of source pixels fetch it through one L2 instead of eight
   const int nb = gridDim.x;
   const int vb = (blockIdx.x & 7) * (nb >> 3) + min((int)(blockIdx.x & 7), nb & 7) + (blockIdx.x >> 3);
   int it = 0;
-  while (it + 1 < a.n_items && vb >= a.item[it + 1].blk_off) ++it;
-  const PrepItem d = a.item[it];
+#pragma unroll
+  for (int step = kPrepItems / 2; step > 0; step >>= 1)
+    if (it + step < a.n_items && vb >= a.item[it + step].blk_off) it += step;
+  const PrepItem& d = a.item[it];
   const int p = a.patch;
-  const int tok = vb - d.blk_off;                         // token inside the item
-  const int col = tok % d.w, row = (tok / d.w) % d.h, ti = tok / (d.w * d.h);
-  const int px = threadIdx.x * V, py = threadIdx.y;
-  const int ho = d.h * p, wo = d.w * p;
-  const int y = row * p + py, x = col * p + px;
-  const long long plane = (long long)d.hs * d.ws;
-  const bool same = d.hs == ho && d.ws == wo;             // no resize: the taps are the pixels themselves
-  Tap ty = {y, y, 0.f}, tx[V];
+  // small quotients in float: (n + 1/2) / k is at least 1 / (2 k) away from any integer
+  const int tl = (int)(((float)threadIdx.x + 0.5f) * a.inv_per_token), pos = threadIdx.x - tl * a.per_token;
+  const int py = (int)(((float)pos + 0.5f) * a.inv_per_row), px = (pos - py * (p >> 1)) * 2;
+  const int blk = vb - d.blk_off, ti = blk / d.slice_blocks, first = (blk - ti * d.slice_blocks) * a.block_tokens;
+  const long long plane = (long long)d.hs * d.ws, channel = (long long)(d.t * a.tp) * plane;
+  constexpr int ES = BF16 ? 2 : 4;
+  char* const out0 = (char*)a.out + ((long long)(d.tok_off + ti * d.h * d.w) * a.pdim) * ES;
+  const uint32_t o = (uint32_t)(tl * a.pdim + py * p + px) * ES;
+  const uint8_t* const frame0 = a.pixels + d.src_off + (long long)(ti * a.tp) * plane;
+  const int slabs = a.channels * a.tp, slab_bytes = p * p * ES;
+  const bool same = d.hs == d.h * p && d.ws == d.w * p;   // no resize: the pixels themselves
+  const bool narrow = d.ws < 2;                           // rows of one pixel: nothing to load two of
+  if (tl >= a.block_tokens || first + tl >= d.h * d.w) return;
+  const int row0 = first / d.w, along = first - row0 * d.w + tl;           // along < w + 256
+  const int down = (int)(((float)along + 0.5f) * d.inv_cols);
+  const int y = (row0 + down) * p + py, x = (along - down * d.w) * p + px;
+  char* out = out0 + (long long)first * a.pdim * ES;
+  SlabWalk w = {0, 0, slabs - 1};
+  if (same) {
+    constexpr int kSlabs = 6;      // slabs whose loads a thread has in flight together
+    const uint32_t f = (uint32_t)(y * d.ws + x);
+    for (int s0 = 0; s0 < slabs; s0 += kSlabs) {
+      uint32_t q[kSlabs];
+      float ac[kSlabs], bc[kSlabs];
 #pragma unroll
-  for (int i = 0; i < V; ++i) tx[i] = Tap{x + i, x + i, 0.f};
-  if (!same) {
-    ty = tap(y, d.hs, ho);
+      for (int k = 0; k < kSlabs; ++k) {
+        q[k] = pixels_at(frame0 + w.c * channel + w.dt * plane, f);
+        ac[k] = a.a[w.c]; bc[k] = a.b[w.c];
+        w.next(a.tp);
+      }
 #pragma unroll
-    for (int i = 0; i < V; ++i) tx[i] = tap(x + i, d.ws, wo);
+      for (int k = 0; k < kSlabs; ++k) {
+        if (s0 + k >= slabs) break;
+        store_pair<BF16>(out, o, fmaf((float)(q[k] & 0xff), ac[k], bc[k]), fmaf((float)(q[k] >> 8), ac[k], bc[k]));
+        out += slab_bytes;
+      }
+    }
+    return;
   }
-  const long long o_row = (long long)(d.tok_off + tok) * a.pdim + py * p + px;
-  for (int c = 0; c < a.channels; ++c) {
-    const float ac = a.a[c], bc = a.b[c];
-    for (int dt = 0; dt < a.tp; ++dt) {
-      const uint8_t* f = a.pixels + d.src_off + ((long long)c * (d.t * a.tp) + (ti * a.tp + dt)) * plane;
-      const uint8_t* r0 = f + (long long)ty.i0 * d.ws;
-      float v[V];
-      if (same) {
+  constexpr int kSlabs = 3;
+  const Tap ty = tap(y, d.hs, d.h * p, d.inv_h);
+  const uint32_t r0 = (uint32_t)ty.i0 * (uint32_t)d.ws, r1 = (uint32_t)min(ty.i0 + 1, d.hs - 1) * (uint32_t)d.ws;
+  float wx[2];
+  uint32_t at[2];
 #pragma unroll
-        for (int i = 0; i < V; ++i) v[i] = fmaf((float)r0[x + i], ac, bc);
+  for (int i = 0; i < 2; ++i) {
+    const Tap t = tap(x + i, d.ws, d.w * p, d.inv_w);
+    // at or beyond the last pixel centre both taps are the last pixel, the second of the pair loaded
+    wx[i] = t.i0 >= d.ws - 1 ? 1.0f : t.w1;
+    at[i] = (uint32_t)max(min(t.i0, d.ws - 2), 0);
+  }
+  for (int s0 = 0; s0 < slabs; s0 += kSlabs) {
+    uint32_t q[kSlabs][2][2];                             // two neighbouring pixels of rows r0 and r1 per element
+    float ac[kSlabs], bc[kSlabs];
+#pragma unroll
+    for (int k = 0; k < kSlabs; ++k) {
+      const uint8_t* f = frame0 + w.c * channel + w.dt * plane;
+      ac[k] = a.a[w.c]; bc[k] = a.b[w.c];
+      if (narrow) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) { q[k][i][0] = (uint32_t)f[r0] * 0x101u; q[k][i][1] = (uint32_t)f[r1] * 0x101u; }
       } else {
-        const uint8_t* r1 = f + (long long)ty.i1 * d.ws;
 #pragma unroll
-        for (int i = 0; i < V; ++i) {
-          const float top = (1.0f - tx[i].w1) * (float)r0[tx[i].i0] + tx[i].w1 * (float)r0[tx[i].i1];
-          const float bot = (1.0f - tx[i].w1) * (float)r1[tx[i].i0] + tx[i].w1 * (float)r1[tx[i].i1];
-          v[i] = fmaf((1.0f - ty.w1) * top + ty.w1 * bot, ac, bc);
-        }
+        for (int i = 0; i < 2; ++i) { q[k][i][0] = pixels_at(f, r0 + at[i]); q[k][i][1] = pixels_at(f, r1 + at[i]); }
       }
-      const long long o = o_row + (long long)(c * a.tp + dt) * p * p;
-      if (a.out_bf16) {
-        typedef __attribute__((ext_vector_type(V))) __bf16 bf16xV;
-        bf16xV w;
+      w.next(a.tp);
+    }
 #pragma unroll
-        for (int i = 0; i < V; ++i) w[i] = (__bf16)v[i];
-        *(bf16xV*)((uint16_t*)a.out + o) = w;
-      } else {
-        typedef __attribute__((ext_vector_type(V))) float f32xV;
-        f32xV w;
+    for (int k = 0; k < kSlabs; ++k) {
+      if (s0 + k >= slabs) break;
+      float v[2];
 #pragma unroll
-        for (int i = 0; i < V; ++i) w[i] = v[i];
-        *(f32xV*)((float*)a.out + o) = w;
+      for (int i = 0; i < 2; ++i) {
+        float line[2];
+#pragma unroll
+        for (int r = 0; r < 2; ++r)
+          line[r] = fmaf(wx[i], (float)(q[k][i][r] >> 8), (1.0f - wx[i]) * (float)(q[k][i][r] & 0xff));
+        v[i] = fmaf(fmaf(ty.w1, line[1], (1.0f - ty.w1) * line[0]), ac[k], bc[k]);
       }
+      store_pair<BF16>(out, o, v[0], v[1]);
+      out += slab_bytes;
     }
   }
 }
 
-void launch_preprocess(const PrepArgs& a, int tokens, hipStream_t s) {
-  if (tokens <= 0) return;
-  // 16-byte stores need the rows (pdim = C * tp * patch^2 elements) and the buffer 16-byte aligned
-  const bool wide = a.patch % 8 == 0 && ((size_t)a.out & (a.out_bf16 ? 15 : 31)) == 0;
-  if (wide) hipLaunchKernelGGL(preprocess_kernel<8>, dim3(tokens), dim3(a.patch / 8, a.patch), 0, s, a);
-  else hipLaunchKernelGGL(preprocess_kernel<2>, dim3(tokens), dim3(a.patch / 2, a.patch), 0, s, a);
+void launch_preprocess(PrepArgs& a, hipStream_t s) {
+  a.per_token = a.patch * a.patch / 2;          // 2 .. 512 threads
+  a.block_tokens = 512 / a.per_token;
+  a.inv_per_token = 1.0f / (float)a.per_token;
+  a.inv_per_row = 1.0f / (float)(a.patch / 2);
+  long long blocks = 0;
+  for (int i = 0; i < a.n_items; ++i) {
+    PrepItem& d = a.item[i];
+    d.blk_off = (int)blocks;
+    d.slice_blocks = (d.h * d.w + a.block_tokens - 1) / a.block_tokens;
+    d.inv_h = 1.0f / (float)(2 * d.h * a.patch);
+    d.inv_w = 1.0f / (float)(2 * d.w * a.patch);
+    d.inv_cols = 1.0f / (float)d.w;
+    blocks += (long long)d.t * d.slice_blocks;
+  }
+  if (blocks <= 0) return;
+  const dim3 threads((a.block_tokens * a.per_token + 63) / 64 * 64);
+  if (a.out_bf16) hipLaunchKernelGGL(preprocess_kernel<true>, dim3((unsigned)blocks), threads, 0, s, a);
+  else hipLaunchKernelGGL(preprocess_kernel<false>, dim3((unsigned)blocks), threads, 0, s, a);
 }
 
 }  // namespace epd
