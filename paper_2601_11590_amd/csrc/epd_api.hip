@@ -45,7 +45,7 @@ struct Layout {
   int fpad;          // leading dimension of Hd and of the fc2 weights: mlp_dim, padded to 64 on the bf16 path
   size_t patch_w, patch_b, final_g, final_b, merge_w, merge_b;
   std::vector<LayerW> layers;
-  size_t x, xn, qkv, vt, o, hd, rot, merge_idx, vcol, pair_freq, pair_axis, zeros, meta, stats;
+  size_t x, xn, qkv, vt, o, hd, rot, merge_idx, vcol, pair_freq, pair_axis, zeros, meta, work, stats;
   bool fold_rms;     // RMSNorm of the blocks folded into the GEMMs around it (bf16 path)
   int stats_n;       // 128-column segments per residual row
   size_t meta_bytes, total;
@@ -112,8 +112,9 @@ Layout make_layout(const epd_encode_cfg& c) {
   L.pair_axis = take((size_t)std::max(L.pairs, 1) * 4);
   L.zeros = take(256);
   const size_t S = c.max_segments, I = c.max_items;
-  L.meta_bytes = align_up(((S + 1) * 2 + (I + 1) * 2 + 3 * I + 4 * (size_t)L.max_work) * 4);
+  L.meta_bytes = align_up(S * sizeof(PlanSeg) + I * sizeof(PlanItem));
   L.meta = take(L.meta_bytes);
+  L.work = take((size_t)L.max_work * sizeof(AttnWork));
   // bf16 + RMSNorm + hidden a multiple of 128: the block norms are not run as kernels.  The
   // residual GEMMs leave the raw rows in bf16 (in the Xn buffer) and their sums of squares per
   // 128-column segment; the consuming GEMM scales its accumulator rows by the resulting
@@ -426,54 +427,50 @@ epd_status epd_encode(epd_handle h, const void* packed_patches, const int32_t* c
   const bool bf = c.dtype == EPD_BF16;
   hipStream_t st = (hipStream_t)stream;
 
-  // ---- per-call metadata -> pinned staging slot -> device
-  const int slot = h->next_slot;
-  if (h->slot_used[slot]) EPD_HIP(h, hipEventSynchronize(h->slot_done[slot]));
-  int32_t* m = (int32_t*)(h->staging + (size_t)slot * L.meta_bytes);
+  // ---- per-call metadata: segments longest first, so that the tail of the attention launch is made of
+  // short items; one work item per query tile.  Small tables travel with the plan kernel's arguments,
+  // larger ones through a slot of the pinned staging ring.
   const int S = num_segments, I = num_items;
-  int32_t* cu = m;
-  int32_t* pcu = cu + (S + 1);
-  int32_t* ioff = pcu + (S + 1);
-  int32_t* moff = ioff + (I + 1);
-  int32_t* grid = moff + (I + 1);
-  AttnWork* work = (AttnWork*)(grid + 3 * I);
-  std::memcpy(cu, cu_seqlens, (S + 1) * 4);
-  pcu[0] = 0;
-  for (int s = 0; s < S; ++s) pcu[s + 1] = (int32_t)align_up((size_t)pcu[s] + (cu[s + 1] - cu[s]), kVtAlign);
-  ioff[0] = moff[0] = 0;
-  for (int i = 0; i < I; ++i) {
-    int t = grid_thw[3 * i], hh = grid_thw[3 * i + 1], ww = grid_thw[3 * i + 2];
-    ioff[i + 1] = ioff[i] + t * hh * ww;
-    moff[i + 1] = moff[i] + t * (hh / c.merge) * (ww / c.merge);
-    grid[3 * i] = t; grid[3 * i + 1] = hh; grid[3 * i + 2] = ww;
-  }
-  // attention work list: one entry per query tile, longest segments first so that the tail
-  // of the launch is made of short items
   int max_len = 0;
-  for (int s = 0; s < S; ++s) max_len = std::max(max_len, cu[s + 1] - cu[s]);
+  for (int s = 0; s < S; ++s) max_len = std::max(max_len, cu_seqlens[s + 1] - cu_seqlens[s]);
   const int bq = attn_q_tile(bf, c.head_dim, max_len, h->attn_groups);
   if (bq <= 0) { h->err = "internal: no attention kernel for the forced query tile"; return EPD_ERR_UNSUPPORTED; }
-  std::vector<int> order(S);
-  for (int s = 0; s < S; ++s) order[s] = s;
-  std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return cu[a + 1] - cu[a] > cu[b + 1] - cu[b]; });
-  int nwork = 0;
-  for (int s : order) {
-    const int len = cu[s + 1] - cu[s];
-    for (int q0 = 0; q0 < len; q0 += bq) work[nwork++] = AttnWork{cu[s] + q0, cu[s], len, pcu[s]};
+  PlanArgs p{};
+  p.inline_tables = S <= kPlanInline && I <= kPlanInline;
+  const int slot = h->next_slot;
+  PlanSeg* seg = p.inl_seg;
+  PlanItem* item = p.inl_item;
+  if (!p.inline_tables) {
+    if (h->slot_used[slot]) EPD_HIP(h, hipEventSynchronize(h->slot_done[slot]));
+    seg = (PlanSeg*)(h->staging + (size_t)slot * L.meta_bytes);
+    item = (PlanItem*)(seg + S);
   }
+  double attn_flops = 0.0;
+  int32_t vcol0 = 0;
+  for (int s = 0; s < S; ++s) {
+    const int32_t len = cu_seqlens[s + 1] - cu_seqlens[s];
+    seg[s] = PlanSeg{cu_seqlens[s], len, vcol0, 0};
+    vcol0 += (int32_t)align_up((size_t)len, kVtAlign);
+    attn_flops += 4.0 * (double)len * len * c.hidden;
+  }
+  std::stable_sort(seg, seg + S, [](const PlanSeg& a, const PlanSeg& b) { return a.len > b.len; });
+  int nwork = 0;
+  for (int s = 0; s < S; ++s) { seg[s].work0 = nwork; nwork += (seg[s].len + bq - 1) / bq; }
   if (nwork > L.max_work) { h->err = "internal: attention work list overflow"; return EPD_ERR_SHAPE; }
-  const size_t meta_used = (size_t)((char*)(work + nwork) - (char*)m);
-  EPD_HIP(h, hipMemcpyAsync(h->ws + L.meta, m, meta_used, hipMemcpyHostToDevice, st));
-  EPD_HIP(h, hipEventRecord(h->slot_done[slot], st));
-  h->slot_used[slot] = true;
-  h->next_slot = (slot + 1) % kStagingSlots;
-
-  const int32_t* d_cu = h->at<int32_t>(L.meta);
-  const int32_t* d_pcu = d_cu + (S + 1);
-  const int32_t* d_ioff = d_pcu + (S + 1);
-  const int32_t* d_moff = d_ioff + (I + 1);
-  const int32_t* d_grid = d_moff + (I + 1);
-  const AttnWork* d_work = (const AttnWork*)(d_grid + 3 * I);
+  int32_t tok0 = 0, mrg0 = 0;
+  for (int i = 0; i < I; ++i) {
+    const int t = grid_thw[3 * i], hh = grid_thw[3 * i + 1], ww = grid_thw[3 * i + 2];
+    item[i] = PlanItem{tok0, mrg0, hh, ww};
+    tok0 += t * hh * ww;
+    mrg0 += t * (hh / c.merge) * (ww / c.merge);
+  }
+  if (!p.inline_tables) {
+    EPD_HIP(h, hipMemcpyAsync(h->ws + L.meta, seg, S * sizeof(PlanSeg) + I * sizeof(PlanItem), hipMemcpyHostToDevice, st));
+    EPD_HIP(h, hipEventRecord(h->slot_done[slot], st));
+    h->slot_used[slot] = true;
+    h->next_slot = (slot + 1) % kStagingSlots;
+  }
+  AttnWork* d_work = h->at<AttnWork>(L.work);
 
   const int D = c.hidden, F = c.mlp_dim;
   float* X = h->at<float>(L.x);
@@ -488,11 +485,10 @@ epd_status epd_encode(epd_handle h, const void* packed_patches, const int32_t* c
 
   {
     StepTimer tm(h, EPD_STEP_PLAN, 0.0, st);
-    PlanArgs p{};
-    p.T = T; p.Tm = Tm; p.num_items = I; p.num_segments = S;
-    p.item_tok_off = d_ioff; p.item_mrg_off = d_moff; p.grid_thw = d_grid; p.cu = d_cu; p.pcu = d_pcu;
+    p.T = T; p.Tm = Tm; p.num_items = I; p.num_segments = S; p.num_work = nwork; p.q_tile = bq;
+    p.seg = h->at<PlanSeg>(L.meta); p.item = (const PlanItem*)(p.seg + S);
     p.pair_freq = h->at<double>(L.pair_freq); p.pair_axis = h->at<int32_t>(L.pair_axis);
-    p.pairs = L.pairs; p.merge = c.merge; p.rot = rot; p.merge_idx = midx;
+    p.pairs = L.pairs; p.merge = c.merge; p.work = d_work; p.rot = rot; p.merge_idx = midx;
     p.vcol = bf ? vcol : nullptr; p.vt = bf ? Vt : nullptr; p.vt_stride = L.vt_stride; p.hidden = D;
     launch_plan(p, st);
   }
@@ -543,9 +539,7 @@ epd_status epd_encode(epd_handle h, const void* packed_patches, const int32_t* c
       a.qkv = QKV; a.ld_qkv = bf ? 2 * D : 3 * D; a.vt = Vt; a.vt_stride = L.vt_stride;
       a.out = O; a.ld_out = D; a.work = d_work; a.num_work = nwork;
       a.num_heads = c.num_heads; a.head_dim = c.head_dim; a.q_tile = bq; a.scale = (float)(1.0 / std::sqrt((double)c.head_dim));
-      double flops = 0.0;
-      for (int s = 0; s < S; ++s) { double n = cu[s + 1] - cu[s]; flops += 4.0 * n * n * D; }
-      StepTimer tm(h, EPD_STEP_ATTN, flops, st);
+      StepTimer tm(h, EPD_STEP_ATTN, attn_flops, st);
       bool ok = bf ? launch_attn_bf16(a, st) : launch_attn_f32(a, st);
       if (!ok) { h->err = "internal: no attention kernel"; return EPD_ERR_UNSUPPORTED; }
     }

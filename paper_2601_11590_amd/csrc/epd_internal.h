@@ -88,26 +88,34 @@ struct AttnArgs {
 };
 
 // ---------------------------------------------------------------- plan (per-call metadata)
+// What the plan kernel is told about a call.  Segments stand longest first, the order in which the
+// attention work list is laid out; items in batch order.
+struct PlanSeg { int32_t start, len, vcol, work0; };   // first token, tokens, first column in vt, first work item
+struct PlanItem { int32_t tok, mrg, h, w; };           // first token, first merged token, grid rows and columns
+constexpr int kPlanInline = 64;     // up to this many segments and items travel as kernel arguments
+
 struct PlanArgs {
-  int T, Tm, num_items, num_segments;
-  const int32_t* item_tok_off;  // device [items + 1]
-  const int32_t* item_mrg_off;  // device [items + 1]
-  const int32_t* grid_thw;      // device [items, 3]
-  const int32_t* cu;            // device [segments + 1]
-  const int32_t* pcu;           // device [segments + 1] padded segment starts in vt
+  int T, Tm, num_items, num_segments, num_work;
+  const PlanSeg* seg;           // device tables, read when one of them exceeds kPlanInline
+  const PlanItem* item;
   const double* pair_freq;      // device [pairs]
   const int32_t* pair_axis;     // device [pairs]
   int pairs;                    // 0 = no rotary
-  int merge;
+  int merge, q_tile;
+  AttnWork* work;               // out [num_work]
   float2* rot;                  // out [T, pairs]
   int32_t* merge_idx;           // out [Tm, merge*merge]
   int32_t* vcol;                // out [T] or nullptr
   void* vt;                     // bf16 [D, vt_stride]: pad columns are cleared, or nullptr
   int vt_stride, hidden;
+  int inline_tables;            // 1 = the tables below are used (set by the launcher)
+  int rot_blocks, work_blocks, merge_blocks, pad_blocks;   // set by the launcher
+  PlanSeg inl_seg[kPlanInline];
+  PlanItem inl_item[kPlanInline];
 };
 
 // launchers (each checks nothing: shapes are validated by the caller); all asynchronous
-void launch_plan(const PlanArgs& p, hipStream_t s);
+void launch_plan(PlanArgs& p, hipStream_t s);
 void launch_norm(const float* x, const void* gamma, const void* beta, void* out, int T, int D,
                  float eps, bool rms, bool bf16, hipStream_t s);
 void launch_gemm_f32(const GemmArgs& g, hipStream_t s);

@@ -10,78 +10,89 @@ namespace epd {
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
 
 // ------------------------------------------------------------------------------ plan
-__device__ __forceinline__ int upper_item(const int32_t* off, int n, int x) {
-  // largest i in [0, n) with off[i] <= x   (off[0] = 0, off increasing)
+template <typename E> __device__ __forceinline__ int last_not_after(const E* t, int n, int x, int32_t E::*key) {
+  // largest i in [0, n) with t[i].*key <= x   (keys increase, t[0].*key = 0)
   int lo = 0, hi = n;
   while (hi - lo > 1) {
-    int mid = (lo + hi) >> 1;
-    if (off[mid] <= x) lo = mid; else hi = mid;
+    const int mid = (lo + hi) >> 1;
+    if (t[mid].*key <= x) lo = mid; else hi = mid;
   }
   return lo;
 }
 
-// One thread per token: rotary table row and the token's column in the transposed V buffer.
-__global__ __launch_bounds__(256) void plan_tokens_kernel(PlanArgs p) {
-  int tok = blockIdx.x * blockDim.x + threadIdx.x;
-  if (tok >= p.T) return;
-  if (p.pairs > 0) {
-    int it = upper_item(p.item_tok_off, p.num_items, tok);
-    int local = tok - p.item_tok_off[it];
-    int h = p.grid_thw[it * 3 + 1], w = p.grid_thw[it * 3 + 2];
-    int coord[3];
-    coord[0] = local / (h * w);
-    int rem = local - coord[0] * h * w;
-    coord[1] = rem / w;
-    coord[2] = rem - coord[1] * w;
-    for (int q = 0; q < p.pairs; ++q) {
-      double ang = (double)coord[p.pair_axis[q]] * p.pair_freq[q];
-      double sn, cs;
-      sincos(ang, &sn, &cs);
-      p.rot[(size_t)tok * p.pairs + q] = make_float2((float)cs, (float)sn);
-    }
+// Everything a call derives from its metadata, in one launch; a block has one of four roles:
+//   rot    (cos, sin) of 256 (token, pair) entries, in double
+//   work   bf16: one entry of the attention work list and the vt columns of its tokens; fp32: 256
+//          entries (no vt)
+//   merge  the source tokens of 256 merged tokens, window rows then columns
+//   pad    clears the columns of vt between a segment's end and the next (aligned) start, four
+//          channel rows per block: attention multiplies them by exact zeros, so they must be finite
+// Up to kPlanInline segments and items the tables are kernel arguments, copied to LDS before they
+// are searched.  Bound: latency.  As a copy of the metadata (3 us) plus three kernels, one thread per
+// token for all its pairs (15 us), this step cost a call 24 us more: one 256-token image 3.9 us now.
+__global__ __launch_bounds__(256) void plan_kernel(PlanArgs p) {
+  __shared__ PlanItem items[kPlanInline];
+  __shared__ PlanSeg segs[kPlanInline];
+  const int tid = threadIdx.x;
+  const PlanItem* item = p.item;
+  const PlanSeg* seg = p.seg;
+  if (p.inline_tables) {
+    if (tid < p.num_items) items[tid] = p.inl_item[tid];
+    if (tid < p.num_segments) segs[tid] = p.inl_seg[tid];
+    __syncthreads();
+    item = items; seg = segs;
   }
-  if (p.vcol) {
-    int sg = upper_item(p.cu, p.num_segments, tok);
-    p.vcol[tok] = p.pcu[sg] + (tok - p.cu[sg]);
+  int b = blockIdx.x;
+  if (b < p.rot_blocks) {
+    const int e = b * 256 + tid, tok = e / p.pairs, q = e - tok * p.pairs;
+    if (tok >= p.T) return;
+    const PlanItem& d = item[last_not_after(item, p.num_items, tok, &PlanItem::tok)];
+    const int local = tok - d.tok, t = local / (d.h * d.w), rem = local - t * d.h * d.w, r = rem / d.w;
+    const int ax = p.pair_axis[q], coord = ax == 0 ? t : ax == 1 ? r : rem - r * d.w;
+    double sn, cs;
+    sincos((double)coord * p.pair_freq[q], &sn, &cs);
+    p.rot[e] = make_float2((float)cs, (float)sn);
+    return;
   }
-}
-
-// One thread per merged token: the merge*merge source tokens, window rows then columns.
-__global__ __launch_bounds__(256) void plan_merge_kernel(PlanArgs p) {
-  int mt = blockIdx.x * blockDim.x + threadIdx.x;
-  if (mt >= p.Tm) return;
-  int it = upper_item(p.item_mrg_off, p.num_items, mt);
-  int local = mt - p.item_mrg_off[it];
-  int m = p.merge;
-  int h = p.grid_thw[it * 3 + 1], w = p.grid_thw[it * 3 + 2];
-  int hm = h / m, wm = w / m;
-  int ti = local / (hm * wm);
-  int rem = local - ti * hm * wm;
-  int i = rem / wm, j = rem - i * wm;
-  int base = p.item_tok_off[it] + ti * h * w;
-  for (int di = 0; di < m; ++di)
-    for (int dj = 0; dj < m; ++dj)
-      p.merge_idx[(size_t)mt * m * m + di * m + dj] = base + (m * i + di) * w + m * j + dj;
-}
-
-// Clear the columns of the transposed V buffer between a segment's end and the next
-// segment's (aligned) start: attention multiplies them by exact zeros, so they must be finite.
-__global__ __launch_bounds__(128) void plan_clear_vt_pad_kernel(PlanArgs p) {
-  int sg = blockIdx.x;
-  int row = blockIdx.y;
-  int len = p.cu[sg + 1] - p.cu[sg];
-  int c0 = p.pcu[sg] + len, c1 = p.pcu[sg + 1];
+  b -= p.rot_blocks;
+  if (b < p.work_blocks) {
+    const int i = p.vcol ? b : b * 256 + tid;
+    if (i >= p.num_work) return;
+    const PlanSeg& s = seg[last_not_after(seg, p.num_segments, i, &PlanSeg::work0)];
+    const int q0 = (i - s.work0) * p.q_tile;
+    if (!p.vcol || tid == 0) p.work[i] = AttnWork{s.start + q0, s.start, s.len, s.vcol};
+    if (p.vcol)
+      for (int t = q0 + tid; t < min(q0 + p.q_tile, s.len); t += 256) p.vcol[s.start + t] = s.vcol + t;
+    return;
+  }
+  b -= p.work_blocks;
+  if (b < p.merge_blocks) {
+    const int mt = b * 256 + tid;
+    if (mt >= p.Tm) return;
+    const PlanItem& d = item[last_not_after(item, p.num_items, mt, &PlanItem::mrg)];
+    const int m = p.merge, hm = d.h / m, wm = d.w / m, local = mt - d.mrg;
+    const int ti = local / (hm * wm), rem = local - ti * hm * wm, i = rem / wm, j = rem - i * wm;
+    const int base = d.tok + ti * d.h * d.w;
+    for (int di = 0; di < m; ++di)
+      for (int dj = 0; dj < m; ++dj)
+        p.merge_idx[(size_t)mt * m * m + di * m + dj] = base + (m * i + di) * d.w + m * j + dj;
+    return;
+  }
+  b -= p.merge_blocks;
+  const int rows = (p.hidden + 3) / 4, sg = b / rows, row = (b - sg * rows) * 4 + (tid >> 6);
+  if (row >= p.hidden) return;
+  const PlanSeg& s = seg[sg];
   uint16_t* vt = (uint16_t*)p.vt + (size_t)row * p.vt_stride;
-  for (int c = c0 + threadIdx.x; c < c1; c += blockDim.x) vt[c] = 0;
+  const int end = s.vcol + (s.len + kVtAlign - 1) / kVtAlign * kVtAlign;
+  for (int c = s.vcol + s.len + (tid & 63); c < end; c += 64) vt[c] = 0;
 }
 
-void launch_plan(const PlanArgs& p, hipStream_t s) {
-  if (p.T > 0 && (p.pairs > 0 || p.vcol))
-    hipLaunchKernelGGL(plan_tokens_kernel, dim3((p.T + 255) / 256), dim3(256), 0, s, p);
-  if (p.Tm > 0 && p.merge > 1)
-    hipLaunchKernelGGL(plan_merge_kernel, dim3((p.Tm + 255) / 256), dim3(256), 0, s, p);
-  if (p.vt && p.num_segments > 0)
-    hipLaunchKernelGGL(plan_clear_vt_pad_kernel, dim3(p.num_segments, p.hidden), dim3(128), 0, s, p);
+void launch_plan(PlanArgs& p, hipStream_t s) {
+  p.rot_blocks = p.pairs > 0 ? (int)(((long)p.T * p.pairs + 255) / 256) : 0;
+  p.work_blocks = p.vcol ? p.num_work : (p.num_work + 255) / 256;
+  p.merge_blocks = p.merge > 1 ? (p.Tm + 255) / 256 : 0;
+  p.pad_blocks = p.vt ? p.num_segments * ((p.hidden + 3) / 4) : 0;
+  hipLaunchKernelGGL(plan_kernel, dim3(p.rot_blocks + p.work_blocks + p.merge_blocks + p.pad_blocks), dim3(256), 0, s, p);
 }
 
 // ------------------------------------------------------------------------------ norm
