@@ -531,7 +531,7 @@ static int bf16_q_rows(int head_dim, int max_seg_len) {
 int attn_q_tile(bool bf16, int head_dim, int max_seg_len, int groups) {
   if (!bf16) {
     switch (head_dim) {
-      case 8: case 16: case 32: case 64: case 72: case 80: case 96: case 128: return 64;
+      case 8: case 16: case 32: case 64: case 72: case 80: case 96: case 128: return 16;
       default: return 0;
     }
   }
