@@ -47,7 +47,7 @@ struct Layout {
   std::vector<LayerW> layers;
   size_t x, xn, qkv, vt, o, hd, rot, merge_idx, vcol, pair_freq, pair_axis, zeros, meta, work, stats;
   bool fold_rms;     // RMSNorm of the blocks folded into the GEMMs around it (bf16 path)
-  int stats_n;       // 128-column segments per residual row
+  int stats_n;       // sums of squares held per residual row: one per 64 columns
   size_t meta_bytes, total;
 };
 
@@ -117,10 +117,10 @@ Layout make_layout(const epd_encode_cfg& c) {
   L.work = take((size_t)L.max_work * sizeof(AttnWork));
   // bf16 + RMSNorm + hidden a multiple of 128: the block norms are not run as kernels.  The
   // residual GEMMs leave the raw rows in bf16 (in the Xn buffer) and their sums of squares per
-  // 128-column segment; the consuming GEMM scales its accumulator rows by the resulting
+  // segment of 128 columns (64 from the smallest tile); the consuming GEMM scales its accumulator rows by the resulting
   // 1/rms, gamma being folded into its weights at create.
   L.fold_rms = bf && c.norm == EPD_RMSNORM && c.hidden % 128 == 0 && c.num_layers > 0;
-  L.stats_n = c.hidden / 128;
+  L.stats_n = c.hidden / 64;
   L.stats = take(T * (size_t)std::max(L.stats_n, 1) * 4, L.fold_rms);
   // The bf16 GEMMs fetch whole operand tiles (up to 320 rows) without clamping rows at the edge of a
   // matrix (what lies beyond only feeds accumulators that are never stored); this tail keeps
@@ -514,11 +514,14 @@ epd_status epd_encode(epd_handle h, const void* packed_patches, const int32_t* c
     gemm(EPD_STEP_PATCH_EMBED, g);
   }
   float* stats = L.fold_rms ? h->at<float>(L.stats) : nullptr;
+  int stats_n = 0;                            // sums per row that the last producer left
   auto consume_stats = [&](GemmArgs& g) {   // A = raw bf16 rows, scale 1/rms applied in the epilogue
-    g.stats_in = stats; g.stats_n = L.stats_n; g.stats_inv_dim = 1.0f / (float)D; g.stats_eps = c.norm_eps;
+    g.stats_in = stats; g.stats_n = stats_n; g.stats_inv_dim = 1.0f / (float)D; g.stats_eps = c.norm_eps;
   };
   auto produce_stats = [&](GemmArgs& g) {   // residual GEMM also leaves bf16 rows + sums of squares
-    g.xb = Xn; g.ldxb = D; g.stats_out = stats; g.stats_n = L.stats_n;
+    g.xb = Xn; g.ldxb = D; g.stats_out = stats;
+    g.tile_cfg = h->tile_cfg; g.compute_units = h->compute_units;
+    g.stats_n = stats_n = D / gemm_bf16_stat_cols(g);
   };
   for (int l = 0; l < c.num_layers; ++l) {
     const LayerW& w = L.layers[l];

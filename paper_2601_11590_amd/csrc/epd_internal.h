@@ -51,7 +51,7 @@ struct GemmArgs {
                         //   without per-lane row clamping
   // bf16 path, RMSNorm folded into the GEMMs around it (see launch_fold_gamma):
   //   producer (EPI_RESIDUAL): also store the updated residual rows as bf16 to xb and the sum
-  //   of their squares per 128-column segment to stats_out[m][n / 128]
+  //   of their squares per segment of c columns to stats_out[m][n / c], c = gemm_bf16_stat_cols(g)
   void* xb;             // bf16 [M, ldxb] or nullptr
   int ldxb;
   float* stats_out;     // [M, stats_n] or nullptr (requires N % 128 == 0)
@@ -126,6 +126,7 @@ void launch_gemm_bf16(const GemmArgs& g, hipStream_t s);
 // covers when the rest is left to a second launch of 128 x 128 tiles (0 = one launch covers all).
 // Reads M, N, epilogue, qk_cols, gather and tile_cfg of g.
 void plan_gemm_bf16(const GemmArgs& g, int compute_units, int* tile_rows, int* tile_cols, int* body_rows);
+int gemm_bf16_stat_cols(const GemmArgs& g);   // columns per sum of squares that the EPI_RESIDUAL launch of g leaves (64 or 128)
 bool launch_attn_bf16(const AttnArgs& a, hipStream_t s);  // false: head_dim not covered
 // query rows per work item for segments up to max_seg_len (0 = unsupported head_dim);
 // never smaller than attn_q_tile(bf16, head_dim, 1).  groups: 0 = the library's choice; 1 or 2 =

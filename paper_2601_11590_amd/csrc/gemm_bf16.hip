@@ -5,7 +5,7 @@
 // accumulate; at equal flops this shape draws less power than the 32x32x16 one, and under the
 // chip's power limit that is clock: +7 % on the large GEMMs with random operands, nothing on
 // all-zero ones), operand tiles brought from global memory straight into LDS
-// (global_load_lds_dwordx4, no register staging) in a two-stage ring.
+// (global_load_lds_dwordx4, no register staging) in a ring of two to four stages.
 //
 // Tile scheme.  A block of WAVES_M x WAVES_N waves owns a BM x BN output tile; K advances in
 // steps of BK.  Both operands are K-contiguous in memory ("NT" form), so one lane's MFMA
@@ -13,7 +13,7 @@
 // the 64 lanes' 16-byte chunks to consecutive LDS addresses, so rows cannot be padded;
 // instead the chunk a lane fetches is chosen so that chunk c of row r lands in slot
 // c ^ swz(r) of that row, which spreads the 16 rows read by one MFMA operand fetch over all
-// bank groups.  Stage s+1 is in flight while stage s is multiplied; one barrier per K step.
+// bank groups.  The next stages are in flight while stage s is multiplied; one barrier per K step.
 //
 // Accumulator orientation.  For a 16x16 MFMA result lane l holds column (l % 16) and rows
 // 4*(l/16) + v, v = 0..3.  By default the W fragment is fed as the first operand, so "rows"
@@ -100,8 +100,8 @@ template <int OFF> __device__ __forceinline__ void ds_read_b128(bf16x8& d, uint3
 }
 template <int N, int STRIDE, int BASE, int I = 0> __device__ __forceinline__ void ds_read_rows(bf16x8* d, uint32_t addr) {
   if constexpr (I < N) {
-    static_assert(BASE + I * STRIDE < 65536, "LDS offset field");
-    ds_read_b128<BASE + I * STRIDE>(d[I], addr);
+    constexpr int off = BASE + I * STRIDE, hi = off & ~0xffff;   // the offset field holds 16 bits
+    ds_read_b128<off - hi>(d[I], addr + (uint32_t)hi);
     ds_read_rows<N, STRIDE, BASE, I + 1>(d, addr);
   }
 }
@@ -130,23 +130,25 @@ template <int N, class F> __device__ __forceinline__ void static_for(F&& f) {
 }
 
 // Compile-time description of one kernel variant.
-template <int BM_, int BN_, int BK_, int WAVES_M_, int WAVES_N_, int MINBLK_, int PARTS_>
+template <int BM_, int BN_, int BK_, int WAVES_M_, int WAVES_N_, int MINBLK_, int PARTS_, int STAGES_, bool SPREAD_ = false>
 struct Tile {
   static constexpr int BM = BM_, BN = BN_, BK = BK_, WAVES_M = WAVES_M_, WAVES_N = WAVES_N_;
-  static constexpr int MINBLK = MINBLK_;
+  static constexpr int MINBLK = MINBLK_, STAGES = STAGES_;
+  static constexpr bool SPREAD = SPREAD_;                // loads of a stage spread over the MFMAs of a step
   static constexpr int NT = 64 * WAVES_M * WAVES_N;
   static constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N, TM = WM / 32, TN = WN / 32;
   static constexpr int TM16 = WM / 16, TN16 = WN / 16;   // 16 x 16 MFMA blocks per wave tile
   static constexpr int PARTS = PARTS_;                   // parts the A blocks of a k step are multiplied in
+  static constexpr int STAT_COLS = BN < 128 ? BN : 128;  // columns per sum of squares that the residual epilogue leaves
   static constexpr int CPR = BK / 8;                     // 16-byte chunks per tile row
   static constexpr int LA = BM * CPR / NT, LW = BN * CPR / NT;   // load instructions per thread and stage
   static constexpr int STAGE_BYTES = (BM + BN) * BK * 2;
   // fp32 epilogue staging (residual add, fp32 outputs): the tile's columns in 2 passes, or 4
   // where two would not fit LDS
-  static constexpr int EPI_PASSES = BM * (BN / 2 * 4 + 16) <= 136 * 1024 ? 2 : 4;
+  static constexpr int EPI_PASSES = BN == 64 ? 1 : BM * (BN / 2 * 4 + 16) <= 136 * 1024 ? 2 : 4;
   static constexpr int EPI_BYTES_A = BM * (BN / EPI_PASSES * 4 + 16), EPI_BYTES_V = (BN / EPI_PASSES) * (BM * 4 + 16);
-  static constexpr int LDS_BYTES = (2 * STAGE_BYTES > EPI_BYTES_A ? 2 * STAGE_BYTES : EPI_BYTES_A) > EPI_BYTES_V
-                                       ? (2 * STAGE_BYTES > EPI_BYTES_A ? 2 * STAGE_BYTES : EPI_BYTES_A) : EPI_BYTES_V;
+  static constexpr int RING = STAGES * STAGE_BYTES;
+  static constexpr int LDS_BYTES = (RING > EPI_BYTES_A ? RING : EPI_BYTES_A) > EPI_BYTES_V ? (RING > EPI_BYTES_A ? RING : EPI_BYTES_A) : EPI_BYTES_V;
   static_assert(BK == 64, "BK: the main loop is written for two MFMA k steps of 32 per stage");
   static_assert((BM * CPR) % NT == 0 && (BN * CPR) % NT == 0, "tile / thread mismatch");
   static_assert(WM % 32 == 0 && WN % 32 == 0, "wave tile");
@@ -161,6 +163,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int m0, const
   constexpr int CPR = T::CPR, LA = T::LA, LW = T::LW;
   constexpr int ROWB = BK * 2;               // bytes per tile row
   constexpr int A_BYTES = BM * ROWB, W_BYTES = BN * ROWB;
+  constexpr int S = T::STAGES, GL = LA + LW;   // ring stages; loads per thread and stage
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -204,50 +207,66 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int m0, const
     return ((c % CPR) ^ T::swz(row)) * 8;
   };
 
+  // GATHER with pieces of whole K steps: a piece is the same for all lanes of a step, and the
+  // rows it comes from are fetched when a new piece begins -- per step, the wait for them would
+  // empty the ring of loads in flight every time
+  // (small tiles: the large ones have no registers to spare for them)
+  const bool whole_pieces = GATHER && LA <= 2 && kcw % BK == 0;
+  [[maybe_unused]] int cur_piece = -1;
+  [[maybe_unused]] int cur_src[LA];
+
   // TAIL = the K step that may run past K (only the last one, only when K % BK != 0):
   // chunks at k >= K are fetched from a zero buffer instead.
-  // LDS: [A stage 0 | A stage 1 | W stage 0 | W stage 1]
-  auto issue = [&](auto TAIL, int stage, int k0) {
+  // LDS: [A stage 0 | A stage 1 | ... | W stage 0 | W stage 1 | ...]
+  //   Loads FROM .. TO - 1 of the LA + LW that bring K step k0 / BK into a stage.
+  auto issue = [&](auto TAIL, auto FROM, auto TO, int stage, int k0) {
     constexpr bool tail = decltype(TAIL)::value;
+    constexpr int from = decltype(FROM)::value, to = decltype(TO)::value;
     char* const sa = lds + stage * A_BYTES;
-    char* const sw = lds + 2 * A_BYTES + stage * W_BYTES;
+    char* const sw = lds + S * A_BYTES + stage * W_BYTES;
     const char* ab = a_base_ptr + (size_t)k0 * 2;
     const char* wb = w_base_ptr + (size_t)k0 * 2;
+    if constexpr (GATHER && from == 0) {
+      if (whole_pieces && k0 / kcw != cur_piece) {
+        cur_piece = k0 / kcw;
+#pragma unroll
+        for (int it = 0; it < LA; ++it)
+          cur_src[it] = g.gather[(size_t)(m0 + min((it * NT + tid) / CPR, g.M - 1 - m0)) * g.gather_n + cur_piece];
+      }
+    }
     // The per-lane offsets pass through an opaque copy here, so that their widening to 64 bits
     // stays next to the load: "scalar base + 32-bit lane offset" is then the load's own
     // addressing form.  Widened once ahead of the loop, every offset would occupy a register
     // pair for the whole loop and every load would need a 64-bit vector add in front of it.
     // (one copy per load: a shared one would let the adds be re-associated into a running
     // 64-bit vector address again)
-    uint32_t ao[LA], wo[LW];
 #pragma unroll
-    for (int it = 0; it < LA; ++it) { ao[it] = a_off[FAST ? 0 : it]; asm volatile("" : "+v"(ao[it])); }
-#pragma unroll
-    for (int it = 0; it < LW; ++it) { wo[it] = w_off[FAST ? 0 : it]; asm volatile("" : "+v"(wo[it])); }
-#pragma unroll
-    for (int it = 0; it < LA; ++it) {
+    for (int ld = from; ld < to; ++ld) {
+      const bool is_a = ld < LA;
+      const int it = is_a ? ld : ld - LA;
+      uint32_t off = is_a ? a_off[FAST ? 0 : it] : w_off[FAST ? 0 : it];
+      asm volatile("" : "+v"(off));
       const char* p;
-      if constexpr (GATHER) {
-        const int k = k0 + chunk_k(it);
-        const int piece = min(k / kcw, g.gather_n - 1);
-        const int row = min((it * NT + tid) / CPR, g.M - 1 - m0);
-        const int src = g.gather[(size_t)(m0 + row) * g.gather_n + piece];
-        p = (const char*)g.A + ((size_t)src * g.lda + (k - piece * kcw)) * 2;
-      } else if constexpr (FAST) {
-        p = (ab + (size_t)(it * RPP) * (size_t)g.lda * 2) + (size_t)ao[it];
+      if (is_a) {
+        if constexpr (GATHER) {
+          const int k = k0 + chunk_k(it);
+          int piece = cur_piece, src = cur_src[it];
+          if (!whole_pieces) {
+            piece = min(k / kcw, g.gather_n - 1);
+            src = g.gather[(size_t)(m0 + min((it * NT + tid) / CPR, g.M - 1 - m0)) * g.gather_n + piece];
+          }
+          p = (const char*)g.A + ((size_t)src * g.lda + (k - piece * kcw)) * 2;
+        } else if constexpr (FAST) {
+          p = (ab + (size_t)(it * RPP) * (size_t)g.lda * 2) + (size_t)off;
+        } else {
+          p = ab + (size_t)off;
+        }
       } else {
-        p = ab + (size_t)ao[it];
+        if constexpr (FAST) p = (wb + (size_t)(it * RPP) * (size_t)ldw * 2) + (size_t)off;
+        else p = wb + (size_t)off;
       }
       if constexpr (tail) { if (k0 + chunk_k(it) >= g.K) p = zeros; }
-      __builtin_amdgcn_global_load_lds(EPD_GPTR(p), EPD_LPTR(sa + (it * NT + wave * 64) * 16), 16, 0, 0);
-    }
-#pragma unroll
-    for (int it = 0; it < LW; ++it) {
-      const char* p;
-      if constexpr (FAST) p = (wb + (size_t)(it * RPP) * (size_t)ldw * 2) + (size_t)wo[it];
-      else p = wb + (size_t)wo[it];
-      if constexpr (tail) { if (k0 + chunk_k(it) >= g.K) p = zeros; }
-      __builtin_amdgcn_global_load_lds(EPD_GPTR(p), EPD_LPTR(sw + (it * NT + wave * 64) * 16), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds(EPD_GPTR(p), EPD_LPTR((is_a ? sa : sw) + (it * NT + wave * 64) * 16), 16, 0, 0);
     }
   };
   // Folded RMSNorm (consumer side): scale of row m = rsqrt(mean of squares + eps), from the
@@ -256,15 +275,19 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int m0, const
   // barriers of the main loop make it visible to the epilogue).
   float* const row_scale = (float*)(lds + T::LDS_BYTES + lds_extra<T, EPI>());
   const bool scaled = g.stats_in != nullptr;
-  // eight segments (hidden 1024): the loads are issued here, ahead of the first operand
-  // loads, and only consumed after the first barrier
+  // 8 or (small tiles only, which leave 64-column sums) 16 segments (hidden 1024): the loads are
+  // issued here, ahead of the first operand loads, and only consumed after the first barrier
   static_assert(BM <= NT, "one row scale per thread");
-  const bool scaled8 = scaled && g.stats_n == 8;
-  float4 st_a = make_float4(0.f, 0.f, 0.f, 0.f), st_b = st_a;
-  if (scaled8) {
+  constexpr int SV = BM * BN <= 128 * 128 ? 4 : 2;       // 16-byte loads held
+  const bool scaled_v = scaled && (g.stats_n == 8 || g.stats_n == 4 * SV);
+  float4 st[SV];
+  if (scaled_v) {
+#pragma unroll
+    for (int j = 0; j < SV; ++j) st[j] = make_float4(0.f, 0.f, 0.f, 0.f);
     if (tid < BM) {
-      const float4* sp = (const float4*)(g.stats_in + (size_t)min(m0 + tid, g.M - 1) * 8);
-      st_a = sp[0]; st_b = sp[1];
+      const float4* sp = (const float4*)(g.stats_in + (size_t)min(m0 + tid, g.M - 1) * g.stats_n);
+      st[0] = sp[0]; st[1] = sp[1];
+      if constexpr (SV == 4) { if (g.stats_n == 16) { st[2] = sp[2]; st[3] = sp[3]; } }
     }
   } else if (scaled) {
     for (int r = tid; r < BM; r += NT) {
@@ -294,12 +317,14 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int m0, const
 
   const int nk = (g.K + BK - 1) / BK;
   const bool ragged_k = (g.K % BK) != 0;
+  using ALL0 = std::integral_constant<int, 0>;
+  using ALLN = std::integral_constant<int, GL>;
   auto issue_step = [&](int stage, int kt) {      // kt < nk
     if constexpr (FAST) {
-      issue(std::false_type{}, stage, kt * BK);
+      issue(std::false_type{}, ALL0{}, ALLN{}, stage, kt * BK);
     } else {
-      if (ragged_k && kt == nk - 1) issue(std::true_type{}, stage, kt * BK);
-      else issue(std::false_type{}, stage, kt * BK);
+      if (ragged_k && kt == nk - 1) issue(std::true_type{}, ALL0{}, ALLN{}, stage, kt * BK);
+      else issue(std::false_type{}, ALL0{}, ALLN{}, stage, kt * BK);
     }
   };
 
@@ -326,12 +351,11 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int m0, const
   // fragments.  W fragments alternate between two buffers by k step, A fragments by slice.
   constexpr int TM16 = T::TM16, TN16 = T::TN16, P = T::PARTS, AP = TM16 / P, NSL = 2 * P;
   static_assert(TM16 % P == 0 && TN16 + AP <= 15, "slices / LDS counter");
-  constexpr bool LATE_REFILL = TM * TN <= 4;
   const uint32_t lds0 = (uint32_t)(size_t)EPD_LPTR(lds);
   // Address of k step 1 = address of k step 0 with bit 6 flipped (chunk slot bit 2; the row
   // base has a zero there); stage and 16-row block go into the instruction's offset field.
   const uint32_t a_rd0 = lds0 + (wm * WM + l16) * ROWB + ((g4 ^ T::swz(l16)) * 16);
-  const uint32_t w_rd0 = lds0 + 2 * A_BYTES + (wn * WN + l16) * ROWB + ((g4 ^ T::swz(l16)) * 16);
+  const uint32_t w_rd0 = lds0 + S * A_BYTES + (wn * WN + l16) * ROWB + ((g4 ^ T::swz(l16)) * 16);
   bf16x8 fw[2][TN16], fa[2][AP];
   auto read_slice = [&](auto SL, auto ST) {
     constexpr int sl = decltype(SL)::value, st = decltype(ST)::value, ks = sl / P, p = sl % P;
@@ -345,31 +369,35 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int m0, const
     constexpr int next_reads = ((sl + 1) % P == 0 ? TN16 : 0) + AP;
     wait_lds_reads<(decltype(DRAIN)::value ? 0 : next_reads), AP, (p == 0 ? TN16 : 0)>(&fa[sl & 1][0], &fw[ks][0]);
   };
-  auto mfmas = [&](auto SL) {
+  // Multiply slice SL.  Meanwhile (REFILL) its share of the loads that refill the stage before
+  // this one is issued, one load after every few matrix instructions: a wave issues in order and
+  // the address unit takes a 1 KB load every 18 cycles or so, so a whole stage's loads in one run
+  // leave the matrix cores idle for as long as they take.
+  constexpr int MPS = AP * TN16;                        // matrix instructions per slice
+  constexpr bool LATE_REFILL = TM * TN <= 4;
+  constexpr int LSL = S == 2 && NSL > 4 ? NSL / 2 : NSL - 1;    // slices that issue loads (never the last one)
+  auto mfmas = [&](auto SL, auto REFILL, int stage, int k0) {
     constexpr int sl = decltype(SL)::value, ks = sl / P, p = sl % P;
-    // consecutive MFMAs keep their first operand: measured ~7% faster than alternating it
-    if constexpr (VMODE) {
-#pragma unroll
-      for (int t = 0; t < AP; ++t)
-#pragma unroll
-        for (int w = 0; w < TN16; ++w) {
-          const int a16 = p * AP + t;
-          acc[a16 >> 1][w >> 1][(a16 & 1) * 2 + (w & 1)] =
-              __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[sl & 1][t], fw[ks][w], acc[a16 >> 1][w >> 1][(a16 & 1) * 2 + (w & 1)], 0, 0, 0);
+    constexpr int l0 = sl < LSL ? GL * sl / LSL : GL, l1 = sl < LSL ? GL * (sl + 1) / LSL : GL, nl = l1 - l0;
+    static_for<MPS>([&](auto I) {
+      constexpr int i = decltype(I)::value;
+      // consecutive MFMAs keep their first operand: measured ~7% faster than alternating it
+      constexpr int t = VMODE ? i / TN16 : i % AP, w = VMODE ? i % TN16 : i / AP;
+      constexpr int a16 = p * AP + t;
+      f32x4& c = acc[a16 >> 1][w >> 1][(a16 & 1) * 2 + (w & 1)];
+      if constexpr (VMODE) c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[sl & 1][t], fw[ks][w], c, 0, 0, 0);
+      else c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[ks][w], fa[sl & 1][t], c, 0, 0, 0);
+      if constexpr (decltype(REFILL)::value && nl > 0) {
+        constexpr int b0 = l0 + nl * i / MPS, b1 = l0 + nl * (i + 1) / MPS;
+        if constexpr (b1 > b0) {
+          __builtin_amdgcn_sched_barrier(0);
+          issue(std::false_type{}, std::integral_constant<int, b0>{}, std::integral_constant<int, b1>{}, stage, k0);
+          __builtin_amdgcn_sched_barrier(0);
         }
-    } else {
-#pragma unroll
-      for (int w = 0; w < TN16; ++w)
-#pragma unroll
-        for (int t = 0; t < AP; ++t) {
-          const int a16 = p * AP + t;
-          acc[a16 >> 1][w >> 1][(a16 & 1) * 2 + (w & 1)] =
-              __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[ks][w], fa[sl & 1][t], acc[a16 >> 1][w >> 1][(a16 & 1) * 2 + (w & 1)], 0, 0, 0);
-        }
-    }
+      }
+    });
   };
   using I0 = std::integral_constant<int, 0>;
-  using I1 = std::integral_constant<int, 1>;
   using LAST = std::integral_constant<int, NSL - 1>;
 
   // Residual rows this thread updates in the epilogue (EPI_RESIDUAL, where its whole share is
@@ -392,57 +420,76 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int m0, const
     }
   };
 
-  // ---- main loop: two LDS stages.  The hand-over to the next stage happens before the last
-  // slice of the current stage is multiplied: wait for the own loads of stage s^1, barrier
-  // (everybody's loads landed, everybody finished reading stage s), refill stage s with K step
-  // kt+2, start reading stage s^1 -- and only then issue the MFMAs of the last slice, which
-  // cover the barrier and the LDS latency.  Every load has one full K step to land.
+  // ---- main loop: a ring of S LDS stages.  The hand-over to the next stage happens before the
+  // last slice of the current stage is multiplied: wait for the own loads of the next stage
+  // (those of up to S - 2 later ones stay in flight), barrier (everybody's loads landed,
+  // everybody finished reading this stage), start reading the next one -- and only then issue the
+  // MFMAs of the last slice, which cover the barrier and the LDS latency.  The freed stage is
+  // refilled at once, or (SPREAD tiles) between the MFMAs of the next step.
+  auto wait_later = [&](int later) {      // loads of at most min(later, S - 2) stages stay in flight
+    if constexpr (S >= 4) { if (later >= 2) { wait_vmcnt<2 * GL>(); return; } }
+    if constexpr (S >= 3) { if (later == 1 || (S == 3 && later > 1)) { wait_vmcnt<GL>(); return; } }
+    wait_vmcnt<0>();
+  };
+  static_assert(S >= 2 && S <= 4, "ring");
   issue_step(0, 0);
-  wait_vmcnt<0>();
+  if constexpr (S >= 3) { if (nk > 1) issue_step(1, 1); }
+  if constexpr (S >= 4) { if (nk > 2) issue_step(2, 2); }
+  wait_later(nk - 1);
   __builtin_amdgcn_s_barrier();
-  if (scaled8 && tid < BM) {
-    const float ss = ((st_a.x + st_a.y) + (st_a.z + st_a.w)) + ((st_b.x + st_b.y) + (st_b.z + st_b.w));
+  if (scaled_v && tid < BM) {
+    float ss = ((st[0].x + st[0].y) + (st[0].z + st[0].w)) + ((st[1].x + st[1].y) + (st[1].z + st[1].w));
+    if constexpr (SV == 4) ss += ((st[2].x + st[2].y) + (st[2].z + st[2].w)) + ((st[3].x + st[3].y) + (st[3].z + st[3].w));
     row_scale[tid] = 1.0f / sqrtf(fmaf(ss, g.stats_inv_dim, g.stats_eps));
   }
-  if (nk > 1) issue_step(1, 1);
+  constexpr bool INNER_LOOP = FAST && T::SPREAD;
+  if (!INNER_LOOP && nk > S - 1) issue_step(S - 1, S - 1);
   read_slice(I0{}, I0{});
 
-  auto step = [&](auto S, int kt) {
-    constexpr int s = decltype(S)::value;
-    using SN = std::integral_constant<int, s ^ 1>;
+  auto step = [&](auto ST, auto INNER, int kt) {
+    constexpr int s = decltype(ST)::value, sp = (s + S - 1) % S;    // sp: the stage to refill, with K step kt + S - 1
+    constexpr bool inner = decltype(INNER)::value;                  // a full ring of steps and loads follows
+    using SN = std::integral_constant<int, (s + 1) % S>;
+    const int k0 = (kt + S - 1) * BK;
     // the fragments of slice sl+1 are requested before slice sl is multiplied
     static_for<NSL - 1>([&](auto SL) {
-      read_slice(std::integral_constant<int, decltype(SL)::value + 1>{}, S);
+      read_slice(std::integral_constant<int, decltype(SL)::value + 1>{}, ST);
       wait_slice(SL, std::false_type{});
-      mfmas(SL);
+      mfmas(SL, INNER, sp, k0);
     });
     // last slice: stage hand-over first
-    if (kt + 1 < nk) {
-      wait_vmcnt<0>();
+    if (inner || kt + 1 < nk) {
+      if constexpr (inner) wait_vmcnt<(S - 2) * GL>();
+      else wait_later(nk - 2 - kt);
       wait_slice(LAST{}, std::true_type{});
       __builtin_amdgcn_s_barrier();
-      if constexpr (!LATE_REFILL) {
-        if (kt + 2 < nk) issue_step(s, kt + 2);
-      }
+      if constexpr (!inner && !LATE_REFILL) { if (kt + S < nk) issue_step(s, kt + S); }
       read_slice(I0{}, SN{});
-      if (kt + 2 >= nk) prefetch_resid();          // last hand-over: no operand load follows
+      if constexpr (!inner) { if (kt + 2 >= nk) prefetch_resid(); }          // last hand-over: no operand load follows
     } else {
       wait_slice(LAST{}, std::true_type{});
     }
-    mfmas(LAST{});
-    if constexpr (LATE_REFILL) {
+    mfmas(LAST{}, std::false_type{}, 0, 0);
+    if constexpr (!inner && LATE_REFILL) {
       // small wave tiles: the refill of stage s is issued behind the queued MFMAs, so the
       // address arithmetic and load instructions run in their shadow (pinning this order
       // costs registers, which the large wave tiles do not have)
       __builtin_amdgcn_sched_barrier(0);
-      if (kt + 2 < nk) issue_step(s, kt + 2);
+      if (kt + S < nk) issue_step(s, kt + S);
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-  for (int kt = 0; kt < nk; kt += 2) {
-    step(I0{}, kt);
-    if (kt + 1 < nk) step(I1{}, kt + 1);
+  int kt = 0;
+  if constexpr (INNER_LOOP) {        // no branches while every step refills a stage
+    constexpr int AHEAD = S == 2 ? 3 : 2 * S - 2;      // the last hand-over stays with the loop below
+    for (; kt + AHEAD < nk; kt += S)
+      static_for<S>([&](auto ST) { step(ST, std::true_type{}, kt + decltype(ST)::value); });
   }
+  if (INNER_LOOP && kt + S - 1 < nk) issue_step(S - 1, kt + S - 1);
+  for (; kt < nk; kt += S)
+    static_for<S>([&](auto ST) {
+      if (kt + decltype(ST)::value < nk) step(ST, std::false_type{}, kt + decltype(ST)::value);
+    });
   if (nk == 1) prefetch_resid();
 
   // ------------------------------------------------------------------ epilogue
@@ -662,7 +709,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int m0, const
     constexpr int LPR4 = HALF / 4, RPS = NT / LPR4;    // lanes per row (4 columns each), rows per sweep
     static_assert(BM % RPS == 0, "sweeps");
     const int cl = (tid % LPR4) * 4;                   // first of the lane's 4 columns inside the half
-    static_assert(HALF == 64 || HALF == 128, "sum-of-squares segments are 128 columns");
+    static_assert(HALF == T::STAT_COLS || 2 * HALF == T::STAT_COLS, "sum-of-squares segments");
     [[maybe_unused]] float seg_ss[BM / RPS];
 #pragma unroll
     for (int h = 0; h < NPASS; ++h) {
@@ -715,8 +762,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int m0, const
           if (g.xb) *(uint2*)((uint16_t*)g.xb + (size_t)m * g.ldxb + n) = pack_bf16x4(x.x, x.y, x.z, x.w);
           if (g.stats_out) {
             const float ss = group_sum<LPR4>(fmaf(x.x, x.x, fmaf(x.y, x.y, fmaf(x.z, x.z, x.w * x.w))));
-            if constexpr (HALF == 128) {
-              if ((tid % LPR4) == 0) g.stats_out[(size_t)m * g.stats_n + (n0 + h * HALF) / 128] = ss;
+            if constexpr (HALF == T::STAT_COLS) {
+              if ((tid % LPR4) == 0) g.stats_out[(size_t)m * g.stats_n + (n0 + h * HALF) / HALF] = ss;
             } else {
               seg_ss[sw] = (h % 2 == 0) ? ss : seg_ss[sw] + ss;
               if (h % 2 == 1 && (tid % LPR4) == 0) g.stats_out[(size_t)m * g.stats_n + (n0 + (h / 2) * 128) / 128] = seg_ss[sw];
@@ -815,11 +862,14 @@ static void launch_cfg(const GemmArgs& g, hipStream_t s) {
   hipLaunchKernelGGL((gemm_bf16_kernel<T, EPI, OUT, GATHER, false, 0>), dim3(tiles_m * tiles_n), dim3(T::NT), 0, s, a);
 }
 
-//            BM   BN  BK  WM WN MINBLK PARTS
-using T0 = Tile<256, 256, 64, 2, 4, 1, 4>;   // 8 waves, 128x64 wave tiles, 128 KB LDS, one block per CU
-using T2 = Tile<256, 128, 64, 2, 2, 1, 4>;   // 4 waves, 128x64 wave tiles, 96 KB LDS
-using T4 = Tile<128, 128, 64, 2, 2, 2, 4>;   // 4 waves, 64x64 wave tiles, 64 KB LDS, two blocks per CU
-using T5 = Tile<320, 256, 64, 2, 4, 1, 5>;   // 8 waves, 160x64 wave tiles, 144 KB LDS, one block per CU
+//            BM   BN  BK  WM WN MINBLK PARTS STAGES
+using T0 = Tile<256, 256, 64, 2, 4, 1, 4, 2>;   // 8 waves, 128x64 wave tiles, 128 KB LDS, one block per CU
+using T2 = Tile<256, 128, 64, 2, 2, 1, 2, 3, true>;   // 4 waves, 128x64 wave tiles, 144 KB LDS, one block per CU
+using T4 = Tile<128, 128, 64, 2, 2, 2, 4, 2>;   // 4 waves, 64x64 wave tiles, 64 KB LDS, two blocks per CU
+using T5 = Tile<320, 256, 64, 2, 4, 1, 5, 2>;   // 8 waves, 160x64 wave tiles, 144 KB LDS, one block per CU
+
+using T7 = Tile<64, 64, 64, 2, 2, 2, 1, 4, true>;    // 4 waves, 32x32 wave tiles, 64 KB LDS, two blocks per CU
+using T8 = Tile<64, 128, 64, 2, 2, 2, 1, 3, true>;   // 4 waves, 32x64 wave tiles, 72 KB LDS, two blocks per CU
 
 // Tile choice.  Both large tiles run one block per compute unit, so an output whose number of
 // tiles is not a multiple of the unit count pays a whole tile time for its last, partial round,
@@ -838,10 +888,20 @@ using T5 = Tile<320, 256, 64, 2, 4, 1, 5>;   // 8 waves, 160x64 wave tiles, 144 
 // So the small tile wins short-K GEMMs with a heavy epilogue (the attention output projection at
 // hidden 1024), the 320 x 256 tile gains with short K and on grids where it needs fewer rounds,
 // and at K >= 3200 the two large tiles are equal.
+static bool known_tile(int t) { return t == 0 || t == 2 || t == 4 || t == 5 || t == 7 || t == 8; }
 struct TileShape { int bm, bn, blocks, cfg; double alpha, eps[4]; };   // eps indexed by Epilogue
+// Few rows: 64 x 128 and 64 x 64 tiles, whose stages are refilled three and two steps ahead between
+// the matrix instructions.  Their main loops are slower still per output (LDS reads), but a call
+// with one to four images has too few large tiles to occupy the chip, and each of those takes as
+// long as on a full one: 784 x 1024 x 4096 is 56 tiles of 128 x 128 in 62 us, 208 of 64 x 64 in 22
+// (784 x 3072 x 1024: 22 us, 64 x 128 tiles 16).  They are offered while they fit two rounds of
+// blocks; beyond, the large tiles fill the chip themselves (3136 x 3072 x 1024, three rounds:
+// 40 us against 36 with 256 x 256 tiles).
 constexpr TileShape kShape256 = {256, 256, 1, 0, 22.6, {13.2, 13.2, 39.4, 21.9}};
 constexpr TileShape kShape320 = {320, 256, 1, 5, 21.8, {11.7, 11.7, 39.4, 24.8}};
 constexpr TileShape kShape128 = {128, 128, 2, 4, 32.8, {4.6, 4.6, 23.8, 19.6}};
+constexpr TileShape kShape64 = {64, 64, 2, 7, 39.0, {41.0, 41.0, 59.0, 41.0}};
+constexpr TileShape kShape64x128 = {64, 128, 2, 8, 33.3, {22.5, 22.5, 36.7, 22.7}};
 constexpr double kSecondLaunch = 4.0;      // what a second launch of the same GEMM adds (gap + ramp), same unit
 
 static double tile_cost(int M, int N, int K, int epi, const TileShape& t, long cus) {
@@ -866,6 +926,10 @@ static TilePlan plan_tiles(int M, int N, int K, int epi, bool may_split, long cu
   };
   offer(kShape128.cfg, 0, tile_cost(M, N, K, epi, kShape128, cus));
   offer(kShape320.cfg, 0, tile_cost(M, N, K, epi, kShape320, cus));
+  for (const TileShape* t : {&kShape64, &kShape64x128}) {
+    const long tiles = (long)((M + t->bm - 1) / t->bm) * ((N + t->bn - 1) / t->bn);
+    if (tiles <= 2 * cus * t->blocks) offer(t->cfg, 0, tile_cost(M, N, K, epi, *t, cus));
+  }
   if (may_split) {
     for (const TileShape* t : {&kShape256, &kShape320}) {
       const long tm = (M + t->bm - 1) / t->bm, tn = (N + t->bn - 1) / t->bn;
@@ -883,12 +947,14 @@ static TilePlan plan_tiles(int M, int N, int K, int epi, bool may_split, long cu
 template <int EPI, int OUT, bool GATHER>
 static void launch_epi(const GemmArgs& g, hipStream_t s) {
   int t = g.tile_cfg > 0 ? g.tile_cfg - 1 : -1;   // tile_cfg: set by the tuning hook of the C ABI, or by a split
-  if (t != 0 && t != 2 && t != 4 && t != 5) t = plan_tiles(g.M, g.N, g.K, g.epilogue, false, g.compute_units > 0 ? g.compute_units : num_cus()).tile;
+  if (!known_tile(t)) t = plan_tiles(g.M, g.N, g.K, g.epilogue, false, g.compute_units > 0 ? g.compute_units : num_cus()).tile;
   if (EPI == EPI_QKV && (t == 0 || t == 5) && g.qk_cols % 256 != 0) t = 2;
   switch (t) {
     case 0: launch_cfg<T0, EPI, OUT, GATHER>(g, s); break;
     case 2: launch_cfg<T2, EPI, OUT, GATHER>(g, s); break;
     case 5: launch_cfg<T5, EPI, OUT, GATHER>(g, s); break;
+    case 7: launch_cfg<T7, EPI, OUT, GATHER>(g, s); break;
+    case 8: launch_cfg<T8, EPI, OUT, GATHER>(g, s); break;
     default: launch_cfg<T4, EPI, OUT, GATHER>(g, s); break;
   }
 }
@@ -906,14 +972,20 @@ static bool may_split_rows(const GemmArgs& g) {
 void plan_gemm_bf16(const GemmArgs& g, int compute_units, int* tile_rows, int* tile_cols, int* body_rows) {
   const long cus = compute_units > 0 ? compute_units : (g.compute_units > 0 ? g.compute_units : num_cus());
   int t = g.tile_cfg > 0 ? g.tile_cfg - 1 : -1, body = 0;
-  if (t != 0 && t != 2 && t != 4 && t != 5) {
+  if (!known_tile(t)) {
     const TilePlan p = plan_tiles(g.M, g.N, g.K, g.epilogue, may_split_rows(g), cus);
     t = p.tile; body = p.body_rows;
   }
   if (g.epilogue == EPI_QKV && (t == 0 || t == 5) && g.qk_cols % 256 != 0) t = 2;
-  *tile_rows = t == 4 ? 128 : t == 5 ? 320 : 256;
-  *tile_cols = t == 4 || t == 2 ? 128 : 256;
+  *tile_rows = t == 7 || t == 8 ? 64 : t == 4 ? 128 : t == 5 ? 320 : 256;
+  *tile_cols = t == 7 ? 64 : t == 0 || t == 5 ? 256 : 128;
   *body_rows = body;
+}
+
+int gemm_bf16_stat_cols(const GemmArgs& g) {
+  int rows, cols, body;
+  plan_gemm_bf16(g, 0, &rows, &cols, &body);
+  return cols < 128 ? cols : 128;
 }
 
 void launch_gemm_bf16(const GemmArgs& g, hipStream_t s) {
