@@ -71,6 +71,19 @@ __device__ __forceinline__ float gelu_tanh_fast(float x) {
   return x * (1.0f - __builtin_amdgcn_rcpf(1.0f + e));   // x * sigmoid(2u)
 }
 
+// (a, b) turned by (cos, sin).  One of the two products of each sum is rounded before it is added;
+// which one is spelled out, because the compiler chose differently for different copies of an
+// unrolled loop: the last eight rows of a tile (of every 128 rows for the 64-row tiles) had the
+// product with the cosine rounded, the others that with the sine.  Kept so, row by row: every tile of
+// up to 128 rows then gives a token the same bits, and calls give the bits they gave when 128 x 128
+// was the smallest tile.
+__device__ __forceinline__ void rotate_pair(float& a, float& b, float cos, float sin, bool sin_last) {
+  const float as = a * sin, ac = a * cos, bs = b * sin, bc = b * cos;
+  const float ra = sin_last ? fmaf(-b, sin, ac) : fmaf(a, cos, -bs);
+  const float rb = sin_last ? fmaf(a, sin, bc) : fmaf(b, cos, as);
+  a = ra; b = rb;
+}
+
 enum OutKind : int { OUT_BF16 = 0, OUT_F32 = 1 };
 
 // Sum over aligned groups of G = 16 or 32 consecutive lanes; every lane of a group gets the sum.
@@ -275,11 +288,15 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int m0, const
   // barriers of the main loop make it visible to the epilogue).
   float* const row_scale = (float*)(lds + T::LDS_BYTES + lds_extra<T, EPI>());
   const bool scaled = g.stats_in != nullptr;
-  // 8 or (small tiles only, which leave 64-column sums) 16 segments (hidden 1024): the loads are
-  // issued here, ahead of the first operand loads, and only consumed after the first barrier
+  // The order of the additions is the same whichever tile left the sums and whichever takes them:
+  // sums of 64 columns (stats_n * 64 = K) are added in pairs first, which is how a tile of 128 columns
+  // makes one, then 8 segments (hidden 1024) as a tree, any other number one after the other.
+  // Hidden 1024: the 8 or (small tiles only) 16 sums of a row are loaded here, ahead of the first
+  // operand loads, and only consumed after the first barrier
   static_assert(BM <= NT, "one row scale per thread");
   constexpr int SV = BM * BN <= 128 * 128 ? 4 : 2;       // 16-byte loads held
-  const bool scaled_v = scaled && (g.stats_n == 8 || g.stats_n == 4 * SV);
+  const bool halves = g.stats_n * 64 == g.K;             // sums of 64 columns
+  const bool scaled_v = scaled && g.K == 1024 && g.stats_n <= 4 * SV;
   float4 st[SV];
   if (scaled_v) {
 #pragma unroll
@@ -287,13 +304,19 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int m0, const
     if (tid < BM) {
       const float4* sp = (const float4*)(g.stats_in + (size_t)min(m0 + tid, g.M - 1) * g.stats_n);
       st[0] = sp[0]; st[1] = sp[1];
-      if constexpr (SV == 4) { if (g.stats_n == 16) { st[2] = sp[2]; st[3] = sp[3]; } }
+      if constexpr (SV == 4) { if (halves) { st[2] = sp[2]; st[3] = sp[3]; } }
     }
   } else if (scaled) {
     for (int r = tid; r < BM; r += NT) {
       const float* sp = g.stats_in + (size_t)min(m0 + r, g.M - 1) * g.stats_n;
+      auto segment = [&](int j) { return halves ? sp[2 * j] + sp[2 * j + 1] : sp[j]; };
       float ss = 0.f;
-      for (int j = 0; j < g.stats_n; ++j) ss += sp[j];
+      if (g.K == 1024) {
+        ss = ((segment(0) + segment(1)) + (segment(2) + segment(3))) + ((segment(4) + segment(5)) + (segment(6) + segment(7)));
+      } else {
+        const int n = halves ? g.stats_n / 2 : g.stats_n;
+        for (int j = 0; j < n; ++j) ss += segment(j);
+      }
       row_scale[r] = 1.0f / sqrtf(fmaf(ss, g.stats_inv_dim, g.stats_eps));
     }
   }
@@ -645,6 +668,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int m0, const
     constexpr int STG = SR * ROWE;
     constexpr int LPR4 = BN / 4, RPS = NT / LPR4;      // lanes per row (4 columns each), rows per sweep
     static_assert(STG <= T::LDS_BYTES && SR % RPS == 0 && NT % LPR4 == 0 && LPR4 >= 16, "row-split staging");
+    static_assert(BM < 128 || RPS == 8, "rows of the last sweep (rotate_pair)");
     const int cl = (tid % LPR4) * 4;
     const int n = n0 + cl;                             // N is a multiple of 4: all or nothing
     float b0 = 0.f, b1 = 0.f, b2 = 0.f, b3 = 0.f;
@@ -693,9 +717,9 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int m0, const
           if (g.rot) {
             const float4 cs = tab_lds ? *(const float4*)(tab + ml * trb + pr * 8)
                                       : *(const float4*)(g.rot + (size_t)m * g.rot_pairs + pr);
-            const float r0 = v0 * cs.x - v1 * cs.y, r1 = v0 * cs.y + v1 * cs.x;
-            const float r2 = v2 * cs.z - v3 * cs.w, r3 = v2 * cs.w + v3 * cs.z;
-            v0 = r0; v1 = r1; v2 = r2; v3 = r3;
+            const bool sin_last = BM >= 128 ? i == TM - 1 && sw == SR / RPS - 1 : (m & 127) >= 120;
+            rotate_pair(v0, v1, cs.x, cs.y, sin_last);
+            rotate_pair(v2, v3, cs.z, cs.w, sin_last);
           }
           // the softmax scale (in log2 units) rides on Q: one rounding of q * scale instead of
           // a multiply per score in the attention kernel
