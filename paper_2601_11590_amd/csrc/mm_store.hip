@@ -299,6 +299,7 @@ uint64_t* g_scratch_ptr[kMaxDevices] = {};     // device address of `scratch` on
 struct epd_store {
   char* pool = nullptr;          // device; [0, kScratchBytes) reserved, entries behind it
   uint64_t* partial = nullptr;   // pinned host memory: partial hashes of one launch, written by the kernel
+  std::vector<uint64_t*> given_up;         // earlier ones that a kernel may still write, freed at destroy
   uint64_t arena = 0;            // bytes available to entries (multiple of kAlign)
   std::map<Key, Entry> entries;
   std::map<uint64_t, uint64_t> by_off;     // offset -> rounded size
@@ -329,6 +330,13 @@ hipError_t pin_partials(epd_store* s) {
   if (e != hipSuccess) { s->partial = nullptr; (void)hipGetLastError(); return e; }
   std::fill(s->partial, s->partial + (size_t)kMaxBlocks * 2, kAbsent);
   return e;
+}
+
+// A launch whose end could not be waited for may write its slots at any time: they are given up, so
+// that no later call takes those sums for its own, and the next call gets others.
+void give_up_partials(epd_store* s) {
+  s->given_up.push_back(s->partial);
+  s->partial = nullptr;
 }
 
 // Sum of the `count` pairs at p, each waited for and then marked absent again for the next launch.
@@ -384,6 +392,7 @@ epd_status epd_store_create(void* device_pool, uint64_t pool_bytes, epd_store_ha
 
 epd_status epd_store_destroy(epd_store_handle s) {
   if (s && s->partial) (void)hipHostFree(s->partial);
+  if (s) for (uint64_t* p : s->given_up) (void)hipHostFree(p);
   delete s;
   return EPD_OK;
 }
@@ -437,11 +446,13 @@ epd_status epd_store_stats(epd_store_handle s, uint64_t* hits, uint64_t* misses,
 }
 
 // Describes ranges [i0, i0 + m) in `a` and launches the hash kernel for them; partial hashes go to
-// a.partial (set by the caller).  Blocks take as many 16 KB groups as keep the launch at about
-// kAimBlocks blocks (two or more waves on every SIMD): one group each up to 32 MB, where a block's
-// fixed part -- its reduction and its power -- costs about as much as a group.
-static void launch_hash(HashArgs& a, const void* device_data, const uint64_t* offsets, const uint64_t* salts, int i0, int m,
-                        hipStream_t st) {
+// a.partial (set by the caller).  Returns the launch's own status: the runtime's last error may be one
+// that the program left behind long before, and the kernel runs all the same.
+// Blocks take as many 16 KB groups as keep the launch at about kAimBlocks blocks (two or more waves
+// on every SIMD): one group each up to 32 MB, where a block's fixed part -- its reduction and its
+// power -- costs about as much as a group.
+static hipError_t launch_hash(HashArgs& a, const void* device_data, const uint64_t* offsets, const uint64_t* salts, int i0, int m,
+                              hipStream_t st) {
   uint64_t total = 0;
   for (int j = 0; j < m; ++j) total += (offsets[i0 + j + 1] - offsets[i0 + j]) / 4 / kGroupWords + 1;
   const uint32_t groups = (uint32_t)((total + kAimBlocks - 1) / kAimBlocks);
@@ -459,7 +470,8 @@ static void launch_hash(HashArgs& a, const void* device_data, const uint64_t* of
   }
   a.n = m;
   a.blocks = blocks;
-  hipLaunchKernelGGL(hash_partial_kernel, dim3(blocks), dim3(kThreads), 0, st, a);
+  void* args[] = {&a};
+  return hipLaunchKernel((const void*)hash_partial_kernel, dim3(blocks), dim3(kThreads), args, 0, st);
 }
 static_assert(kAimBlocks + 2 * kRanges <= kMaxBlocks, "partial hashes of one launch");
 
@@ -480,7 +492,15 @@ epd_status epd_store_hash(epd_store_handle s, const void* device_data, const uin
   }
   if (!ranges_ok(offsets, n, s->err)) return EPD_ERR_SHAPE;
   hipStream_t st = (hipStream_t)stream;
-  if (hipError_t e = pin_partials(s)) { s->err = fmt("pinned memory for the partial hashes: %s", hipGetErrorString(e)); return EPD_ERR_HIP; }
+  // a captured launch would run again with every replay, when nobody takes its sums
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  hipError_t e = hipStreamIsCapturing(st, &capture);
+  if (e != hipSuccess || capture != hipStreamCaptureStatusNone) {
+    s->err = e != hipSuccess ? fmt("hipStreamIsCapturing: %s", hipGetErrorString(e)) : "the stream is being captured: the call waits for its keys";
+    return EPD_ERR_HIP;
+  }
+  e = pin_partials(s);
+  if (e != hipSuccess) { s->err = fmt("pinned memory for the partial hashes: %s", hipGetErrorString(e)); return EPD_ERR_HIP; }
   // The kernel leaves its blocks' partial hashes in host memory and the host adds them up: no second
   // kernel, no copy (the host has to wait for the keys anyway -- they decide what is launched next).
   // A call on four 9.6 MB clips: 92 us with a second kernel, a copy and a wait for the stream (61 us of
@@ -489,16 +509,16 @@ epd_status epd_store_hash(epd_store_handle s, const void* device_data, const uin
   a.partial = s->partial;
   for (int i0 = 0; i0 < n; i0 += kRanges) {
     const int m = n - i0 < kRanges ? n - i0 : kRanges;
-    launch_hash(a, device_data, offsets, salts, i0, m, st);
-    hipError_t e = hipGetLastError();
+    e = launch_hash(a, device_data, offsets, salts, i0, m, st);
+    if (e != hipSuccess) { s->err = fmt("hash launch failed: %s", hipGetErrorString(e)); return EPD_ERR_HIP; }   // nothing was queued
     bool synced = false;
     for (int j = 0; j < m && e == hipSuccess; ++j) {
       const uint32_t b0 = a.r[j].first_block, b1 = j + 1 < m ? a.r[j + 1].first_block : a.blocks;
       e = take_partials(s->partial + (size_t)b0 * 2, b1 - b0, st, synced, keys_out + (size_t)(i0 + j) * 2);
     }
     if (e != hipSuccess) {
-      std::fill(s->partial, s->partial + (size_t)kMaxBlocks * 2, kAbsent);
-      s->err = fmt("hash launch failed: %s", hipGetErrorString(e)); return EPD_ERR_HIP;
+      give_up_partials(s);
+      s->err = fmt("waiting for the hash kernel failed: %s", hipGetErrorString(e)); return EPD_ERR_HIP;
     }
   }
   return EPD_OK;
@@ -542,7 +562,7 @@ epd_status epd_store_hash_noalloc(const void* device_data, const uint64_t* offse
   HashArgs a{};
   a.partial = ptr;
   a.result = keys_device_out;
-  launch_hash(a, device_data, offsets, salts, 0, n, (hipStream_t)stream);
+  (void)launch_hash(a, device_data, offsets, salts, 0, n, (hipStream_t)stream);   // a failure shows below
   hipLaunchKernelGGL(hash_final_kernel, dim3(n), dim3(64), 0, (hipStream_t)stream, a);
   e = hipGetLastError();
   if (e != hipSuccess) { g_store_error = fmt("hash launch failed: %s", hipGetErrorString(e)); return EPD_ERR_HIP; }

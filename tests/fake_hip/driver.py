@@ -1,0 +1,135 @@
+"""The built library on the stand-in runtime of fake_hip.cpp, in a process of its own that never loads
+torch:  python driver.py <stand-in .so> <libepd_encode.so> <function of this file>."""
+
+import ctypes as C
+import os
+import sys
+
+import numpy as np
+
+sys.path.insert(0, os.path.dirname(os.path.dirname(os.path.dirname(os.path.abspath(__file__)))))
+from oracle import mm_store as S                                        # noqa: E402
+
+OK, MISS, ERR_HIP = 0, 1, -5
+LAST_ERROR, CAPTURE, LATE, LAUNCH_STATUS, SYNC_STATUS, HOST_FLAGS = range(6)
+POOL = 0x7F0000000000                                                   # never dereferenced
+U64P = C.POINTER(C.c_uint64)
+
+
+def load(fake_path, lib_path):
+    fake = C.CDLL(fake_path, mode=C.RTLD_GLOBAL)
+    fake.fake_set.argtypes = [C.c_int, C.c_longlong]
+    fake.fake_get.restype = C.c_longlong
+    fake.fake_calls.restype = C.c_longlong
+    fake.fake_calls.argtypes = [C.c_char_p]
+    fake.fake_launch.restype = C.c_char_p
+    fake.fake_launch.argtypes = [C.c_int, C.POINTER(C.c_uint32)]
+    lib = C.CDLL(lib_path)
+    lib.epd_store_create.argtypes = [C.c_void_p, C.c_uint64, C.POINTER(C.c_void_p)]
+    lib.epd_store_destroy.argtypes = [C.c_void_p]
+    lib.epd_store_hash.argtypes = [C.c_void_p, C.c_void_p, U64P, U64P, C.c_int32, U64P, C.c_void_p]
+    return fake, lib
+
+
+def launches(fake):
+    out = []
+    for i in range(fake.fake_launches()):
+        v = (C.c_uint32 * 6)()
+        out.append((fake.fake_launch(i, v).decode(), tuple(v[:3]), tuple(v[3:])))
+    return out
+
+
+class Store:
+    def __init__(self, lib):
+        self.lib, self.h = lib, C.c_void_p()
+        assert lib.epd_store_create(POOL, 2 << 20, C.byref(self.h)) == OK
+
+    def hash(self, *buffers):
+        """(status, keys) of the buffers, hashed in one call."""
+        data = np.frombuffer(b"".join(buffers), np.uint8)
+        off = np.cumsum([0] + [len(b) for b in buffers]).astype(np.uint64)
+        salt = np.arange(len(buffers), dtype=np.uint64)
+        keys = np.zeros((len(buffers), 2), np.uint64)
+        p = lambda a: a.ctypes.data_as(U64P)
+        st = self.lib.epd_store_hash(self.h, data.ctypes.data, p(off), p(salt), len(buffers), p(keys), None)
+        return st, [tuple(int(v) for v in k) for k in keys]
+
+    def close(self):
+        assert self.lib.epd_store_destroy(self.h) == OK
+
+
+def buffers(seed, n=3):
+    rng = np.random.default_rng(seed)
+    return [rng.integers(0, 256, size=int(rng.integers(1, 40000)), dtype=np.uint8).tobytes() for _ in range(n)]
+
+
+def keys_of(bufs):
+    return [S.hash128(b, i) for i, b in enumerate(bufs)]
+
+
+def hash_right(store, seed, n=3):
+    b = buffers(seed, n)
+    st, keys = store.hash(*b)
+    assert st == OK and keys == keys_of(b), (st, keys, keys_of(b))
+
+
+# ------------------------------------------------------------------ the tests
+
+def hash_plain(fake, lib):
+    s = Store(lib)
+    for late in (0, 1):
+        fake.fake_set(LATE, late)
+        for seed in range(3):
+            hash_right(s, seed)
+        hash_right(s, 9, n=70)                                          # three launches
+    s.close()
+
+
+def hash_with_an_uncollected_error(fake, lib):
+    s = Store(lib)
+    for late in (0, 1):
+        fake.fake_set(LATE, late)
+        for seed in range(4):
+            fake.fake_set(LAST_ERROR, 1)                                # left by some earlier call of the program
+            hash_right(s, seed)
+    s.close()
+
+
+def hash_after_a_failed_launch(fake, lib):
+    s = Store(lib)
+    hash_right(s, 0)
+    fake.fake_set(LAUNCH_STATUS, 98)
+    assert s.hash(*buffers(1))[0] == ERR_HIP
+    fake.fake_set(LAUNCH_STATUS, 0)
+    hash_right(s, 2)
+    s.close()
+
+
+def hash_after_a_failed_wait(fake, lib):
+    s = Store(lib)
+    fake.fake_set(LATE, 1)
+    for seed in range(3):
+        hash_right(s, seed)
+        fake.fake_set(SYNC_STATUS, 719)
+        assert s.hash(*buffers(seed + 10))[0] == ERR_HIP
+        fake.fake_set(SYNC_STATUS, 0)
+        fake.fake_drain()                                               # the kernel of the failed call ends only now
+    hash_right(s, 5)
+    s.close()
+
+
+def hash_on_a_capturing_stream(fake, lib):
+    s = Store(lib)
+    hash_right(s, 0)
+    fake.fake_forget()
+    fake.fake_set(CAPTURE, 1)
+    assert s.hash(*buffers(1))[0] == ERR_HIP
+    assert launches(fake) == []                                         # a captured launch would run again with every replay
+    fake.fake_set(CAPTURE, 0)
+    hash_right(s, 2)
+    s.close()
+
+
+if __name__ == "__main__":
+    globals()[sys.argv[3]](*load(sys.argv[1], sys.argv[2]))
+    print("passed", sys.argv[3])
