@@ -326,7 +326,9 @@ uint64_t first_fit(const epd_store* s, uint64_t need) {
 
 hipError_t pin_partials(epd_store* s) {
   if (s->partial) return hipSuccess;
-  const hipError_t e = hipHostMalloc((void**)&s->partial, (size_t)kMaxBlocks * 16, hipHostMallocPortable);
+  // coherent whatever the environment says: the host reads and resets slots while the kernel runs, and
+  // a late write-back over a reset slot would be read as the next launch's sum
+  const hipError_t e = hipHostMalloc((void**)&s->partial, (size_t)kMaxBlocks * 16, hipHostMallocPortable | hipHostMallocCoherent);
   if (e != hipSuccess) { s->partial = nullptr; (void)hipGetLastError(); return e; }
   std::fill(s->partial, s->partial + (size_t)kMaxBlocks * 2, kAbsent);
   return e;

@@ -95,6 +95,14 @@ def hash_with_an_uncollected_error(fake, lib):
     s.close()
 
 
+def partial_hashes_lie_in_coherent_memory(fake, lib):
+    s = Store(lib)
+    hash_right(s, 0)
+    portable, coherent, non_coherent = 0x1, 0x40000000, 0x80000000      # hipHostMalloc flags
+    assert fake.fake_get(HOST_FLAGS) & (portable | coherent | non_coherent) == portable | coherent
+    s.close()
+
+
 def hash_after_a_failed_launch(fake, lib):
     s = Store(lib)
     hash_right(s, 0)
