@@ -324,6 +324,7 @@ uint64_t first_fit(const epd_store* s, uint64_t need) {
   return s->arena - pos >= need ? pos : UINT64_MAX;
 }
 
+// Taken by the store's first hash and not when it is made: the bookkeeping starts no GPU.
 hipError_t pin_partials(epd_store* s) {
   if (s->partial) return hipSuccess;
   // coherent whatever the environment says: the host reads and resets slots while the kernel runs, and
@@ -387,7 +388,6 @@ epd_status epd_store_create(void* device_pool, uint64_t pool_bytes, epd_store_ha
   epd_store* s = new epd_store();
   s->pool = (char*)device_pool;
   s->arena = (pool_bytes - kScratchBytes) / kAlign * kAlign;
-  (void)pin_partials(s);         // without a GPU (bookkeeping only) this fails; epd_store_hash asks again
   *out = s;
   return EPD_OK;
 }

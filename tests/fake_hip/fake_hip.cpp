@@ -57,6 +57,7 @@ void fake_set(int what, long long value) { g_set[what] = value; }
 long long fake_get(int what) { return g_set[what]; }
 void fake_drain() { drain(); }
 long long fake_calls(const char* name) { return g_calls[name]; }
+int fake_all_calls() { int n = 0; for (auto& c : g_calls) n += (int)c.second; return n; }
 int fake_launches() { return (int)g_launches.size(); }
 void fake_forget() { g_launches.clear(); g_calls.clear(); }
 // launch i: name, grid and block sizes
