@@ -723,10 +723,15 @@ epd_status epd_encode_cached(epd_handle h, epd_store_handle s, uint64_t model_sa
     h->err = std::string("epd_store_hash: ") + epd_store_last_error(s); return e;
   }
   if (keys_out) std::memcpy(keys_out, keys.data(), keys.size() * 8);
-  // hits: copy out, all in one launch; misses: collect
+  // hits: copy out, all in one launch; misses: collect.  Only a launch's own status counts: the
+  // runtime's last error may be one that the program left behind, and the copies run all the same.
   std::vector<int> miss;
   CopyArgs cp{};
-  auto flush = [&]() { if (cp.n) launch_copies(cp, st); cp.n = 0; };
+  auto flush = [&]() {
+    const hipError_t e = cp.n ? launch_copies(cp, st) : hipSuccess;
+    cp.n = 0;
+    return e;
+  };
   for (int i = 0; i < n; ++i) {
     void* p = nullptr;
     uint64_t bytes = 0;
@@ -735,11 +740,10 @@ epd_status epd_encode_cached(epd_handle h, epd_store_handle s, uint64_t model_sa
     const bool hit = e == EPD_OK && bytes == want;
     if (hit_out) hit_out[i] = hit ? 1 : 0;
     if (!hit) { miss.push_back(i); continue; }
-    if (cp.n == kCopyItems) flush();
+    if (cp.n == kCopyItems) EPD_HIP(h, flush());
     cp.item[cp.n++] = CopyItem{p, (char*)out_visual_tokens + (size_t)mrg[i] * row_bytes, nullptr, (long long)want};
   }
-  flush();
-  EPD_HIP(h, hipGetLastError());
+  EPD_HIP(h, flush());
   if (miss.empty()) return EPD_OK;
   // misses: preprocess every run of neighbouring items into the compact batch, then encode it
   std::vector<int32_t> cu(miss.size() + 1, 0), grid(miss.size() * 3);
@@ -764,7 +768,7 @@ epd_status epd_encode_cached(epd_handle h, epd_store_handle s, uint64_t model_sa
     const int i = miss[j];
     const size_t bytes = (size_t)(mrg[i + 1] - mrg[i]) * row_bytes;
     char* const src = (char*)out_scratch + m0 * row_bytes;
-    if (cp.n == kCopyItems) flush();
+    if (cp.n == kCopyItems) EPD_HIP(h, flush());
     void* slot = nullptr;
     if (epd_store_insert(s, &keys[2 * i], bytes, &slot) != EPD_OK) slot = nullptr;
     // an insert may have dropped an entry that this launch was to file: its range is taken over
@@ -775,8 +779,7 @@ epd_status epd_encode_cached(epd_handle h, epd_store_handle s, uint64_t model_sa
     cp.item[cp.n++] = CopyItem{src, (char*)out_visual_tokens + (size_t)mrg[i] * row_bytes, slot, (long long)bytes};
     m0 += (size_t)(mrg[i + 1] - mrg[i]);
   }
-  flush();
-  EPD_HIP(h, hipGetLastError());
+  EPD_HIP(h, flush());
   return EPD_OK;
 }
 

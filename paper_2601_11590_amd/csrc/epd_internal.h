@@ -178,7 +178,7 @@ struct CopyArgs {
   int first_block[kCopyItems];   // set by the launcher
   CopyItem item[kCopyItems];
 };
-void launch_copies(CopyArgs& a, hipStream_t s);   // destinations of one launch must not overlap
+hipError_t launch_copies(CopyArgs& a, hipStream_t s);   // the launch's own status; destinations of one launch must not overlap
 
 constexpr int kVtAlign = 128;   // segment starts in the transposed-V buffer are multiples of this
 

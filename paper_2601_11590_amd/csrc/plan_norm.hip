@@ -274,13 +274,15 @@ __global__ __launch_bounds__(256) void copies_kernel(CopyArgs a) {
   }
 }
 
-void launch_copies(CopyArgs& a, hipStream_t s) {
+hipError_t launch_copies(CopyArgs& a, hipStream_t s) {
   long long blocks = 0;
   for (int i = 0; i < a.n; ++i) {
     a.first_block[i] = (int)blocks;
     blocks += (a.item[i].bytes + kCopyPiece - 1) / kCopyPiece;
   }
-  if (blocks > 0) hipLaunchKernelGGL(copies_kernel, dim3((unsigned)blocks), dim3(256), 0, s, a);
+  if (blocks == 0) return hipSuccess;
+  void* args[] = {&a};
+  return hipLaunchKernel((const void*)copies_kernel, dim3((unsigned)blocks), dim3(256), args, 0, s);
 }
 
 // ---------------------------------------------------------------- gamma folding (create time)

@@ -4,11 +4,13 @@ torch:  python driver.py <stand-in .so> <libepd_encode.so> <function of this fil
 import ctypes as C
 import os
 import sys
+import types
 
 import numpy as np
 
 sys.path.insert(0, os.path.dirname(os.path.dirname(os.path.dirname(os.path.abspath(__file__)))))
 from oracle import mm_store as S                                        # noqa: E402
+from paper_2601_11590_amd import build, workloads as W                  # noqa: E402
 
 OK, MISS, ERR_HIP = 0, 1, -5
 LAST_ERROR, CAPTURE, LATE, LAUNCH_STATUS, SYNC_STATUS, HOST_FLAGS = range(6)
@@ -24,11 +26,32 @@ def load(fake_path, lib_path):
     fake.fake_calls.argtypes = [C.c_char_p]
     fake.fake_launch.restype = C.c_char_p
     fake.fake_launch.argtypes = [C.c_int, C.POINTER(C.c_uint32)]
-    lib = C.CDLL(lib_path)
-    lib.epd_store_create.argtypes = [C.c_void_p, C.c_uint64, C.POINTER(C.c_void_p)]
-    lib.epd_store_destroy.argtypes = [C.c_void_p]
-    lib.epd_store_hash.argtypes = [C.c_void_p, C.c_void_p, U64P, U64P, C.c_int32, U64P, C.c_void_p]
-    return fake, lib
+    # the package's own binding, with a torch that holds names only: the real one would load the real runtime
+    torch = types.ModuleType("torch")
+    torch.__getattr__ = lambda name: type(name, (), {})
+    sys.modules["torch"] = torch
+    build.library_path = lambda: lib_path
+    from paper_2601_11590_amd import binding
+    return fake, binding.lib
+
+
+def binding():
+    return sys.modules["paper_2601_11590_amd.binding"]
+
+
+def encoder(cfg, max_tokens, max_segments, max_items):
+    """An encoder handle over made-up device addresses."""
+    B = binding()
+    c, w = B.make_cfg(cfg, max_tokens, max_segments, max_items), B.epd_weights()
+    layers = (B.epd_layer_weights * max(1, cfg.num_layers))()
+    for f, _ in B.epd_layer_weights._fields_:
+        for l in layers:
+            setattr(l, f, 0x1000)
+    for f in ("patch_w", "patch_b", "final_norm_g", "final_norm_b", "merge_w", "merge_b"):
+        setattr(w, f, 0x1000)
+    w.layers = C.cast(layers, C.POINTER(B.epd_layer_weights))
+    c.weights, c.workspace, c.workspace_bytes = C.pointer(w), 0x100000, 1 << 60
+    return B.epd_encode_create(c)
 
 
 def launches(fake):
@@ -104,8 +127,6 @@ def partial_hashes_lie_in_coherent_memory(fake, lib):
 
 
 def bookkeeping_makes_no_runtime_calls(fake, lib):
-    lib.epd_store_lookup.argtypes = [C.c_void_p, U64P, C.POINTER(C.c_void_p), U64P]
-    lib.epd_store_insert.argtypes = [C.c_void_p, U64P, C.c_uint64, C.POINTER(C.c_void_p)]
     fake.fake_forget()
     s, key, where = Store(lib), (C.c_uint64 * 2)(1, 2), C.c_void_p()
     assert lib.epd_store_lookup(s.h, key, C.byref(where), None) == MISS
@@ -154,6 +175,28 @@ def hash_on_a_capturing_stream(fake, lib):
     fake.fake_set(CAPTURE, 0)
     hash_right(s, 2)
     s.close()
+
+
+def cached_hits_beside_an_uncollected_error(fake, lib):
+    B = binding()
+    cfg = W.C2.replace(num_layers=1)
+    grids, src = [(1, 2, 2), (1, 4, 2)], [(40, 30), (64, 32)]
+    h, s = encoder(cfg, 64, 8, 8), Store(lib)
+    px = np.random.default_rng(0).integers(0, 256, size=3 * (40 * 30 + 64 * 32), dtype=np.uint8)
+    call = lambda: B.epd_encode_cached(h, s.h, 7, px.ctypes.data, src, grids, [0.5] * 3, [0.25] * 3, POOL, POOL, POOL, None)
+    hit, keys = call()
+    assert hit.tolist() == [0, 0]
+    for status, want in ((0, None), (1, None), (98, ERR_HIP)):
+        fake.fake_forget()
+        fake.fake_set(LAST_ERROR, 1 if status == 1 else 0)              # left by some earlier call of the program
+        if status == 98:
+            fake.fake_refuse(b"copies_kernel", 98)
+        try:
+            hit, again = call()
+            assert want is None and hit.tolist() == [1, 1] and (keys == again).all()
+            assert sum("copies_kernel" in l[0] for l in launches(fake)) == 1
+        except B.EpdError as e:
+            assert e.status == want, e
 
 
 if __name__ == "__main__":

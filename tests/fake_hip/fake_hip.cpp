@@ -24,6 +24,9 @@ std::map<std::string, long long> g_calls;
 long long g_set[8];                                      // see fake_set
 enum { kLastError, kCapture, kLate, kLaunchStatus, kSyncStatus, kHostFlags };
 
+std::string g_refuse;                                    // see fake_refuse
+int g_refuse_status = 0;
+
 constexpr uint64_t kP = (1ull << 61) - 1;
 uint64_t mul(uint64_t a, uint64_t b) { return (uint64_t)((unsigned __int128)a * b % kP); }
 
@@ -54,6 +57,8 @@ extern "C" {
 // what: 0 = the thread's uncollected last error, 1 = capture status of every stream, 2 = stores of
 // kernels appear late (at the next wait), 3 / 4 = status of launches / of waits for a stream
 void fake_set(int what, long long value) { g_set[what] = value; }
+// launches of kernels whose name holds `part` fail with `status`
+void fake_refuse(const char* part, int status) { g_refuse = part; g_refuse_status = status; }
 long long fake_get(int what) { return g_set[what]; }
 void fake_drain() { drain(); }
 long long fake_calls(const char* name) { return g_calls[name]; }
@@ -80,6 +85,7 @@ int __hipPopCallConfiguration(Dim3* g, Dim3* b, size_t* s, void** st) { *g = g_g
 int hipLaunchKernel(const void* f, Dim3 grid, Dim3 block, void** args, size_t, void*) {
   CALL();
   if (g_set[kLaunchStatus]) { g_set[kLastError] = g_set[kLaunchStatus]; return (int)g_set[kLaunchStatus]; }
+  if (!g_refuse.empty() && g_names[f].find(g_refuse) != std::string::npos) { g_set[kLastError] = g_refuse_status; return g_refuse_status; }
   g_launches.push_back({g_names[f], grid, block});
   if (g_names[f].find("hash_partial_kernel") != std::string::npos) {
     HashArgs a;
