@@ -10,7 +10,7 @@
 //
 // Bound: HBM (1 byte in per source pixel, 2 or 4 bytes out per element) once enough loads are in
 // flight.  The tap positions are exact integer arithmetic, (2j + 1) * n_in - n_out over 2 * n_out,
-// so that equal sizes copy pixels untouched; the weights carry the rounding of one product.
+// so that equal sizes copy pixels untouched and the weights carry a single rounding.
 #include "epd_internal.h"
 
 namespace epd {
@@ -19,7 +19,8 @@ struct Tap { int i0; float w1; };
 
 // taps of output sample j along an axis of n_in source and n_out output samples: i0 and i0 + 1
 // (clamped by the caller), the second weighted w1.  inv = 1 / (2 n_out): the quotient of the float
-// product is off by at most one (it stays below 2^14), which the remainder shows.
+// product is off by at most one (it stays below 2^14), which the remainder shows.  The weight is a
+// true division (remainder times inv would be rounded twice: mean error 2.2e-8 instead of 0.8e-8).
 __device__ __forceinline__ Tap tap(int j, int n_in, int n_out, float inv) {
   const int num = max((2 * j + 1) * n_in - n_out, 0), den = 2 * n_out;
   int q = (int)((float)num * inv), r = num - q * den;
@@ -27,7 +28,7 @@ __device__ __forceinline__ Tap tap(int j, int n_in, int n_out, float inv) {
   if (r >= den) { ++q; r -= den; }
   Tap t;
   t.i0 = min(q, n_in - 1);
-  t.w1 = (float)r * inv;
+  t.w1 = (float)r / (float)den;
   return t;
 }
 
