@@ -183,12 +183,14 @@ epd_status epd_preprocess(epd_handle h, const uint8_t* pixels, const int32_t* sr
  *          arena of contiguous, 256-byte aligned entries; an insert drops least-recently-used
  *          entries until a free range (first fit, lowest address) holds the new entry; a
  *          lookup that hits makes its entry the most recent.
- * One call per store at a time.  Bookkeeping (create / lookup / insert / stats / destroy) is
- * host code and never touches device memory. */
+ * One call per store at a time.  Bookkeeping (lookup / insert / stats) is host code and makes no
+ * call of the HIP runtime; create and destroy allocate and free 64 KiB of pinned host memory, where the
+ * hash kernel leaves its sums.  None of them touches device memory. */
 typedef struct epd_store* epd_store_handle;
 
 /* device_pool: device, 256-byte aligned, pool_bytes > 1 MiB; owned by the caller, must outlive
- * the store.  *out is written only on success. */
+ * the store.  *out is written only on success.  Where the pinned memory cannot be had (no GPU: a store
+ * for bookkeeping alone) create succeeds all the same and epd_store_hash asks for it again. */
 epd_status epd_store_create(void* device_pool, uint64_t pool_bytes, epd_store_handle* out);
 epd_status epd_store_destroy(epd_store_handle s);
 /* Message of the last failure on this store (of the last failed create when s == NULL). */

@@ -13,7 +13,9 @@
 //         256-byte aligned; insert drops least-recently-used entries until a first-fit range
 //         (lowest address) is free; a hit makes its entry the most recent.
 // The bookkeeping is host code and touches no device memory; only epd_store_hash and
-// epd_encode_cached launch work.
+// epd_encode_cached launch work.  Pinned memory is allocated when a store is made, beside its pool, and not
+// by its first hash: an allocation there would take 27 us of the call and break a stream capture that
+// another thread has under way.
 #include "../../include/epd_encode.h"
 
 #include <hip/hip_runtime.h>
@@ -324,7 +326,6 @@ uint64_t first_fit(const epd_store* s, uint64_t need) {
   return s->arena - pos >= need ? pos : UINT64_MAX;
 }
 
-// Taken by the store's first hash and not when it is made: the bookkeeping starts no GPU.
 hipError_t pin_partials(epd_store* s) {
   if (s->partial) return hipSuccess;
   // coherent whatever the environment says: the host reads and resets slots while the kernel runs, and
@@ -388,6 +389,7 @@ epd_status epd_store_create(void* device_pool, uint64_t pool_bytes, epd_store_ha
   epd_store* s = new epd_store();
   s->pool = (char*)device_pool;
   s->arena = (pool_bytes - kScratchBytes) / kAlign * kAlign;
+  (void)pin_partials(s);         // without a GPU (bookkeeping only) this fails; epd_store_hash asks again
   *out = s;
   return EPD_OK;
 }

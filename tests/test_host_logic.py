@@ -23,8 +23,9 @@ def fake(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("name", ["hash_plain", "bookkeeping_makes_no_runtime_calls", "partial_hashes_lie_in_coherent_memory",
-                                  "hash_with_an_uncollected_error", "hash_after_a_failed_launch", "hash_after_a_failed_wait", "hash_on_a_capturing_stream",
+@pytest.mark.parametrize("name", ["hash_plain", "pinned_memory_is_taken_at_create_and_the_bookkeeping_calls_nothing",
+                                  "partial_hashes_lie_in_coherent_memory", "hash_with_an_uncollected_error",
+                                  "hash_after_a_failed_launch", "hash_after_a_failed_wait", "hash_on_a_capturing_stream",
                                   "cached_hits_beside_an_uncollected_error"])
 def test_on_the_stand_in_runtime(fake, name):
     r = subprocess.run([sys.executable, os.path.join(HERE, "driver.py"), fake, build.library_path(), name],
