@@ -94,6 +94,19 @@ struct PlanSeg { int32_t start, len, vcol, work0; };   // first token, tokens, f
 struct PlanItem { int32_t tok, mrg, h, w; };           // first token, first merged token, grid rows and columns
 constexpr int kPlanInline = 64;     // up to this many segments and items travel as kernel arguments
 
+// Rotary role of the plan kernel: thread `thread` (of 256) of block `block` makes one entry of the table,
+// a block the entries of whole tokens.  The position in the table is 64-bit: tokens * pairs passes
+// 2^31 long before the table fills a card.
+struct RotEntry { int tok, pair; size_t at; };
+__host__ __device__ inline int rot_tokens_per_block(int pairs) { return 256 / pairs; }   // pairs <= 64
+__host__ __device__ inline bool rot_entry(int T, int pairs, int block, int thread, RotEntry& e) {
+  const int t = thread / pairs;
+  e.tok = block * rot_tokens_per_block(pairs) + t;
+  e.pair = thread - t * pairs;
+  e.at = (size_t)e.tok * pairs + e.pair;
+  return t < rot_tokens_per_block(pairs) && e.tok < T;
+}
+
 struct PlanArgs {
   int T, Tm, num_items, num_segments, num_work;
   const PlanSeg* seg;           // device tables, read when one of them exceeds kPlanInline

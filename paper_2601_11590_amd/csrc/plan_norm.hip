@@ -21,7 +21,7 @@ template <typename E> __device__ __forceinline__ int last_not_after(const E* t, 
 }
 
 // Everything a call derives from its metadata, in one launch; a block has one of four roles:
-//   rot    (cos, sin) of 256 (token, pair) entries, in double
+//   rot    (cos, sin) of the (token, pair) entries of 256 / pairs tokens, in double
 //   work   bf16: one entry of the attention work list and the vt columns of its tokens; fp32: 256
 //          entries (no vt)
 //   merge  the source tokens of 256 merged tokens, window rows then columns
@@ -44,14 +44,14 @@ __global__ __launch_bounds__(256) void plan_kernel(PlanArgs p) {
   }
   int b = blockIdx.x;
   if (b < p.rot_blocks) {
-    const int e = b * 256 + tid, tok = e / p.pairs, q = e - tok * p.pairs;
-    if (tok >= p.T) return;
-    const PlanItem& d = item[last_not_after(item, p.num_items, tok, &PlanItem::tok)];
-    const int local = tok - d.tok, t = local / (d.h * d.w), rem = local - t * d.h * d.w, r = rem / d.w;
-    const int ax = p.pair_axis[q], coord = ax == 0 ? t : ax == 1 ? r : rem - r * d.w;
+    RotEntry e;
+    if (!rot_entry(p.T, p.pairs, b, tid, e)) return;
+    const PlanItem& d = item[last_not_after(item, p.num_items, e.tok, &PlanItem::tok)];
+    const int local = e.tok - d.tok, t = local / (d.h * d.w), rem = local - t * d.h * d.w, r = rem / d.w;
+    const int ax = p.pair_axis[e.pair], coord = ax == 0 ? t : ax == 1 ? r : rem - r * d.w;
     double sn, cs;
-    sincos((double)coord * p.pair_freq[q], &sn, &cs);
-    p.rot[e] = make_float2((float)cs, (float)sn);
+    sincos((double)coord * p.pair_freq[e.pair], &sn, &cs);
+    p.rot[e.at] = make_float2((float)cs, (float)sn);
     return;
   }
   b -= p.rot_blocks;
@@ -88,7 +88,8 @@ __global__ __launch_bounds__(256) void plan_kernel(PlanArgs p) {
 }
 
 void launch_plan(PlanArgs& p, hipStream_t s) {
-  p.rot_blocks = p.pairs > 0 ? (int)(((long)p.T * p.pairs + 255) / 256) : 0;
+  const int rot_tokens = p.pairs > 0 ? rot_tokens_per_block(p.pairs) : 1;
+  p.rot_blocks = p.pairs > 0 ? (p.T + rot_tokens - 1) / rot_tokens : 0;
   p.work_blocks = p.vcol ? p.num_work : (p.num_work + 255) / 256;
   p.merge_blocks = p.merge > 1 ? (p.Tm + 255) / 256 : 0;
   p.pad_blocks = p.vt ? p.num_segments * ((p.hidden + 3) / 4) : 0;
