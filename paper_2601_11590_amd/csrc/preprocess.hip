@@ -32,6 +32,10 @@ __device__ __forceinline__ Tap tap(int j, int n_in, int n_out, float inv) {
   return t;
 }
 
+// (1 - w) a + w b, the second product rounded first: spelled out, so that the outputs do not follow
+// what the compiler makes of the sum
+__device__ __forceinline__ float blend(float w, float a, float b) { return fmaf(1.0f - w, a, w * b); }
+
 typedef uint16_t u16_any __attribute__((aligned(1)));
 
 // two neighbouring elements of the output
@@ -163,8 +167,8 @@ __global__ __launch_bounds__(512) void preprocess_kernel(PrepArgs a) {
         float line[2];
 #pragma unroll
         for (int r = 0; r < 2; ++r)
-          line[r] = fmaf(wx[i], (float)(q[k][i][r] >> 8), (1.0f - wx[i]) * (float)(q[k][i][r] & 0xff));
-        v[i] = fmaf(fmaf(ty.w1, line[1], (1.0f - ty.w1) * line[0]), ac[k], bc[k]);
+          line[r] = blend(wx[i], (float)(q[k][i][r] & 0xff), (float)(q[k][i][r] >> 8));
+        v[i] = fmaf(blend(ty.w1, line[0], line[1]), ac[k], bc[k]);
       }
       store_pair<BF16>(out, o, v[0], v[1]);
       out += slab_bytes;

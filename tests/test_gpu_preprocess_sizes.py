@@ -58,3 +58,37 @@ def test_tap_weights_are_the_correctly_rounded_quotients(axis, n_in, patches, pa
     want = (want.astype(np.float64) * float(scale)).astype(np.float32)
     want = np.broadcast_to(want[None, None, :] if axis == "columns" else want[None, :, None], img.shape)
     assert np.array_equal(img, want), "%d of %d differ" % ((img != want).sum(), img.size)
+
+
+@pytest.mark.parametrize("patch,grid,size", [(4, (1, 10, 12), (61, 25)), (14, (1, 4, 6), (100, 151)), (16, (1, 6, 4), (7, 300))])
+def test_interpolation_rounds_where_it_is_written_to(patch, grid, size):
+    # fp32 outputs bit for bit: (1 - w) a + w b with w b rounded first, along the columns, then the rows, then
+    # scale and shift.  Each step is a product of fp32 values (48 bits) plus an fp32 value, which
+    # 64-bit significands hold; where an axis ends, its last pixel counts alone along the columns
+    cfg = make("f32", patch=patch, tp=1)
+    rng = np.random.default_rng(patch)
+    px = rng.integers(0, 256, size=(3, 1) + size, dtype=np.uint8)
+    gw, layers = W.all_weights(cfg)
+    enc = B.EpdEncoder(cfg, gw, layers, max_tokens=W.num_tokens([grid]), max_segments=1, max_items=1)
+    mean, std = np.float32([0.48, 0.46, 0.41]), np.float32([0.27, 0.26, 0.28])
+    got = enc.preprocess(torch.from_numpy(px).reshape(-1).to("cuda:0"), [size], [grid], mean.tolist(), std.tolist()).cpu().numpy()
+    enc.close()
+    fma = lambda a, b, c: (a.astype(np.longdouble) * b + c).astype(np.float32)
+    blend = lambda w, a, b: fma(np.float32(1) - w, a, w * b)
+
+    def taps(n_in, n_out):
+        num = np.maximum((2 * np.arange(n_out) + 1) * n_in - n_out, 0)
+        i0 = np.minimum(num // (2 * n_out), n_in - 1)
+        return i0, np.minimum(i0 + 1, n_in - 1), (num % (2 * n_out)).astype(np.float32) / np.float32(2 * n_out)
+
+    x0, x1, wx = taps(size[1], grid[2] * patch)
+    wx = np.where(x0 == x1, np.float32(1), wx)
+    y0, y1, wy = taps(size[0], grid[1] * patch)
+    f = px[:, 0].astype(np.float32)
+    line = blend(wx[None, None, :], f[:, :, x0], f[:, :, x1])
+    val = blend(wy[None, :, None], line[:, y0], line[:, y1])
+    a = np.float32(1.0 / (255.0 * std.astype(np.float64)))
+    b = np.float32(-mean.astype(np.float64) / std.astype(np.float64))
+    want = fma(val, a[:, None, None], b[:, None, None])
+    img = got.reshape(grid[1], grid[2], 3, patch, patch).transpose(2, 0, 3, 1, 4).reshape(want.shape)
+    assert np.array_equal(img, want), "%d of %d differ" % ((img != want).sum(), img.size)
