@@ -94,6 +94,10 @@ struct PlanSeg { int32_t start, len, vcol, work0; };   // first token, tokens, f
 struct PlanItem { int32_t tok, mrg, h, w; };           // first token, first merged token, grid rows and columns
 constexpr int kPlanInline = 64;     // up to this many segments and items travel as kernel arguments
 
+// A launch takes fewer than 2^32 threads along x.  Kernels whose threads could be more -- several per token
+// or per (segment, channel) -- launch at most this many blocks (of up to 512 threads) at a time.
+constexpr int kMaxGrid = 1 << 22;
+
 // Rotary role of the plan kernel: thread `thread` (of 256) of block `block` makes one entry of the table,
 // a block the entries of whole tokens.  The position in the table is 64-bit: tokens * pairs passes
 // 2^31 long before the table fills a card.
@@ -154,7 +158,7 @@ void launch_permute_qkv(const void* src_w, const void* src_b, void* dst_w, void*
                         int hidden, int num_heads, int head_dim, int elem_bytes, hipStream_t s);
 
 // ---------------------------------------------------------------- raw pixels -> patch rows
-constexpr int kPrepItems = 32;      // items per launch (descriptors travel as kernel arguments)
+constexpr int kPrepItems = 32;      // items per set of arguments (descriptors travel as kernel arguments)
 constexpr int kPrepChannels = 8;
 struct PrepItem {
   long long src_off;     // byte offset of the item's first pixel
@@ -171,6 +175,7 @@ struct PrepArgs {
   void* out;             // [T, pdim] bf16 or fp32
   int out_bf16;
   int n_items, channels, patch, tp, pdim;
+  int first_block;                          // of this launch (set by the launcher)
   int block_tokens, per_token;              // tokens per block, threads per token (set by the launcher)
   float inv_per_token, inv_per_row;         // 1 / threads per token, 1 / threads per patch row (set by the launcher)
   float a[kPrepChannels], b[kPrepChannels];    // value = pixel * a[c] + b[c]

@@ -301,11 +301,12 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_kernel(AttnArgs a) {
 bool launch_attn_f32(const AttnArgs& a, hipStream_t s) {
   if (a.num_work <= 0) return true;
   if (a.q_tile != F32_BQ) return false;
-  dim3 grid(a.num_work, a.num_heads);
 #define EPD_ATTN_F32(DH)                                                                             \
   case DH: {                                                                                         \
     constexpr int NW = DH <= 64 ? 8 : 4;                                                             \
-    hipLaunchKernelGGL((attn_f32_kernel<DH, NW>), grid, dim3(64 * NW), 0, s, a);                     \
+    for (AttnArgs c = a; c.num_work > 0; c.num_work -= kMaxGrid, c.work += kMaxGrid)                 \
+      hipLaunchKernelGGL((attn_f32_kernel<DH, NW>), dim3(std::min(c.num_work, kMaxGrid), a.num_heads), \
+                         dim3(64 * NW), 0, s, c);                                                    \
     return true;                                                                                     \
   }
   switch (a.head_dim) {

@@ -5,6 +5,8 @@
 // accesses and wave-level (64 lane) reductions, no matrix cores.
 #include "epd_internal.h"
 
+#include <algorithm>
+
 namespace epd {
 
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
@@ -27,6 +29,7 @@ template <typename E> __device__ __forceinline__ int last_not_after(const E* t, 
 //   merge  the source tokens of 256 merged tokens, window rows then columns
 //   pad    clears the columns of vt between a segment's end and the next (aligned) start, four
 //          channel rows per block: attention multiplies them by exact zeros, so they must be finite
+// The rot and pad roles take at most kMaxGrid blocks, which stride over larger tables.
 // Up to kPlanInline segments and items the tables are kernel arguments, copied to LDS before they
 // are searched.  Bound: latency.  As a copy of the metadata (3 us) plus three kernels, one thread per
 // token for all its pairs (15 us), this step cost a call 24 us more: one 256-token image 3.9 us now.
@@ -44,14 +47,15 @@ __global__ __launch_bounds__(256) void plan_kernel(PlanArgs p) {
   }
   int b = blockIdx.x;
   if (b < p.rot_blocks) {
-    RotEntry e;
-    if (!rot_entry(p.T, p.pairs, b, tid, e)) return;
-    const PlanItem& d = item[last_not_after(item, p.num_items, e.tok, &PlanItem::tok)];
-    const int local = e.tok - d.tok, t = local / (d.h * d.w), rem = local - t * d.h * d.w, r = rem / d.w;
-    const int ax = p.pair_axis[e.pair], coord = ax == 0 ? t : ax == 1 ? r : rem - r * d.w;
-    double sn, cs;
-    sincos((double)coord * p.pair_freq[e.pair], &sn, &cs);
-    p.rot[e.at] = make_float2((float)cs, (float)sn);
+    for (RotEntry e; b * rot_tokens_per_block(p.pairs) < p.T; b += p.rot_blocks) {
+      if (!rot_entry(p.T, p.pairs, b, tid, e)) continue;
+      const PlanItem& d = item[last_not_after(item, p.num_items, e.tok, &PlanItem::tok)];
+      const int local = e.tok - d.tok, t = local / (d.h * d.w), rem = local - t * d.h * d.w, r = rem / d.w;
+      const int ax = p.pair_axis[e.pair], coord = ax == 0 ? t : ax == 1 ? r : rem - r * d.w;
+      double sn, cs;
+      sincos((double)coord * p.pair_freq[e.pair], &sn, &cs);
+      p.rot[e.at] = make_float2((float)cs, (float)sn);
+    }
     return;
   }
   b -= p.rot_blocks;
@@ -79,20 +83,23 @@ __global__ __launch_bounds__(256) void plan_kernel(PlanArgs p) {
     return;
   }
   b -= p.merge_blocks;
-  const int rows = (p.hidden + 3) / 4, sg = b / rows, row = (b - sg * rows) * 4 + (tid >> 6);
-  if (row >= p.hidden) return;
-  const PlanSeg& s = seg[sg];
-  uint16_t* vt = (uint16_t*)p.vt + (size_t)row * p.vt_stride;
-  const int end = s.vcol + (s.len + kVtAlign - 1) / kVtAlign * kVtAlign;
-  for (int c = s.vcol + s.len + (tid & 63); c < end; c += 64) vt[c] = 0;
+  const int rows = (p.hidden + 3) / 4;
+  for (; b < p.num_segments * rows; b += p.pad_blocks) {
+    const int sg = b / rows, row = (b - sg * rows) * 4 + (tid >> 6);
+    if (row >= p.hidden) continue;
+    const PlanSeg& s = seg[sg];
+    uint16_t* vt = (uint16_t*)p.vt + (size_t)row * p.vt_stride;
+    const int end = s.vcol + (s.len + kVtAlign - 1) / kVtAlign * kVtAlign;
+    for (int c = s.vcol + s.len + (tid & 63); c < end; c += 64) vt[c] = 0;
+  }
 }
 
 void launch_plan(PlanArgs& p, hipStream_t s) {
   const int rot_tokens = p.pairs > 0 ? rot_tokens_per_block(p.pairs) : 1;
-  p.rot_blocks = p.pairs > 0 ? (p.T + rot_tokens - 1) / rot_tokens : 0;
+  p.rot_blocks = p.pairs > 0 ? std::min((p.T + rot_tokens - 1) / rot_tokens, kMaxGrid) : 0;
   p.work_blocks = p.vcol ? p.num_work : (p.num_work + 255) / 256;
   p.merge_blocks = p.merge > 1 ? (p.Tm + 255) / 256 : 0;
-  p.pad_blocks = p.vt ? p.num_segments * ((p.hidden + 3) / 4) : 0;
+  p.pad_blocks = p.vt ? std::min(p.num_segments * ((p.hidden + 3) / 4), kMaxGrid) : 0;   // product: the vt buffer holds 1 KB per unit of it
   hipLaunchKernelGGL(plan_kernel, dim3(p.rot_blocks + p.work_blocks + p.merge_blocks + p.pad_blocks), dim3(256), 0, s, p);
 }
 

@@ -13,6 +13,8 @@
 // so that equal sizes copy pixels untouched and the weights carry a single rounding.
 #include "epd_internal.h"
 
+#include <algorithm>
+
 namespace epd {
 
 struct Tap { int i0; float w1; };
@@ -84,7 +86,7 @@ __global__ __launch_bounds__(512) void preprocess_kernel(PrepArgs a) {
   // contiguous eighth of the blocks, so that the neighbouring patches that share a 128-byte line
   // of source pixels fetch it through one L2 instead of eight
   const int nb = gridDim.x;
-  const int vb = (blockIdx.x & 7) * (nb >> 3) + min((int)(blockIdx.x & 7), nb & 7) + (blockIdx.x >> 3);
+  const int vb = a.first_block + (blockIdx.x & 7) * (nb >> 3) + min((int)(blockIdx.x & 7), nb & 7) + (blockIdx.x >> 3);
   int it = 0;
 #pragma unroll
   for (int step = kPrepItems / 2; step > 0; step >>= 1)
@@ -191,10 +193,13 @@ void launch_preprocess(PrepArgs& a, hipStream_t s) {
     d.inv_cols = 1.0f / (float)d.w;
     blocks += (long long)d.t * d.slice_blocks;
   }
-  if (blocks <= 0) return;
   const dim3 threads((a.block_tokens * a.per_token + 63) / 64 * 64);
-  if (a.out_bf16) hipLaunchKernelGGL(preprocess_kernel<true>, dim3((unsigned)blocks), threads, 0, s, a);
-  else hipLaunchKernelGGL(preprocess_kernel<false>, dim3((unsigned)blocks), threads, 0, s, a);
+  for (long long b = 0; b < blocks; b += kMaxGrid) {
+    a.first_block = (int)b;
+    const dim3 grid((unsigned)std::min(blocks - b, (long long)kMaxGrid));
+    if (a.out_bf16) hipLaunchKernelGGL(preprocess_kernel<true>, grid, threads, 0, s, a);
+    else hipLaunchKernelGGL(preprocess_kernel<false>, grid, threads, 0, s, a);
+  }
 }
 
 }  // namespace epd

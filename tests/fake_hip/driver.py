@@ -199,6 +199,53 @@ def cached_hits_beside_an_uncollected_error(fake, lib):
             assert e.status == want, e
 
 
+def launches_stay_within_the_thread_limit(fake, lib):
+    B = binding()
+
+    def check(what, names):
+        seen = set()
+        for name, grid, block in launches(fake):
+            seen |= {n for n in names if n in name}
+            assert all(g * b < 2 ** 32 for g, b in zip(grid, block)), (what, name, grid, block)
+        assert seen == set(names), (what, seen)
+
+    one = dict(name="x", num_layers=1, mlp_dim=64, patch=4, temporal_patch=1, out_dim=64, merge=1, norm="rmsnorm")
+    # fp32, 2^26 - 256 tokens with 64 rotary pairs each
+    cfg = W.EncoderConfig(dtype="f32", hidden=128, num_heads=1, head_dim=128, rope="2d", rope_pairs=(0, 32, 32), **one)
+    T = 2 ** 26 - 256
+    h = encoder(cfg, T, 1024, 1)
+    fake.fake_forget()
+    B.epd_encode(h, POOL, np.linspace(0, T, 1025).astype(np.int32), [(T // 2 ** 8, 2 ** 4, 2 ** 4)], POOL, None)
+    check("rotary table", ["plan_kernel", "attn_f32_kernel", "norm_kernel"])
+    # fp32, 4.5 million segments of two tokens
+    cfg = W.EncoderConfig(dtype="f32", hidden=8, num_heads=1, head_dim=8, rope="2d", rope_pairs=(0, 2, 2), **one)
+    S = 4500000
+    h = encoder(cfg, 2 * S, S, 1)
+    fake.fake_forget()
+    B.epd_encode(h, POOL, np.arange(S + 1, dtype=np.int32) * 2, [(S, 1, 2)], POOL, None)
+    check("segments", ["plan_kernel", "attn_f32_kernel"])
+    assert sum(g[0] for n, g, _ in launches(fake) if "attn_f32" in n) == S
+    # bf16, 65 536 segments of two tokens at hidden 1024: as many (segment, four channels) pairs as blocks of 256 threads may be
+    cfg = W.EncoderConfig(dtype="bf16", hidden=1024, num_heads=16, head_dim=64, rope="2d", rope_pairs=(0, 16, 16), **one)
+    S = 65536
+    h = encoder(cfg, 2 * S, S, 1)
+    fake.fake_forget()
+    B.epd_encode(h, POOL, np.arange(S + 1, dtype=np.int32) * 2, [(S, 1, 2)], POOL, None)
+    check("pads", ["plan_kernel", "attn_bf16", "gemm_bf16"])
+    # preprocessing: 33 slices of 512 x 512 patches of 32 x 32 pixels, a block of 512 threads each
+    cfg = W.EncoderConfig(dtype="bf16", hidden=64, num_heads=1, head_dim=64, rope="2d", rope_pairs=(0, 16, 16), in_channels=1,
+                          **dict(one, patch=32))
+    T = 33 * 512 * 512
+    h = encoder(cfg, T, 1, 2)
+    fake.fake_forget()
+    B.epd_preprocess(h, POOL, [(16384, 16384)], [(33, 512, 512)], [0.5], [0.25], POOL, None)
+    check("patches", ["preprocess_kernel"])
+    assert sum(g[0] for n, g, _ in launches(fake)) == T
+    fake.fake_forget()
+    B.epd_preprocess(h, POOL, [(50, 60), (64, 64)], [(1, 3, 5), (1, 2, 2)], [0.5], [0.25], POOL, None)
+    assert [l[1:] for l in launches(fake)] == [((19, 1, 1), (512, 1, 1))]
+
+
 if __name__ == "__main__":
     globals()[sys.argv[3]](*load(sys.argv[1], sys.argv[2]))
     print("passed", sys.argv[3])

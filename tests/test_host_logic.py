@@ -26,7 +26,7 @@ def fake(tmp_path_factory):
 @pytest.mark.parametrize("name", ["hash_plain", "pinned_memory_is_taken_at_create_and_the_bookkeeping_calls_nothing",
                                   "partial_hashes_lie_in_coherent_memory", "hash_with_an_uncollected_error",
                                   "hash_after_a_failed_launch", "hash_after_a_failed_wait", "hash_on_a_capturing_stream",
-                                  "cached_hits_beside_an_uncollected_error"])
+                                  "cached_hits_beside_an_uncollected_error", "launches_stay_within_the_thread_limit"])
 def test_on_the_stand_in_runtime(fake, name):
     r = subprocess.run([sys.executable, os.path.join(HERE, "driver.py"), fake, build.library_path(), name],
                        stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=300)
