@@ -86,7 +86,7 @@ __global__ __launch_bounds__(512) void preprocess_kernel(PrepArgs a) {
   // contiguous eighth of the blocks, so that the neighbouring patches that share a 128-byte line
   // of source pixels fetch it through one L2 instead of eight
   const int nb = gridDim.x;
-  const int vb = a.first_block + (blockIdx.x & 7) * (nb >> 3) + min((int)(blockIdx.x & 7), nb & 7) + (blockIdx.x >> 3);
+  const int vb = (blockIdx.x & 7) * (nb >> 3) + min((int)(blockIdx.x & 7), nb & 7) + (blockIdx.x >> 3);
   int it = 0;
 #pragma unroll
   for (int step = kPrepItems / 2; step > 0; step >>= 1)
@@ -195,7 +195,10 @@ void launch_preprocess(PrepArgs& a, hipStream_t s) {
   }
   const dim3 threads((a.block_tokens * a.per_token + 63) / 64 * 64);
   for (long long b = 0; b < blocks; b += kMaxGrid) {
-    a.first_block = (int)b;
+    // block numbers of an item count from the launch's first block (first_block as an argument took 1 % of
+    // the clips' time: 33.45 -> 33.78 us)
+    if (b > 0)
+      for (int i = 0; i < a.n_items; ++i) a.item[i].blk_off -= kMaxGrid;
     const dim3 grid((unsigned)std::min(blocks - b, (long long)kMaxGrid));
     if (a.out_bf16) hipLaunchKernelGGL(preprocess_kernel<true>, grid, threads, 0, s, a);
     else hipLaunchKernelGGL(preprocess_kernel<false>, grid, threads, 0, s, a);
