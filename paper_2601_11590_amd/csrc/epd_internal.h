@@ -55,7 +55,7 @@ struct GemmArgs {
   void* xb;             // bf16 [M, ldxb] or nullptr
   int ldxb;
   float* stats_out;     // [M, stats_n] or nullptr (requires N % 128 == 0)
-  //   consumer (any epilogue): the accumulator of row m is multiplied by
+  //   consumer (EPI_GELU, EPI_QKV): the accumulator of row m is multiplied by
   //   rsqrt(sum_j stats_in[m][j] * stats_inv_dim + stats_eps) before bias / rotary / activation
   const float* stats_in;  // [M, stats_n] or nullptr
   int stats_n;
@@ -175,7 +175,6 @@ struct PrepArgs {
   void* out;             // [T, pdim] bf16 or fp32
   int out_bf16;
   int n_items, channels, patch, tp, pdim;
-  int first_block;                          // of this launch (set by the launcher)
   int block_tokens, per_token;              // tokens per block, threads per token (set by the launcher)
   float inv_per_token, inv_per_row;         // 1 / threads per token, 1 / threads per patch row (set by the launcher)
   float a[kPrepChannels], b[kPrepChannels];    // value = pixel * a[c] + b[c]

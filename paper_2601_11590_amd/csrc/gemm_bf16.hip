@@ -287,7 +287,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int m0, const
   // the shadow of the main loop, and kept in LDS behind the stages and the staging area (the
   // barriers of the main loop make it visible to the epilogue).
   float* const row_scale = (float*)(lds + T::LDS_BYTES + lds_extra<T, EPI>());
-  const bool scaled = g.stats_in != nullptr;
+  constexpr bool CONSUMER = EPI == EPI_GELU || EPI == EPI_QKV;
+  const bool scaled = CONSUMER && g.stats_in != nullptr;
   // The order of the additions is the same whichever tile left the sums and whichever takes them:
   // sums of 64 columns (stats_n * 64 = K) are added in pairs first, which is how a tile of 128 columns
   // makes one, then 8 segments (hidden 1024) as a tree, any other number one after the other.
@@ -311,7 +312,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int m0, const
       const float* sp = g.stats_in + (size_t)min(m0 + r, g.M - 1) * g.stats_n;
       auto segment = [&](int j) { return halves ? sp[2 * j] + sp[2 * j + 1] : sp[j]; };
       float ss = 0.f;
-      if (g.K == 1024) {
+      if (SV == 2 && g.K == 1024) {                      // 16 sums in front of a large tile
         ss = ((segment(0) + segment(1)) + (segment(2) + segment(3))) + ((segment(4) + segment(5)) + (segment(6) + segment(7)));
       } else {
         const int n = halves ? g.stats_n / 2 : g.stats_n;
@@ -717,7 +718,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int m0, const
           if (g.rot) {
             const float4 cs = tab_lds ? *(const float4*)(tab + ml * trb + pr * 8)
                                       : *(const float4*)(g.rot + (size_t)m * g.rot_pairs + pr);
-            const bool sin_last = BM >= 128 ? i == TM - 1 && sw == SR / RPS - 1 : (m & 127) >= 120;
+            const bool sin_last = i == TM - 1 && sw == SR / RPS - 1 && (BM >= 128 || ((m0 & 64) && ml >= 56));
             rotate_pair(v0, v1, cs.x, cs.y, sin_last);
             rotate_pair(v2, v3, cs.z, cs.w, sin_last);
           }
