@@ -227,7 +227,8 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_kernel(AttnArgs a) {
 #pragma unroll
       for (int i = 0; i < DC; ++i) {
         const int d = 16 * i + 4 * g4;
-        kf[b][i] = *(const f32x4*)(kr + (d < DH ? d : 0));   // beyond DH it meets zeros of q
+        kf[b][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (d < DH) kf[b][i] = *(const f32x4*)(kr + d);
       }
     }
 #pragma unroll
@@ -240,6 +241,7 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_kernel(AttnArgs a) {
       }
     f32x4 s[2];
     float mt = -INFINITY;
+    const float m0 = m;
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
       s[b] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -255,10 +257,12 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_kernel(AttnArgs a) {
     }
     mt = fmaxf(mt, __shfl_xor(mt, 16));
     mt = fmaxf(mt, __shfl_xor(mt, 32));
-    const float mn = fmaxf(m, mt);
-    const float alpha = expf(m - mn);      // first keys: exp(-inf) = 0
+    m = fmaxf(m, mt);
+    // scores may all be -inf (a product beyond the range): those of a wave's share of the keys, of weight
+    // zero beside the other waves' -- the maximum subtracted must be finite
+    const float mn = m == -INFINITY ? 0.f : m;
+    const float alpha = expf(m0 - mn);     // first keys: exp(-inf) = 0
     l *= alpha;
-    m = mn;
 #pragma unroll
     for (int i = 0; i < DC; ++i) o[i] *= alpha;
 #pragma unroll
