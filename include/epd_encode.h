@@ -269,8 +269,9 @@ epd_status epd_encode_debug_hidden(epd_handle h, void* out_T_by_D_f32, void* str
 
 /* Tuning and test hook: force one variant of the bf16 kernels for all following epd_encode calls
  * of this handle (ignored by the fp32 path).
- *   gemm_tile    -1 = the library's choice per GEMM; 0 (256x256), 2 (256x128), 4 (128x128) or
- *                5 (320x256) = that output tile for every GEMM that can take it
+ *   gemm_tile    -1 = the library's choice per GEMM; 0 (256x256), 2 (256x128), 4 (128x128),
+ *                5 (320x256), 7 (64x64) or 8 (64x128) = that output tile for every GEMM that can
+ *                take it
  *   attn_groups  0 = the library's choice; 1 = 128, 2 = 256 query rows per block of the attention
  *                kernel (256: two 32-row groups per wave for head_dim <= 64, eight waves of one
  *                group for larger head dims); EPD_ERR_UNSUPPORTED where a setting has no kernel

@@ -785,8 +785,8 @@ epd_status epd_encode_cached(epd_handle h, epd_store_handle s, uint64_t model_sa
 
 epd_status epd_encode_set_tuning(epd_handle h, int32_t gemm_tile, int32_t attn_groups) {
   if (!h) { g_create_error = "handle is NULL"; return EPD_ERR_INVALID_ARG; }
-  if (gemm_tile != -1 && gemm_tile != 0 && gemm_tile != 2 && gemm_tile != 4 && gemm_tile != 5) {
-    h->err = fmt("gemm_tile %d: -1 (automatic), 0, 2, 4 or 5", gemm_tile); return EPD_ERR_INVALID_ARG;
+  if (gemm_tile != -1 && !gemm_bf16_tile_known(gemm_tile)) {
+    h->err = fmt("gemm_tile %d: -1 (automatic), 0, 2, 4, 5, 7 or 8", gemm_tile); return EPD_ERR_INVALID_ARG;
   }
   if (attn_groups < 0 || attn_groups > 2) { h->err = fmt("attn_groups %d: 0 (automatic), 1 or 2", attn_groups); return EPD_ERR_INVALID_ARG; }
   if (attn_groups && attn_q_tile(h->cfg.dtype == EPD_BF16, h->cfg.head_dim, 1, attn_groups) <= 0) {

@@ -143,6 +143,7 @@ void launch_gemm_bf16(const GemmArgs& g, hipStream_t s);
 // covers when the rest is left to a second launch of 128 x 128 tiles (0 = one launch covers all).
 // Reads M, N, epilogue, qk_cols, gather and tile_cfg of g.
 void plan_gemm_bf16(const GemmArgs& g, int compute_units, int* tile_rows, int* tile_cols, int* body_rows);
+bool gemm_bf16_tile_known(int tile);          // tile variants: 0, 2, 4, 5, 7, 8
 int gemm_bf16_stat_cols(const GemmArgs& g);   // columns per sum of squares that the EPI_RESIDUAL launch of g leaves (64 or 128)
 bool launch_attn_bf16(const AttnArgs& a, hipStream_t s);  // false: head_dim not covered
 // query rows per work item for segments up to max_seg_len (0 = unsupported head_dim);

@@ -913,7 +913,7 @@ using T8 = Tile<64, 128, 64, 2, 2, 2, 1, 3, true>;   // 4 waves, 32x64 wave tile
 // So the small tile wins short-K GEMMs with a heavy epilogue (the attention output projection at
 // hidden 1024), the 320 x 256 tile gains with short K and on grids where it needs fewer rounds,
 // and at K >= 3200 the two large tiles are equal.
-static bool known_tile(int t) { return t == 0 || t == 2 || t == 4 || t == 5 || t == 7 || t == 8; }
+bool gemm_bf16_tile_known(int t) { return t == 0 || t == 2 || t == 4 || t == 5 || t == 7 || t == 8; }
 struct TileShape { int bm, bn, blocks, cfg; double alpha, eps[4]; };   // eps indexed by Epilogue
 // Few rows: 64 x 128 and 64 x 64 tiles, whose stages are refilled three and two steps ahead between
 // the matrix instructions.  Their main loops are slower still per output (LDS reads), but a call
@@ -972,7 +972,7 @@ static TilePlan plan_tiles(int M, int N, int K, int epi, bool may_split, long cu
 template <int EPI, int OUT, bool GATHER>
 static void launch_epi(const GemmArgs& g, hipStream_t s) {
   int t = g.tile_cfg > 0 ? g.tile_cfg - 1 : -1;   // tile_cfg: set by the tuning hook of the C ABI, or by a split
-  if (!known_tile(t)) t = plan_tiles(g.M, g.N, g.K, g.epilogue, false, g.compute_units > 0 ? g.compute_units : num_cus()).tile;
+  if (!gemm_bf16_tile_known(t)) t = plan_tiles(g.M, g.N, g.K, g.epilogue, false, g.compute_units > 0 ? g.compute_units : num_cus()).tile;
   if (EPI == EPI_QKV && (t == 0 || t == 5) && g.qk_cols % 256 != 0) t = 2;
   switch (t) {
     case 0: launch_cfg<T0, EPI, OUT, GATHER>(g, s); break;
@@ -997,7 +997,7 @@ static bool may_split_rows(const GemmArgs& g) {
 void plan_gemm_bf16(const GemmArgs& g, int compute_units, int* tile_rows, int* tile_cols, int* body_rows) {
   const long cus = compute_units > 0 ? compute_units : (g.compute_units > 0 ? g.compute_units : num_cus());
   int t = g.tile_cfg > 0 ? g.tile_cfg - 1 : -1, body = 0;
-  if (!known_tile(t)) {
+  if (!gemm_bf16_tile_known(t)) {
     const TilePlan p = plan_tiles(g.M, g.N, g.K, g.epilogue, may_split_rows(g), cus);
     t = p.tile; body = p.body_rows;
   }

@@ -238,6 +238,13 @@ def test_gemm_launch_planner_on_the_benchmark_shapes():
     assert plan(73896, 1024, 4096, R) == (320, 256, 0)
     # Q | K columns that do not end on a 256-column boundary: the 256 x 128 tile, never cut
     assert plan(13540, 960, 320, Q, 640) == (256, 128, 0)
+    # few tokens: 64-row tiles while they fit two rounds of blocks -- one 448 x 448 image (784 tokens), four, and
+    # the point where 128 x 128 tiles fill the chip themselves
+    assert plan(784, 1024, 1024, R) == plan(784, 1024, 4096, R) == (64, 64, 0)
+    assert plan(784, 3072, 1024, Q, 2048) == plan(784, 4096, 1024, G) == (64, 128, 0)
+    assert plan(196, 4096, 4096) == (64, 64, 0)
+    assert plan(3136, 1024, 1024, R) == plan(3136, 1024, 4096, R) == (64, 128, 0)
+    assert plan(3136, 3072, 1024, Q, 2048) == (256, 256, 0) and plan(4900, 1024, 1024, R) == (128, 128, 0)
     # a QKV projection that is cut (9124 x 2304 at K = 768)
     assert plan(9124, 2304, 768, Q, 1536) == (256, 256, 7168)
     # a chip with fewer units changes the rounds, hence the plan

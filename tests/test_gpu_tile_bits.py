@@ -6,7 +6,9 @@ sums of squares are added must not depend on the tile either.)"""
 import pytest
 import torch
 
+from oracle import vit_encode as O
 from paper_2601_11590_amd import binding as B, workloads as W
+from parity_util import check
 from test_gpu_parity import case, small
 
 pytestmark = pytest.mark.gpu
@@ -32,4 +34,26 @@ def test_few_row_tiles_give_the_bits_of_the_128_tile(kw, grids):
     want = enc.encode(p, cu, grid)
     torch.cuda.synchronize()
     assert torch.equal(got, want), "%d of %d values differ" % (int((got != want).sum()), got.numel())
+    enc.close()
+
+
+# K steps of 64 around the turns of a ring of three or four stages: 2 ... 7, and one (patch rows of 48 elements);
+# merger pieces of whole steps and not (96, 72), Q | K columns that do not end on a 128-column boundary (96, 72)
+@pytest.mark.parametrize("hidden,heads", [(128, 2), (192, 3), (256, 4), (320, 5), (384, 6), (448, 7), (96, 3), (72, 1)])
+@pytest.mark.parametrize("act,norm", [("gelu_erf", "rmsnorm"), ("gelu_tanh", "layernorm")])
+def test_forced_64_row_tiles_give_the_bits_of_the_128_tile(hidden, heads, act, norm):
+    d = hidden // heads
+    cfg = small("bf16", hidden=hidden, num_heads=heads, head_dim=d, rope_pairs=(0, d // 4, d // 2 - d // 4), mlp_dim=hidden + 72, act=act, norm=norm, out_dim=200)
+    grids = [(1, 14, 18), (1, 2, 2), (1, 6, 10)]
+    gw, layers, patches, cu, grid = case(cfg, grids)
+    ref = O.encode(cfg, gw, layers, patches, cu, grid)
+    enc = B.EpdEncoder(cfg, gw, layers, max_tokens=patches.shape[0], max_segments=len(grids), max_items=len(grids))
+    p = B.to_device_patches(patches, cfg.dtype)
+    out = {}
+    for tile in (4, 7, 8):
+        enc.set_tuning(tile, 0)
+        out[tile] = enc.encode(p, cu, grid).clone()
+    torch.cuda.synchronize()
+    check(cfg, out[7].float().cpu().numpy(), ref, "64 x 64")
+    assert torch.equal(out[7], out[4]) and torch.equal(out[8], out[4])
     enc.close()
