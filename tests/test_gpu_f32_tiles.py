@@ -1,0 +1,43 @@
+"""GPU parity of every form of the fp32 GEMM: 16 x 16 tiles split over eight and four waves, 32 x 32 tiles split
+over four, 64 x 64 blocks of four wave tiles, each with 16-byte loads and -- where a row length, K or an
+address is not a multiple of 16 bytes -- with 4-byte ones; rows and columns that end inside a tile.
+Tolerance as for every fp32 case (max abs error <= 1e-4)."""
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import vit_encode as O
+from paper_2601_11590_amd import binding as B, workloads as W
+from parity_util import check
+from test_gpu_parity import case, small
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("offset", [0, 1])            # floats that the patch rows start behind a 16-byte boundary
+@pytest.mark.parametrize("kw, grids", [
+    # 64 tokens: 16 x 16 tiles over four waves (K = 27 and 256) and over eight (K = 1023, second MLP GEMM)
+    (dict(patch=3, mlp_dim=1023, out_dim=190), [(1, 8, 8)]),
+    # 2126 tokens: 32 x 32 split tiles (N = 256, K = 27, 256, 1023), 64 x 64 blocks (N = 1023 of the first MLP GEMM)
+    (dict(patch=3, mlp_dim=1023, out_dim=190), [(1, 26, 40), (1, 30, 36), (1, 2, 3)]),
+    # hidden 1024: 64 x 64 blocks with K = 27 (4-byte loads) and 1024, N = 1024, 3072 and 1021
+    (dict(hidden=1024, num_heads=16, patch=3, mlp_dim=1021, num_layers=1), [(1, 26, 40), (1, 30, 36), (1, 2, 3)]),
+    # every length a multiple of four: 16-byte loads unless the patch rows are not aligned
+    (dict(mlp_dim=1024), [(1, 26, 40), (1, 30, 36), (1, 1, 6)]),
+], ids=["64-tokens", "2126-tokens", "d1024", "aligned"])
+def test_every_form_of_the_fp32_gemm(kw, grids, offset):
+    cfg = small("f32", merge=1, **kw)
+    gw, layers, patches, cu, grid = case(cfg, grids)
+    T = patches.shape[0]
+    ref, ref_h = O.encode(cfg, gw, layers, patches, cu, grid, return_hidden=True)
+    enc = B.EpdEncoder(cfg, gw, layers, max_tokens=T, max_segments=len(grids), max_items=len(grids))
+    flat = torch.zeros(patches.size + 4, dtype=torch.float32, device="cuda:0")
+    p = flat[offset:offset + patches.size].view(T, -1)
+    p.copy_(torch.from_numpy(np.ascontiguousarray(patches)))
+    assert p.data_ptr() % 16 == 4 * offset
+    out = enc.encode(p, cu, grid)
+    torch.cuda.synchronize()
+    check(cfg, enc.hidden().cpu().numpy(), ref_h, "hidden")
+    check(cfg, out.cpu().numpy(), ref, "output")
+    enc.close()
