@@ -563,7 +563,7 @@ def main():
     ap.add_argument("--no-cpu", action="store_true", help="skip the CPU oracle leg")
     ap.add_argument("--gemm-tile", type=int, default=-1, choices=[-1, 0, 2, 4, 5, 7, 8],
                     help="tuning experiment: force one bf16 GEMM tile for every GEMM of the call (0 = 256x256, 2 = 256x128, 4 = 128x128, "
-                         "5 = 320x256; -1 = the library's plan); never the headline")
+                         "5 = 320x256, 7 = 64x64, 8 = 64x128; -1 = the library's plan); never the headline")
     ap.add_argument("--attn-rows", type=int, default=0, choices=[0, 128, 256],
                     help="tuning experiment: force the attention kernel's query rows per block (0 = the library's choice)")
     ap.add_argument("--copy-calibration", action="store_true",

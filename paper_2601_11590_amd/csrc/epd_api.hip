@@ -117,8 +117,8 @@ Layout make_layout(const epd_encode_cfg& c) {
   L.work = take((size_t)L.max_work * sizeof(AttnWork));
   // bf16 + RMSNorm + hidden a multiple of 128: the block norms are not run as kernels.  The
   // residual GEMMs leave the raw rows in bf16 (in the Xn buffer) and their sums of squares per
-  // segment of 128 columns (64 from the smallest tile); the consuming GEMM scales its accumulator rows by the resulting
-  // 1/rms, gamma being folded into its weights at create.
+  // segment of 128 columns (64 from the smallest tile); the consuming GEMM scales its accumulator
+  // rows by the resulting 1/rms, gamma being folded into its weights at create.
   L.fold_rms = bf && c.norm == EPD_RMSNORM && c.hidden % 128 == 0 && c.num_layers > 0;
   L.stats_n = c.hidden / 64;
   L.stats = take(T * (size_t)std::max(L.stats_n, 1) * 4, L.fold_rms);

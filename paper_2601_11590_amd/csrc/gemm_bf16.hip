@@ -793,7 +793,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int m0, const
           x.x += v0; x.y += v1; x.z += v2; x.w += v3;
           *xp = x;
           // folded RMSNorm (producer side): the raw rows in bf16 for the next GEMM, and their
-          // sums of squares per 128-column segment (HALF = 64: two passes make one segment)
+          // sums of squares per segment of T::STAT_COLS columns (64 in the 64 x 64 tile, else 128;
+          // where a pass has half as many, two passes make one segment)
           if (g.xb) *(uint2*)((uint16_t*)g.xb + (size_t)m * g.ldxb + n) = pack_bf16x4(x.x, x.y, x.z, x.w);
           if (g.stats_out) {
             const float ss = group_sum<LPR4>(fmaf(x.x, x.x, fmaf(x.y, x.y, fmaf(x.z, x.z, x.w * x.w))));
@@ -897,6 +898,9 @@ static void launch_cfg(const GemmArgs& g, hipStream_t s) {
   hipLaunchKernelGGL((gemm_bf16_kernel<T, EPI, OUT, GATHER, false, 0>), dim3(tiles_m * tiles_n), dim3(T::NT), 0, s, a);
 }
 
+// 256 x 128 serves QKV where 2 * hidden is not a multiple of 256.  With three stages, spread loads and two
+// parts instead of two, at once and four: 25088 x 3 D x D in 305 -> 270 us (D = 1088), 590 -> 494 (1600),
+// 64 -> 62 (320); 128 x 128 tiles forced on the same products take 224, 424 and 44.
 //            BM   BN  BK  WM WN MINBLK PARTS STAGES
 using T0 = Tile<256, 256, 64, 2, 4, 1, 4, 2>;   // 8 waves, 128x64 wave tiles, 128 KB LDS, one block per CU
 using T2 = Tile<256, 128, 64, 2, 2, 1, 2, 3, true>;   // 4 waves, 128x64 wave tiles, 144 KB LDS, one block per CU
@@ -925,13 +929,15 @@ using T8 = Tile<64, 128, 64, 2, 2, 2, 1, 3, true>;   // 4 waves, 32x64 wave tile
 // and at K >= 3200 the two large tiles are equal.
 bool gemm_bf16_tile_known(int t) { return t == 0 || t == 2 || t == 4 || t == 5 || t == 7 || t == 8; }
 struct TileShape { int bm, bn, blocks, cfg; double alpha, eps[4]; };   // eps indexed by Epilogue
-// Few rows: 64 x 128 and 64 x 64 tiles, whose stages are refilled three and two steps ahead between
+// Few rows: 64 x 64 and 64 x 128 tiles, whose stages are refilled three and two steps ahead between
 // the matrix instructions.  Their main loops are slower still per output (LDS reads), but a call
 // with one to four images has too few large tiles to occupy the chip, and each of those takes as
-// long as on a full one: 784 x 1024 x 4096 is 56 tiles of 128 x 128 in 62 us, 208 of 64 x 64 in 22
-// (784 x 3072 x 1024: 22 us, 64 x 128 tiles 16).  They are offered while they fit two rounds of
-// blocks; beyond, the large tiles fill the chip themselves (3136 x 3072 x 1024, three rounds:
-// 40 us against 36 with 256 x 256 tiles).
+// long as on a full one: 784 x 1024 x 4096 is 56 tiles of 128 x 128 in 61 us, 208 of 64 x 64 in 21
+// (784 x 3072 x 1024: 23 us, 64 x 128 tiles 16).  They are offered while they fit two rounds of
+// blocks; beyond, the large tiles fill the chip themselves (3136 x 3072 x 1024: 1 round of 256 x 256
+// tiles 36 us, 64 x 64 in four rounds 44).  Their constants rank, they do not predict: measured in
+// calls with every tile forced, 196 ... 4608 tokens at hidden 1024, 1152 and 3200, the tile chosen is
+// the fastest or within 10 % of it, while the model is off by up to 40 % on single launches.
 constexpr TileShape kShape256 = {256, 256, 1, 0, 22.6, {13.2, 13.2, 39.4, 21.9}};
 constexpr TileShape kShape320 = {320, 256, 1, 5, 21.8, {11.7, 11.7, 39.4, 24.8}};
 constexpr TileShape kShape128 = {128, 128, 2, 4, 32.8, {4.6, 4.6, 23.8, 19.6}};

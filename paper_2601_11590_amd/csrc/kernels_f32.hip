@@ -25,9 +25,10 @@ __device__ __forceinline__ float gelu_f32(float v, int act) {
   return 0.5f * v * (1.0f + tanhf(u));
 }
 
-// A block of NW waves.  SPLIT: all of them share one 16 T x 16 T tile and take its K in turn, 64 at a
+// A block of NW waves.  SPLIT: all of them share one 16 T x 16 T tile and take its K in turn, 32 at a
 // time, and their sums meet in LDS; otherwise NW = 4 and each has a tile of its own, 2 x 2.
-// VEC: rows start 16-byte aligned and K (and a gathered piece) is a multiple of 4.
+// VEC: rows start 16-byte aligned and K (and a gathered piece) is a multiple of 4; otherwise 16-byte
+// loads from any float's address, and the last of a row taken apart.
 template <int T, int NW, bool SPLIT, bool VEC>
 __global__ __launch_bounds__(64 * NW) void gemm_f32_kernel(GemmArgs g) {
   constexpr int WT = 16 * T, BT = SPLIT ? WT : 2 * WT;       // wave and block tile

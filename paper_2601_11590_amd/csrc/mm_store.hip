@@ -9,8 +9,8 @@
 //         low / high):  H_k = sum_j (s_j + 1) R_k^(L - j) mod P.  Every term carries its own
 //         power, so the sum can be taken in any order: exact integer arithmetic, bit for bit the
 //         value a serial evaluation gives (how the kernel orders it: hash_partial_kernel).
-//   pool  a byte arena behind a reserved area of 1 MiB; entries are contiguous,
-//         256-byte aligned; insert drops least-recently-used entries until a first-fit range
+//   pool  a byte arena behind a reserved area of 1 MiB (it held the partial hashes once; entries
+//         stay where callers know them to be); entries are contiguous, 256-byte aligned; insert drops least-recently-used entries until a first-fit range
 //         (lowest address) is free; a hit makes its entry the most recent.
 // The bookkeeping is host code and touches no device memory; only epd_store_hash and
 // epd_encode_cached launch work.  Pinned memory is allocated when a store is made, beside its pool, and not

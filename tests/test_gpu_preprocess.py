@@ -67,7 +67,7 @@ def test_ragged_items_upscaled_downscaled_and_untouched(dtype):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-def test_patch_sizes_that_take_the_16_byte_store_path(dtype):
+def test_patch_size_8_equal_upscaled_and_mixed(dtype):
     cfg = make(dtype, patch=8)
     grids = [(1, 4, 6), (1, 2, 2), (1, 6, 2)]
     src = [(32, 48), (11, 23), (100, 9)]                          # equal, up, mixed

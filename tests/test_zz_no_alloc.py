@@ -1,5 +1,5 @@
 """epd_store_hash_noalloc (the entry point for callers that cannot allocate: its scratch is a
-static device array inside the library) against epd_store_hash (scratch in the caller's pool)
+static device array inside the library) against epd_store_hash (sums taken from pinned memory)
 through the C ABI: the keys must be bit-identical, on two calls in a row, the second with a
 smaller input -- the array keeps the first call's contents and nothing may leak from them."""
 
