@@ -937,7 +937,7 @@ struct TileShape { int bm, bn, blocks, cfg; double alpha, eps[4]; };   // eps in
 // blocks; beyond, the large tiles fill the chip themselves (3136 x 3072 x 1024: 1 round of 256 x 256
 // tiles 36 us, 64 x 64 in four rounds 44).  Their constants rank, they do not predict: measured in
 // calls with every tile forced, 196 ... 4608 tokens at hidden 1024, 1152 and 3200, the tile chosen is
-// the fastest or within 10 % of it, while the model is off by up to 40 % on single launches.
+// the fastest or within 11 % of it, while the model is off by up to a half on single launches.
 constexpr TileShape kShape256 = {256, 256, 1, 0, 22.6, {13.2, 13.2, 39.4, 21.9}};
 constexpr TileShape kShape320 = {320, 256, 1, 5, 21.8, {11.7, 11.7, 39.4, 24.8}};
 constexpr TileShape kShape128 = {128, 128, 2, 4, 32.8, {4.6, 4.6, 23.8, 19.6}};
