@@ -29,11 +29,12 @@ template <typename E> __device__ __forceinline__ int last_not_after(const E* t, 
 //   merge  the source tokens of 256 merged tokens, window rows then columns
 //   pad    clears the columns of vt between a segment's end and the next (aligned) start, four
 //          channel rows per block: attention multiplies them by exact zeros, so they must be finite
-// The rot and pad roles take at most kMaxGrid blocks, which stride over larger tables.
+// The rot and pad roles take at most kMaxGrid blocks, which stride over larger tables (STRIDED; a
+// kernel of its own, since small calls notice the loops: 0.2 us of 57).
 // Up to kPlanInline segments and items the tables are kernel arguments, copied to LDS before they
 // are searched.  Bound: latency.  As a copy of the metadata (3 us) plus three kernels, one thread per
 // token for all its pairs (15 us), this step cost a call 24 us more: one 256-token image 3.9 us now.
-__global__ __launch_bounds__(256) void plan_kernel(PlanArgs p) {
+template <bool STRIDED> __global__ __launch_bounds__(256) void plan_kernel(PlanArgs p) {
   __shared__ PlanItem items[kPlanInline];
   __shared__ PlanSeg segs[kPlanInline];
   const int tid = threadIdx.x;
@@ -47,7 +48,8 @@ __global__ __launch_bounds__(256) void plan_kernel(PlanArgs p) {
   }
   int b = blockIdx.x;
   if (b < p.rot_blocks) {
-    for (RotEntry e; b * rot_tokens_per_block(p.pairs) < p.T; b += p.rot_blocks) {
+    RotEntry e;
+    do {
       if (!rot_entry(p.T, p.pairs, b, tid, e)) continue;
       const PlanItem& d = item[last_not_after(item, p.num_items, e.tok, &PlanItem::tok)];
       const int local = e.tok - d.tok, t = local / (d.h * d.w), rem = local - t * d.h * d.w, r = rem / d.w;
@@ -55,7 +57,7 @@ __global__ __launch_bounds__(256) void plan_kernel(PlanArgs p) {
       double sn, cs;
       sincos((double)coord * p.pair_freq[e.pair], &sn, &cs);
       p.rot[e.at] = make_float2((float)cs, (float)sn);
-    }
+    } while (STRIDED && (b += p.rot_blocks) * rot_tokens_per_block(p.pairs) < p.T);
     return;
   }
   b -= p.rot_blocks;
@@ -84,23 +86,27 @@ __global__ __launch_bounds__(256) void plan_kernel(PlanArgs p) {
   }
   b -= p.merge_blocks;
   const int rows = (p.hidden + 3) / 4;
-  for (; b < p.num_segments * rows; b += p.pad_blocks) {
+  do {
     const int sg = b / rows, row = (b - sg * rows) * 4 + (tid >> 6);
     if (row >= p.hidden) continue;
     const PlanSeg& s = seg[sg];
     uint16_t* vt = (uint16_t*)p.vt + (size_t)row * p.vt_stride;
     const int end = s.vcol + (s.len + kVtAlign - 1) / kVtAlign * kVtAlign;
     for (int c = s.vcol + s.len + (tid & 63); c < end; c += 64) vt[c] = 0;
-  }
+  } while (STRIDED && (b += p.pad_blocks) < p.num_segments * rows);
 }
 
 void launch_plan(PlanArgs& p, hipStream_t s) {
   const int rot_tokens = p.pairs > 0 ? rot_tokens_per_block(p.pairs) : 1;
-  p.rot_blocks = p.pairs > 0 ? std::min((p.T + rot_tokens - 1) / rot_tokens, kMaxGrid) : 0;
+  const int rot = p.pairs > 0 ? (p.T + rot_tokens - 1) / rot_tokens : 0;
+  const int pad = p.vt ? p.num_segments * ((p.hidden + 3) / 4) : 0;      // the vt buffer holds 1 KB per unit of it
+  p.rot_blocks = std::min(rot, kMaxGrid);
   p.work_blocks = p.vcol ? p.num_work : (p.num_work + 255) / 256;
   p.merge_blocks = p.merge > 1 ? (p.Tm + 255) / 256 : 0;
-  p.pad_blocks = p.vt ? std::min(p.num_segments * ((p.hidden + 3) / 4), kMaxGrid) : 0;   // product: the vt buffer holds 1 KB per unit of it
-  hipLaunchKernelGGL(plan_kernel, dim3(p.rot_blocks + p.work_blocks + p.merge_blocks + p.pad_blocks), dim3(256), 0, s, p);
+  p.pad_blocks = std::min(pad, kMaxGrid);
+  const dim3 grid(p.rot_blocks + p.work_blocks + p.merge_blocks + p.pad_blocks);
+  if (rot > kMaxGrid || pad > kMaxGrid) hipLaunchKernelGGL(plan_kernel<true>, grid, dim3(256), 0, s, p);
+  else hipLaunchKernelGGL(plan_kernel<false>, grid, dim3(256), 0, s, p);
 }
 
 // ------------------------------------------------------------------------------ norm
