@@ -101,6 +101,7 @@ template <int G> __device__ __forceinline__ float group_sum(float x) {
 // LDS beyond the operand stages: the rotary epilogue keeps the tile's cos / sin table there, up
 // to 256 + QKV_TABLE_EXTRA bytes per token (head_dim 72 has 36 pairs of 8 bytes)
 constexpr int QKV_TABLE_EXTRA = 32;
+constexpr int MAX_PIECES = 4;       // pieces per gathered row that the ping-pong loop takes
 template <class T, int EPI> __host__ __device__ constexpr int lds_extra() { return EPI == 3 ? T::BM * QKV_TABLE_EXTRA : 0; }
 
 template <int N> __device__ __forceinline__ void wait_vmcnt() {
@@ -143,11 +144,13 @@ template <int N, class F> __device__ __forceinline__ void static_for(F&& f) {
 }
 
 // Compile-time description of one kernel variant.
-template <int BM_, int BN_, int BK_, int WAVES_M_, int WAVES_N_, int MINBLK_, int PARTS_, int STAGES_, bool SPREAD_ = false>
+template <int BM_, int BN_, int BK_, int WAVES_M_, int WAVES_N_, int MINBLK_, int PARTS_, int STAGES_, bool SPREAD_ = false, int PP_PARTS_ = 0>
 struct Tile {
   static constexpr int BM = BM_, BN = BN_, BK = BK_, WAVES_M = WAVES_M_, WAVES_N = WAVES_N_;
   static constexpr int MINBLK = MINBLK_, STAGES = STAGES_;
   static constexpr bool SPREAD = SPREAD_;                // loads of a stage spread over the MFMAs of a step
+  static constexpr int PP_PARTS = PP_PARTS_;             // ping-pong main loop: parts of a wave tile's rows, one per phase (0: plain loop)
+  static constexpr bool PINGPONG = PP_PARTS > 0;
   static constexpr int NT = 64 * WAVES_M * WAVES_N;
   static constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N, TM = WM / 32, TN = WN / 32;
   static constexpr int TM16 = WM / 16, TN16 = WN / 16;   // 16 x 16 MFMA blocks per wave tile
@@ -169,6 +172,79 @@ struct Tile {
   // time, so 16 consecutive rows must map to 16 different 16-byte columns modulo 256 bytes.
   __device__ static __forceinline__ int swz(int row) { return (row >> 1) & 7; }
 };
+
+// Ping-pong main loop (eight waves, WAVES_M = 2, two waves per SIMD).  The two wave rows run half a phase
+// apart: while one multiplies, the other fetches its next fragments, so the matrix cores never wait for
+// an LDS read, a barrier or the issue of a load.  The rows of a wave tile come in one or two parts and a K
+// step is a phase per part:
+//     fragment reads, waited for | barrier | matrix instructions, loads between them | barrier
+// and wave row 1 passes one barrier more ahead of the loop (wave row 0 one behind it).  Operands come in
+// units: part h of the rows of both wave rows, and all of W.  Unit u of a step is read in phase p(u), and
+// its place in the ring is refilled, STAGES steps ahead, with the matrix instructions of phase q(u) > p(u)
+// counted from the same step: by then both wave rows have read it, one barrier apart at most.  A wave waits
+// for its loads of a unit in the phase before the one that reads it (the barriers between make that hold
+// for the loads of all waves) and never for a later one.
+//   What it replaced on the large tiles was one barrier per K step, behind which all waves read, waited and
+// multiplied together: 256 x 256 x 64 took 3440 clocks of 2048 that the matrix instructions need, now 2390
+// (320 x 256: 2930 of 2560).  LDS is not what bounds it (fragment reads run at 256 B per clock and unit, direct-
+// to-LDS loads at 64: 768 and 1024 clocks a step).  Four phases a step of a quarter each: 2540; matrix
+// instructions at raised priority: no difference.  8192^3, random operands: 1406 -> 1490 TFLOP/s (the chip's
+// power limit; all-zero ones 1618 -> 1890), 32768 x 12800 x 3200 with GELU 1244 -> 1316, four clips 450 -> 432 ms.
+template <class T> struct PingPong {
+  static constexpr int S = T::STAGES, NP = T::PP_PARTS, NU = NP + 1;    // units in the order A0, W [, A1]
+  // 16-row fragment blocks per part: ten of rows go as four and six, so that every wave issues as many loads
+  static constexpr int NA0 = T::TM16 == 10 ? 4 : T::TM16 / NP, NA1 = T::TM16 - NA0, NW = T::TN16;
+  static constexpr int p(int u) { return u / 2; }
+  static constexpr int q(int u) { return u / 2 + 1; }
+  static constexpr int blocks(int u) { return u == 1 ? NW : u == 2 ? NA1 : NA0; }
+  static constexpr int loads(int u) { return (u == 1 ? 4 : 2) * blocks(u) / 4; }   // of 8 rows, 1 KB, per wave and unit
+  // With `rem` steps behind the current one: this wave's loads that may be in flight at the wait of phase f
+  // (-1: ahead of the loop), or -1 where the next phase reads no unit.  A load of step t (relative to the current
+  // one) and unit u is issued in phase (t - S) * NP + q(u); loads are issued in that order.
+  static constexpr int in_flight(int rem, int f) {
+    int need = -1000000, n = 0;
+    for (int t = 0; t <= 1 && t <= rem; ++t)
+      for (int u = 0; u < NU; ++u)
+        if (t * NP + p(u) == f + 1) { const int r = ((t - S) * NP + q(u)) * NU + u; need = r > need ? r : need; }
+    if (need == -1000000) return -1;
+    for (int t = 0; t <= rem && t <= 2 * S; ++t)
+      for (int u = 0; u < NU; ++u) {
+        const int ph = (t - S) * NP + q(u);
+        if (ph * NU + u > need && ph < (f < 0 ? 0 : f)) n += loads(u);
+      }
+    return n;
+  }
+};
+
+// Fragment reads of the ping-pong loop: blocks of 16 rows of one operand at offset OFF (f[2 * block + k half], k
+// halves at a0 and a1), with them two blocks of the other one, and the wait for all of them -- in one
+// asm block, so that no result is ever pending outside of it.
+#define EPD_DSR(d, a, o) "ds_read_b128 %" #d ", %" #a " offset:%" #o "\n\t"
+template <int N, int OFF> __device__ __forceinline__ void read_frags(bf16x8* f, uint32_t a0, uint32_t a1) {
+  static_assert(N == 4 || N == 6, "blocks");
+  if constexpr (N == 4) {
+    asm volatile(EPD_DSR(0, 8, 10) EPD_DSR(2, 8, 11) EPD_DSR(4, 8, 12) EPD_DSR(6, 8, 13)
+                 EPD_DSR(1, 9, 10) EPD_DSR(3, 9, 11) EPD_DSR(5, 9, 12) EPD_DSR(7, 9, 13) "s_waitcnt lgkmcnt(0)"
+                 : "=&v"(f[0]), "=&v"(f[1]), "=&v"(f[2]), "=&v"(f[3]), "=&v"(f[4]), "=&v"(f[5]), "=&v"(f[6]), "=&v"(f[7])
+                 : "v"(a0), "v"(a1), "n"(OFF), "n"(OFF + 2048), "n"(OFF + 4096), "n"(OFF + 6144) : "memory");
+  } else {
+    asm volatile(EPD_DSR(0, 12, 14) EPD_DSR(2, 12, 15) EPD_DSR(4, 12, 16) EPD_DSR(6, 12, 17)
+                 EPD_DSR(8, 12, 18) EPD_DSR(10, 12, 19) EPD_DSR(1, 13, 14) EPD_DSR(3, 13, 15)
+                 EPD_DSR(5, 13, 16) EPD_DSR(7, 13, 17) EPD_DSR(9, 13, 18) EPD_DSR(11, 13, 19) "s_waitcnt lgkmcnt(0)"
+                 : "=&v"(f[0]), "=&v"(f[1]), "=&v"(f[2]), "=&v"(f[3]), "=&v"(f[4]), "=&v"(f[5]), "=&v"(f[6]), "=&v"(f[7]), "=&v"(f[8]), "=&v"(f[9]), "=&v"(f[10]), "=&v"(f[11])
+                 : "v"(a0), "v"(a1), "n"(OFF), "n"(OFF + 2048), "n"(OFF + 4096), "n"(OFF + 6144), "n"(OFF + 8192), "n"(OFF + 10240) : "memory");
+  }
+}
+template <int NA, int NW> __device__ __forceinline__ void read_frags_both(bf16x8* f, uint32_t a0, uint32_t a1, bf16x8* w, uint32_t w0, uint32_t w1) {
+  static_assert(NA == 4 && NW == 4, "blocks");
+  asm volatile(EPD_DSR(8, 18, 20) EPD_DSR(10, 18, 21) EPD_DSR(12, 18, 22) EPD_DSR(14, 18, 23)
+               EPD_DSR(0, 16, 20) EPD_DSR(2, 16, 21) EPD_DSR(4, 16, 22) EPD_DSR(6, 16, 23)
+               EPD_DSR(9, 19, 20) EPD_DSR(11, 19, 21) EPD_DSR(13, 19, 22) EPD_DSR(15, 19, 23)
+               EPD_DSR(1, 17, 20) EPD_DSR(3, 17, 21) EPD_DSR(5, 17, 22) EPD_DSR(7, 17, 23) "s_waitcnt lgkmcnt(0)"
+               : "=&v"(f[0]), "=&v"(f[1]), "=&v"(f[2]), "=&v"(f[3]), "=&v"(f[4]), "=&v"(f[5]), "=&v"(f[6]), "=&v"(f[7]), "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[2]), "=&v"(w[3]), "=&v"(w[4]), "=&v"(w[5]), "=&v"(w[6]), "=&v"(w[7])
+               : "v"(a0), "v"(a1), "v"(w0), "v"(w1), "n"(0), "n"(2048), "n"(4096), "n"(6144) : "memory");
+}
+#undef EPD_DSR
 
 template <class T, int EPI, int OUT, bool VMODE, bool GATHER, bool FAST>
 __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int m0, const int n0, char* const lds) {
@@ -466,16 +542,146 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int m0, const
     wait_vmcnt<0>();
   };
   static_assert(S >= 2 && S <= 4, "ring");
+  // the sums of squares held since before the first operand load
+  auto store_row_scale = [&]() {
+    if (scaled_v && tid < BM) {
+      float ss = ((st[0].x + st[0].y) + (st[0].z + st[0].w)) + ((st[1].x + st[1].y) + (st[1].z + st[1].w));
+      if constexpr (SV == 4) ss += ((st[2].x + st[2].y) + (st[2].z + st[2].w)) + ((st[3].x + st[3].y) + (st[3].z + st[3].w));
+      row_scale[tid] = 1.0f / sqrtf(fmaf(ss, g.stats_inv_dim, g.stats_eps));
+    }
+  };
+  if constexpr (T::PINGPONG && FAST) {
+    using PP = PingPong<T>;
+    static_assert(T::WAVES_M == 2 && T::WAVES_N == 4 && PP::NP <= 2, "ping-pong tile");
+    constexpr int NP = PP::NP, NW = PP::NW;
+    // a load covers 8 rows that start at a multiple of 8, odd for odd waves: its lanes' offsets are the same for all
+    // loads of a wave
+    const int lrow = lane >> 3, lcol = ((lane & 7) ^ T::swz((wave & 1) * 8 + lrow)) * 16;
+    const uint32_t a_lane = (uint32_t)lrow * (uint32_t)g.lda * 2u + lcol, w_lane = (uint32_t)lrow * (uint32_t)ldw * 2u + lcol;
+    // gathered operand: the tile's row numbers lie in LDS, [piece][row]; those of a wave's loads are fetched into
+    // registers when a new piece begins (pieces are whole K steps), ahead of the phase that issues the loads
+    [[maybe_unused]] const uint32_t idx0 = lds0 + (uint32_t)(T::LDS_BYTES + lds_extra<T, EPI>() + BM * 4);
+    [[maybe_unused]] int src[GATHER ? 2 : 1][GATHER ? 3 : 1], piece[2] = {-1, -1}, kin[2] = {0, 0};
+    if constexpr (GATHER) {
+      int* const idx = (int*)(lds + T::LDS_BYTES + lds_extra<T, EPI>() + BM * 4);
+      for (int r = tid; r < BM; r += NT)
+        for (int c = 0; c < g.gather_n; ++c) idx[c * BM + r] = g.gather[(size_t)min(m0 + r, g.M - 1) * g.gather_n + c];
+      __syncthreads();
+    }
+    auto tile_row = [&](auto U, int j) {     // first row of load j of unit U
+      constexpr int u = decltype(U)::value, per = PP::blocks(u) * 2;   // loads per wave row / column
+      const int n = j * 8 + wave;
+      return (n / per) * (u != 1 ? WM : WN) + (u == 2 ? PP::NA0 * 16 : 0) + (n % per) * 8;
+    };
+    // called once per step and unit, in order, ahead of the unit's loads
+    auto next_rows = [&](auto U) {
+      constexpr int u = decltype(U)::value, h = u / 2;
+      if constexpr (GATHER && u != 1) {
+        kin[h] += BK;
+        if (piece[h] < 0 || kin[h] == kcw) {
+          kin[h] = 0; ++piece[h];
+#pragma unroll
+          for (int j = 0; j < PP::loads(u); ++j) {
+            const uint32_t at = idx0 + (uint32_t)(piece[h] * BM + tile_row(U, j) + lrow) * 4u;
+            int row;
+            asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(row) : "v"(at) : "memory");
+            src[h][j] = row;
+          }
+        }
+      }
+    };
+    auto load = [&](auto U, auto J, int stage, int kt) {
+      constexpr int u = decltype(U)::value, j = decltype(J)::value;
+      const int row = tile_row(U, j);
+      char* const dst = lds + (u != 1 ? stage * A_BYTES : S * A_BYTES + stage * W_BYTES) + row * ROWB;
+      if constexpr (GATHER && u != 1) {
+        constexpr int h = u / 2;
+        const char* from = (const char*)g.A + (size_t)kin[h] * 2 + lcol + (uint64_t)(uint32_t)src[h][j] * ((uint32_t)g.lda * 2u);
+        __builtin_amdgcn_global_load_lds(EPD_GPTR(from), EPD_LPTR(dst), 16, 0, 0);
+        return;
+      }
+      uint32_t off = u != 1 ? a_lane : w_lane;
+      asm volatile("" : "+v"(off));          // see issue()
+      const char* base = u != 1 ? a_base_ptr + ((size_t)row * g.lda + (size_t)kt * BK) * 2 : w_base_ptr + ((size_t)row * ldw + (size_t)kt * BK) * 2;
+      __builtin_amdgcn_global_load_lds(EPD_GPTR(base + (size_t)off), EPD_LPTR(dst), 16, 0, 0);
+    };
+    auto load_unit = [&](auto U, int stage, int kt) {
+      next_rows(U);
+      static_for<PP::loads(decltype(U)::value)>([&](auto J) { load(U, J, stage, kt); });
+    };
+    bf16x8 pa[2 * PP::NA1], pw[2 * NW];
+    // loads ahead of the loop: everything the loop does not issue
+    static_for<S>([&](auto TT) {
+      static_for<PP::NU>([&](auto U) {
+        constexpr int t = decltype(TT)::value;
+        if constexpr ((t - S) * NP + PP::q(decltype(U)::value) < 0) { if (t < nk) load_unit(U, t, t); }
+      });
+    });
+    if (nk >= S) wait_vmcnt<PP::in_flight(2 * S, -1)>();
+    else wait_vmcnt<0>();
+    __builtin_amdgcn_s_barrier();
+    store_row_scale();
+    if (wm == 1) __builtin_amdgcn_s_barrier();
+    auto phase = [&](auto P, auto REM, int t, int stg) {
+      constexpr int p = decltype(P)::value, rem = decltype(REM)::value, NA = p ? PP::NA1 : PP::NA0, NM = NA * NW * 2;
+      const uint32_t a0 = a_rd0 + stg * A_BYTES, w0 = w_rd0 + stg * W_BYTES;
+      static_for<PP::NU>([&](auto U) {
+        constexpr int u = decltype(U)::value, ahead = S + (p - PP::q(u) < 0 ? -1 : 0);
+        if constexpr (PP::q(u) % NP == p && ahead <= rem) next_rows(U);
+      });
+      if constexpr (p == 0) read_frags_both<PP::NA0, NW>(pa, a0, a0 ^ 64u, pw, w0, w0 ^ 64u);
+      else read_frags<PP::NA1, PP::NA0 * 2048>(pa, a0, a0 ^ 64u);
+      constexpr int keep = PP::in_flight(rem, p);
+      if constexpr (keep >= 0) wait_vmcnt<keep>();
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+      static_for<NM>([&](auto I) {
+        constexpr int i = decltype(I)::value, ks = i / (NW * NA), w = i / NA % NW, x = i % NA, a16 = p * PP::NA0 + x;
+        f32x4& c = acc[a16 >> 1][w >> 1][(a16 & 1) * 2 + (w & 1)];
+        if constexpr (VMODE) c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pa[2 * x + ks], pw[2 * w + ks], c, 0, 0, 0);
+        else c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pw[2 * w + ks], pa[2 * x + ks], c, 0, 0, 0);
+        // units refilled in this phase, their loads spread over the instructions
+        static_for<PP::NU>([&](auto U) {
+          constexpr int u = decltype(U)::value, ahead = S + (p - PP::q(u) < 0 ? -1 : 0);
+          if constexpr (PP::q(u) % NP == p && ahead <= rem) {
+            constexpr int n = PP::loads(u);
+            static_for<n>([&](auto J) {
+              if constexpr (i == NM * (2 * decltype(J)::value + 1) / (2 * n)) {
+                __builtin_amdgcn_sched_barrier(0);
+                int ns = stg + ahead; ns = ns >= S ? ns - S : ns;
+                load(U, J, ns, t + ahead);
+                __builtin_amdgcn_sched_barrier(0);
+              }
+            });
+          }
+        });
+      });
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    int t = 0, stg = 0;
+    for (; t + S < nk; ++t) {
+      static_for<NP>([&](auto P) { phase(P, std::integral_constant<int, 2 * S>{}, t, stg); });
+      if (++stg == S) stg = 0;
+    }
+    static_for<S>([&](auto R) {              // the last S steps: fewer loads, and fewer to wait for
+      constexpr int rem = S - 1 - decltype(R)::value;
+      if (nk > rem) {
+        static_for<NP>([&](auto P) { phase(P, std::integral_constant<int, rem>{}, t, stg); });
+        ++t;
+        if (++stg == S) stg = 0;
+      }
+    });
+    if (wm == 0) __builtin_amdgcn_s_barrier();
+  } else {
   issue_step(0, 0);
   if constexpr (S >= 3) { if (nk > 1) issue_step(1, 1); }
   if constexpr (S >= 4) { if (nk > 2) issue_step(2, 2); }
   wait_later(nk - 1);
   __builtin_amdgcn_s_barrier();
-  if (scaled_v && tid < BM) {
-    float ss = ((st[0].x + st[0].y) + (st[0].z + st[0].w)) + ((st[1].x + st[1].y) + (st[1].z + st[1].w));
-    if constexpr (SV == 4) ss += ((st[2].x + st[2].y) + (st[2].z + st[2].w)) + ((st[3].x + st[3].y) + (st[3].z + st[3].w));
-    row_scale[tid] = 1.0f / sqrtf(fmaf(ss, g.stats_inv_dim, g.stats_eps));
-  }
+  store_row_scale();
   constexpr bool INNER_LOOP = FAST && T::SPREAD;
   if (!INNER_LOOP && nk > S - 1) issue_step(S - 1, S - 1);
   read_slice(I0{}, I0{});
@@ -524,6 +730,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int m0, const
     static_for<S>([&](auto ST) {
       if (kt + decltype(ST)::value < nk) step(ST, std::false_type{}, kt + decltype(ST)::value);
     });
+  }
   if (nk == 1) prefetch_resid();
 
   // ------------------------------------------------------------------ epilogue
@@ -679,7 +886,6 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int m0, const
     constexpr int STG = SR * ROWE;
     constexpr int LPR4 = BN / 4, RPS = NT / LPR4;      // lanes per row (4 columns each), rows per sweep
     static_assert(STG <= T::LDS_BYTES && SR % RPS == 0 && NT % LPR4 == 0 && LPR4 >= 16, "row-split staging");
-    static_assert(BM < 128 || RPS == 8, "rows of the last sweep (rotate_pair)");
     const int cl = (tid % LPR4) * 4;
     const int n = n0 + cl;                             // N is a multiple of 4: all or nothing
     float b0 = 0.f, b1 = 0.f, b2 = 0.f, b3 = 0.f;
@@ -840,7 +1046,8 @@ __device__ __forceinline__ void tile_coords(int t, int tiles_m, int tiles_n, int
 template <class T, int EPI, int OUT, bool GATHER, bool FAST, int TAG>
 __global__ __launch_bounds__(T::NT, T::MINBLK) void gemm_bf16_kernel(GemmArgs g) {
   // + room for a wider rotary table (QKV epilogue) + per-row scales of the epilogue
-  __shared__ __attribute__((aligned(1024))) char lds[T::LDS_BYTES + lds_extra<T, EPI>() + T::BM * 4];
+  // + the row numbers of a gathered operand (ping-pong loop)
+  __shared__ __attribute__((aligned(1024))) char lds[T::LDS_BYTES + lds_extra<T, EPI>() + T::BM * 4 + (GATHER && FAST ? T::BM * MAX_PIECES * 4 : 0)];
   const int tiles_n = (g.N + T::BN - 1) / T::BN, tiles_m = (g.M + T::BM - 1) / T::BM;
   int tm, tn;
   tile_coords(xcd_remap(blockIdx.x, gridDim.x), tiles_m, tiles_n, g.group_m, tm, tn);
@@ -895,6 +1102,12 @@ static void launch_cfg(const GemmArgs& g, hipStream_t s) {
       return;
     }
   }
+  if constexpr (GATHER && T::PINGPONG) {
+    if (g.gather_n <= MAX_PIECES && g.K % (g.gather_n * T::BK) == 0) {
+      hipLaunchKernelGGL((gemm_bf16_kernel<T, EPI, OUT, true, true, 0>), dim3(tiles_m * tiles_n), dim3(T::NT), 0, s, a);
+      return;
+    }
+  }
   hipLaunchKernelGGL((gemm_bf16_kernel<T, EPI, OUT, GATHER, false, 0>), dim3(tiles_m * tiles_n), dim3(T::NT), 0, s, a);
 }
 
@@ -902,10 +1115,10 @@ static void launch_cfg(const GemmArgs& g, hipStream_t s) {
 // parts instead of two, at once and four: 25088 x 3 D x D in 305 -> 270 us (D = 1088), 590 -> 494 (1600),
 // 64 -> 62 (320); 128 x 128 tiles forced on the same products take 224, 424 and 44.
 //            BM   BN  BK  WM WN MINBLK PARTS STAGES
-using T0 = Tile<256, 256, 64, 2, 4, 1, 4, 2>;   // 8 waves, 128x64 wave tiles, 128 KB LDS, one block per CU
+using T0 = Tile<256, 256, 64, 2, 4, 1, 4, 2, false, 2>;   // 8 waves, 128x64 wave tiles, 128 KB LDS, one block per CU
 using T2 = Tile<256, 128, 64, 2, 2, 1, 2, 3, true>;   // 4 waves, 128x64 wave tiles, 144 KB LDS, one block per CU
 using T4 = Tile<128, 128, 64, 2, 2, 2, 4, 2>;   // 4 waves, 64x64 wave tiles, 64 KB LDS, two blocks per CU
-using T5 = Tile<320, 256, 64, 2, 4, 1, 5, 2>;   // 8 waves, 160x64 wave tiles, 144 KB LDS, one block per CU
+using T5 = Tile<320, 256, 64, 2, 4, 1, 5, 2, false, 2>;   // 8 waves, 160x64 wave tiles, 144 KB LDS, one block per CU
 
 using T7 = Tile<64, 64, 64, 2, 2, 2, 1, 4, true>;    // 4 waves, 32x32 wave tiles, 64 KB LDS, two blocks per CU
 using T8 = Tile<64, 128, 64, 2, 2, 2, 1, 3, true>;   // 4 waves, 32x64 wave tiles, 72 KB LDS, two blocks per CU

@@ -1,0 +1,35 @@
+"""GPU test of the ping-pong main loop (256 x 256 and 320 x 256 tiles): forced on calls whose products have one K
+step, two, and numbers around the ring's turn, with ragged last tiles and gathered rows in pieces of whole K steps
+(64, 128) and not (96, 216), it gives bit for bit what the plain loop of the 128 x 128 tile gives -- an output
+element is the same chain of matrix instructions in both.  (Without rotary embedding: which product of a rotary
+pair is rounded before the sum depends on the tile's rows.)"""
+
+import pytest
+import torch
+
+from oracle import vit_encode as O
+from paper_2601_11590_amd import binding as B, workloads as W
+from parity_util import check
+from test_gpu_parity import case, small
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("hidden,heads", [(64, 1), (128, 2), (192, 3), (256, 4), (320, 5), (96, 3), (216, 3)])
+@pytest.mark.parametrize("merge", [1, 2, 4])
+def test_large_tiles_give_the_bits_of_the_128_tile(hidden, heads, merge):
+    cfg = small("bf16", hidden=hidden, num_heads=heads, head_dim=hidden // heads, rope="none", rope_pairs=(0, 0, 0), norm="layernorm",
+                mlp_dim=2 * hidden + 72, out_dim=328, merge=merge)
+    grids = [(1, 20, 32), (1, 4, 4), (1, 12, 8)]
+    gw, layers, patches, cu, grid = case(cfg, grids)
+    ref = O.encode(cfg, gw, layers, patches, cu, grid)
+    enc = B.EpdEncoder(cfg, gw, layers, max_tokens=patches.shape[0], max_segments=len(grids), max_items=len(grids))
+    p = B.to_device_patches(patches, cfg.dtype)
+    out = {}
+    for tile in (4, 0, 5):
+        enc.set_tuning(tile, 0)
+        out[tile] = enc.encode(p, cu, grid).clone()
+    torch.cuda.synchronize()
+    check(cfg, out[0].float().cpu().numpy(), ref, "256 x 256")
+    assert torch.equal(out[0], out[4]) and torch.equal(out[5], out[4])
+    enc.close()
