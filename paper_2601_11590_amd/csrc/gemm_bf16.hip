@@ -86,23 +86,30 @@ __device__ __forceinline__ void rotate_pair(float& a, float& b, float cos, float
 
 enum OutKind : int { OUT_BF16 = 0, OUT_F32 = 1 };
 
-// Sum over aligned groups of G = 16 or 32 consecutive lanes; every lane of a group gets the sum.
+// Sum over aligned groups of G = 8 or 16 consecutive lanes; every lane of a group gets the sum.
 template <int G> __device__ __forceinline__ float group_sum(float x) {
-  static_assert(G == 16 || G == 32, "group size");
+  static_assert(G == 8 || G == 16, "group size");
   x += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0xB1, 0xF, 0xF, true));   // quad_perm 1,0,3,2
   x += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x4E, 0xF, 0xF, true));   // quad_perm 2,3,0,1
   x += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x141, 0xF, 0xF, true));  // row_half_mirror
-  x += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x140, 0xF, 0xF, true));  // row_mirror
-  if constexpr (G == 32)
-    x += __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute((int)((threadIdx.x ^ 16) & 63) * 4, __builtin_bit_cast(int, x)));
+  if constexpr (G == 16)
+    x += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x140, 0xF, 0xF, true));  // row_mirror
   return x;
 }
 
-// LDS beyond the operand stages: the rotary epilogue keeps the tile's cos / sin table there, up
-// to 256 + QKV_TABLE_EXTRA bytes per token (head_dim 72 has 36 pairs of 8 bytes)
-constexpr int QKV_TABLE_EXTRA = 32;
 constexpr int MAX_PIECES = 4;       // pieces per gathered row that the ping-pong loop takes
-template <class T, int EPI> __host__ __device__ constexpr int lds_extra() { return EPI == 3 ? T::BM * QKV_TABLE_EXTRA : 0; }
+
+// Rows of a matrix from `base` on, `bytes` of them in all: accesses beyond are dropped (loads give zero), which spares
+// the epilogues a branch per access.  A lane that must not take part passes OUTSIDE as its offset.
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
+constexpr uint32_t OUTSIDE = 0x80000000u;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t row_window(const void* base, size_t bytes) {
+  // (made of scalars by hand: where the compiler does not see that they are, every access becomes a loop over the lanes)
+  const uint64_t p = (uint64_t)base;
+  const uint64_t u = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)p) | (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(p >> 32)) << 32;
+  return __builtin_amdgcn_make_buffer_rsrc((void*)u, 0, __builtin_amdgcn_readfirstlane((int)bytes), 0x00027000);
+}
 
 template <int N> __device__ __forceinline__ void wait_vmcnt() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
@@ -155,16 +162,11 @@ struct Tile {
   static constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N, TM = WM / 32, TN = WN / 32;
   static constexpr int TM16 = WM / 16, TN16 = WN / 16;   // 16 x 16 MFMA blocks per wave tile
   static constexpr int PARTS = PARTS_;                   // parts the A blocks of a k step are multiplied in
-  static constexpr int STAT_COLS = BN < 128 ? BN : 128;  // columns per sum of squares that the residual epilogue leaves
+  static constexpr int STAT_COLS = 2 * WN;               // columns per sum of squares that the residual epilogue leaves
   static constexpr int CPR = BK / 8;                     // 16-byte chunks per tile row
   static constexpr int LA = BM * CPR / NT, LW = BN * CPR / NT;   // load instructions per thread and stage
   static constexpr int STAGE_BYTES = (BM + BN) * BK * 2;
-  // fp32 epilogue staging (residual add, fp32 outputs): the tile's columns in 2 passes, or 4
-  // where two would not fit LDS
-  static constexpr int EPI_PASSES = BN == 64 ? 1 : BM * (BN / 2 * 4 + 16) <= 136 * 1024 ? 2 : 4;
-  static constexpr int EPI_BYTES_A = BM * (BN / EPI_PASSES * 4 + 16), EPI_BYTES_V = (BN / EPI_PASSES) * (BM * 4 + 16);
-  static constexpr int RING = STAGES * STAGE_BYTES;
-  static constexpr int LDS_BYTES = (RING > EPI_BYTES_A ? RING : EPI_BYTES_A) > EPI_BYTES_V ? (RING > EPI_BYTES_A ? RING : EPI_BYTES_A) : EPI_BYTES_V;
+  static constexpr int LDS_BYTES = STAGES * STAGE_BYTES;
   static_assert(BK == 64, "BK: the main loop is written for two MFMA k steps of 32 per stage");
   static_assert((BM * CPR) % NT == 0 && (BN * CPR) % NT == 0, "tile / thread mismatch");
   static_assert(WM % 32 == 0 && WN % 32 == 0, "wave tile");
@@ -372,7 +374,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int m0, const
   // per-segment sums the producing GEMM left.  Computed first, so that the loads complete in
   // the shadow of the main loop, and kept in LDS behind the stages and the staging area (the
   // barriers of the main loop make it visible to the epilogue).
-  float* const row_scale = (float*)(lds + T::LDS_BYTES + lds_extra<T, EPI>());
+  float* const row_scale = (float*)(lds + T::LDS_BYTES);
   constexpr bool CONSUMER = EPI == EPI_GELU || EPI == EPI_QKV;
   const bool scaled = CONSUMER && g.stats_in != nullptr;
   // The order of the additions is the same whichever tile left the sums and whichever takes them:
@@ -406,22 +408,22 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int m0, const
       }
       row_scale[r] = 1.0f / sqrtf(fmaf(ss, g.stats_inv_dim, g.stats_eps));
     }
+  } else if (CONSUMER) {
+    for (int r = tid; r < BM; r += NT) row_scale[r] = 1.0f;
   }
 
-  // bf16 store / activation epilogue: its bias values (4 columns per 8-column group of the
-  // lane) are fetched here, so that their latency passes in the shadow of the main loop; the
-  // largest tile has no registers to spare for them and fetches them in the epilogue
-  constexpr bool BF16_EPI = (EPI == EPI_STORE || EPI == EPI_GELU) && OUT == OUT_BF16 && !VMODE;
-  constexpr bool BIAS_PRE = BF16_EPI && BM * BN <= 256 * 256;
-  [[maybe_unused]] uint2 bb[TN][2];
+  // The epilogue's bias values (4 columns per 16-column block of the lane) are fetched here, so that their
+  // latency passes in the shadow of the main loop; the largest tile has no registers to spare for them
+  // and fetches them in the epilogue
+  constexpr int TN16 = T::TN16;
+  constexpr bool BIAS_USED = !VMODE && EPI != EPI_RESIDUAL && OUT == OUT_BF16, BIAS_PRE = BIAS_USED && BM * BN <= 256 * 256;
+  [[maybe_unused]] uint2 bb[TN16];
   auto load_bias = [&]() {
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int c = 0; c < 2; ++c) {
-        const int nb = n0 + wn * WN + j * 32 + c * 16 + g4 * 4;
-        bb[j][c] = (g.bias && nb < g.N) ? *(const uint2*)((const uint16_t*)g.bias + nb) : make_uint2(0u, 0u);   // N is a multiple of 4
-      }
+    for (int w = 0; w < TN16; ++w) {
+      const int nb = n0 + wn * WN + w * 16 + g4 * 4;
+      bb[w] = (g.bias && nb < g.N) ? *(const uint2*)((const uint16_t*)g.bias + nb) : make_uint2(0u, 0u);   // N is a multiple of 4
+    }
   };
   if constexpr (BIAS_PRE) load_bias();
 
@@ -459,7 +461,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int m0, const
   // slice sl = (k step ks = sl / P, part p = sl % P of the A blocks): slice (ks, 0) needs the
   // TN16 W fragments of the k step and the first AP A fragments, the others the next AP A
   // fragments.  W fragments alternate between two buffers by k step, A fragments by slice.
-  constexpr int TM16 = T::TM16, TN16 = T::TN16, P = T::PARTS, AP = TM16 / P, NSL = 2 * P;
+  constexpr int TM16 = T::TM16, P = T::PARTS, AP = TM16 / P, NSL = 2 * P;
   static_assert(TM16 % P == 0 && TN16 + AP <= 15, "slices / LDS counter");
   const uint32_t lds0 = (uint32_t)(size_t)EPD_LPTR(lds);
   // Address of k step 1 = address of k step 0 with bit 6 flipped (chunk slot bit 2; the row
@@ -510,23 +512,43 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int m0, const
   using I0 = std::integral_constant<int, 0>;
   using LAST = std::integral_constant<int, NSL - 1>;
 
-  // Residual rows this thread updates in the epilogue (EPI_RESIDUAL, where its whole share is
-  // at most 16 float4): fetched behind the last stage hand-over, so that the read of the
-  // residual stream overlaps the last K step instead of standing at the head of the epilogue.
-  // Rows and columns beyond the matrix are clamped (what they fetch is not used).
-  constexpr int E_HALF = BN / T::EPI_PASSES, E_LPR4 = E_HALF / 4, E_RPS = NT / E_LPR4, E_SW = BM / E_RPS;
-  constexpr bool PREF = EPI == EPI_RESIDUAL && !VMODE && T::EPI_PASSES * E_SW <= 16;
-  [[maybe_unused]] float4 xpre[PREF ? T::EPI_PASSES * E_SW : 1];
-  auto prefetch_resid = [&]() {
+  // What the epilogue adds to or multiplies with the accumulators of a 16-token block: as many fp32 values as it has --
+  // of the residual rows (EPI_RESIDUAL, lanes along rows), or cos and sin of the lane's rotary pairs (EPI_QKV).
+  // Where all of it is at most 16 loads they are issued behind the last stage hand-over, so that they
+  // overlap the last K step; otherwise AUX blocks are kept in flight through the epilogue.
+  constexpr int FC = WN / 4, FR = 64 / FC;              // lanes per row of fp32 values, rows per access of a wave
+  constexpr bool HAS_AUX = !VMODE && (EPI == EPI_RESIDUAL || EPI == EPI_QKV);
+  constexpr bool PREF = HAS_AUX && TM16 * TN16 <= 16;
+  constexpr int AUX = PREF ? TM16 : BM > 256 ? (EPI == EPI_QKV ? 2 : 3) : 4;
+  [[maybe_unused]] float4 aux[HAS_AUX ? AUX : 1][TN16];
+  const int rows_left = max(0, min(WM, g.M - m0 - wm * WM));       // rows of the wave's tile that exist
+  [[maybe_unused]] const uint32_t aux_pitch = EPI == EPI_QKV ? (uint32_t)g.rot_pairs * 8u : (uint32_t)g.ldr * 4u;
+  [[maybe_unused]] uint32_t aux_off[EPI == EPI_QKV ? TN16 : 1];
+  [[maybe_unused]] __amdgpu_buffer_rsrc_t aux_rows;
+  if constexpr (HAS_AUX) {
+    aux_rows = row_window((EPI == EPI_QKV ? (const char*)g.rot : (const char*)g.resid) + (size_t)(m0 + wm * WM) * aux_pitch, (size_t)rows_left * aux_pitch);
+    if constexpr (EPI == EPI_QKV) {
+#pragma unroll
+      for (int w = 0; w < TN16; ++w) aux_off[w] = (uint32_t)l16 * aux_pitch + (uint32_t)(((n0 + wn * WN + w * 16 + g4 * 4) % g.head_dim) >> 1) * 8u;
+    } else {
+      const int n = n0 + wn * WN + (lane % FC) * 4;
+      aux_off[0] = n < g.N ? (uint32_t)(lane / FC) * aux_pitch + (uint32_t)n * 4u : OUTSIDE;
+    }
+  }
+  auto load_aux = [&](int b) {
+    if constexpr (HAS_AUX) {
+#pragma unroll
+      for (int w = 0; w < TN16; ++w) {
+        const uint32_t off = aux_off[EPI == EPI_QKV ? w : 0] + (uint32_t)(b * 16 + (EPI == EPI_QKV ? 0 : w * FR)) * aux_pitch;
+        aux[b % AUX][w] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(aux_rows, off, 0, 0));
+      }
+    }
+  };
+  auto prefetch_aux = [&]() {
     if constexpr (PREF) {
+      if (EPI == EPI_QKV && !g.rot) return;
 #pragma unroll
-      for (int h = 0; h < T::EPI_PASSES; ++h)
-#pragma unroll
-        for (int sw = 0; sw < E_SW; ++sw) {
-          const int m = min(m0 + sw * E_RPS + tid / E_LPR4, g.M - 1);
-          const int n = min(n0 + h * E_HALF + (tid % E_LPR4) * 4, g.N - 4);
-          xpre[h * E_SW + sw] = *(const float4*)(g.resid + (size_t)m * g.ldr + n);
-        }
+      for (int b = 0; b < TM16; ++b) load_aux(b);
     }
   };
 
@@ -560,10 +582,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int m0, const
     const uint32_t a_lane = (uint32_t)lrow * (uint32_t)g.lda * 2u + lcol, w_lane = (uint32_t)lrow * (uint32_t)ldw * 2u + lcol;
     // gathered operand: the tile's row numbers lie in LDS, [piece][row]; those of a wave's loads are fetched into
     // registers when a new piece begins (pieces are whole K steps), ahead of the phase that issues the loads
-    [[maybe_unused]] const uint32_t idx0 = lds0 + (uint32_t)(T::LDS_BYTES + lds_extra<T, EPI>() + BM * 4);
+    [[maybe_unused]] const uint32_t idx0 = lds0 + (uint32_t)(T::LDS_BYTES + BM * 4);
     [[maybe_unused]] int src[GATHER ? 2 : 1][GATHER ? 3 : 1], piece[2] = {-1, -1}, kin[2] = {0, 0};
     if constexpr (GATHER) {
-      int* const idx = (int*)(lds + T::LDS_BYTES + lds_extra<T, EPI>() + BM * 4);
+      int* const idx = (int*)(lds + T::LDS_BYTES + BM * 4);
       for (int r = tid; r < BM; r += NT)
         for (int c = 0; c < g.gather_n; ++c) idx[c * BM + r] = g.gather[(size_t)min(m0 + r, g.M - 1) * g.gather_n + c];
       __syncthreads();
@@ -705,7 +727,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int m0, const
       __builtin_amdgcn_s_barrier();
       if constexpr (!inner && !LATE_REFILL) { if (kt + S < nk) issue_step(s, kt + S); }
       read_slice(I0{}, SN{});
-      if constexpr (!inner) { if (kt + 2 >= nk) prefetch_resid(); }          // last hand-over: no operand load follows
+      if constexpr (!inner) { if (kt + 2 >= nk) prefetch_aux(); }          // last hand-over: no operand load follows
     } else {
       wait_slice(LAST{}, std::true_type{});
     }
@@ -731,292 +753,214 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int m0, const
       if (kt + decltype(ST)::value < nk) step(ST, std::false_type{}, kt + decltype(ST)::value);
     });
   }
-  if (nk == 1) prefetch_resid();
+  if (nk == 1) prefetch_aux();
 
   // ------------------------------------------------------------------ epilogue
-  // The accumulators go through LDS (the operand stages are dead by now) so that global
-  // memory sees row-contiguous accesses: straight from the MFMA layout every store
-  // instruction would touch 32 different rows with 16 bytes each.  Four forms follow: the V
-  // tiles of QKV (transposed), bf16 store / activation and Q | K with rotary (passes over row
-  // blocks, described where they stand), and the general one, used by the residual add and
-  // fp32 outputs: two or four passes, each staging a slice of the tile's columns as fp32 (BM
-  // rows x BN/passes floats, rows padded by 16 bytes); then every group of 16 or 32 lanes owns
-  // one row and a lane owns 4 consecutive columns, which is where bias and the residual add
-  // are applied.
-  constexpr int NPASS = T::EPI_PASSES;
-  constexpr int HALF = BN / NPASS;                    // columns per pass
-  constexpr int WPH = T::WAVES_N / NPASS;             // wave columns per pass
-  static_assert(T::WAVES_N % NPASS == 0 && HALF % 32 == 0, "epilogue passes");
-  const uint16_t* bias = (const uint16_t*)g.bias;
-  wait_vmcnt<0>();
   if constexpr (VMODE) {
     // The MFMA operands are swapped for these tiles, so a lane holds 4 consecutive tokens of
-    // one channel: scale and bias are applied there and the bf16 values staged transposed,
-    // ET[channel][token], the whole tile at once where it fits and in two channel halves where
-    // not; a lane then takes 8 consecutive tokens (one 16-byte store) of a channel row.
-    constexpr int ROWV = BM * 2 + 16;
-    constexpr int NPV = BN * ROWV <= T::LDS_BYTES ? 1 : 2;          // passes
-    constexpr int CPV = BN / NPV;                                   // channels per pass
-    static_assert(CPV * ROWV <= T::LDS_BYTES && CPV % WN == 0, "transposed staging area");
+    // one channel: scale and bias are applied there, and 16 channels x up to 128 tokens at a time are staged
+    // in a piece of LDS of the wave's own, [channel][token]; a lane then takes 8 consecutive tokens (one 16-byte
+    // store) of a channel row.  (Staged by the whole block, channel halves on the 320-row tile: 19.4 k clocks a tile.)
+    const uint16_t* bias = (const uint16_t*)g.bias;
     uint16_t* vt = (uint16_t*)g.vt;
-    // thread coordinates derived afresh (through an opaque copy of the thread id): nothing of
-    // this epilogue's index arithmetic is then computed ahead of the main loop and kept in
-    // registers across it, where the largest tile has none to spare
-    int tid_v = threadIdx.x;
-    asm volatile("" : "+v"(tid_v));
-    const int tid = tid_v, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave / T::WAVES_N, wn = wave % T::WAVES_N, l16 = lane & 15, g4 = lane >> 4;
-    // BM tokens per channel row: BM/8 lanes per row, 8 tokens per lane
-    constexpr int LPRV = BM / 8, RPS = NT / LPRV;        // threads beyond RPS whole rows idle
-    const int tl = (tid % LPRV) * 8;
-    const int m = tid < RPS * LPRV ? m0 + tl : g.M;
-    int4 vc0 = make_int4(0, 0, 0, 0), vc1 = make_int4(0, 0, 0, 0);
-    const bool full = m + 7 < g.M;
-    if (full) { vc0 = *(const int4*)(g.vcol + m); vc1 = *(const int4*)(g.vcol + m + 4); }
-    const bool fast = full && (vc1.w - vc0.x == 7) && ((vc0.x & 7) == 0);
+    float bv[TN16];
 #pragma unroll
-    for (int ps = 0; ps < NPV; ++ps) {
-      __syncthreads();
-      if ((wn * WN) / CPV == ps) {
-#pragma unroll
-        for (int jc = 0; jc < 2 * TN; ++jc) {
-          const int j = jc >> 1, c = jc & 1;
-          const int chl = wn * WN + jc * 16 + l16;       // channel inside the tile
-          const float bv = (bias && n0 + chl < g.N) ? bf16_bits_to_float(bias[n0 + chl]) : 0.f;
-#pragma unroll
-          for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int t = 0; t < 2; ++t) {
-              const int ml = wm * WM + i * 32 + t * 16 + g4 * 4;
-              const f32x4 a = acc[i][j][2 * t + c];
-              float4 rs = make_float4(1.f, 1.f, 1.f, 1.f);
-              if (scaled) rs = *(const float4*)(row_scale + ml);
-              *(uint2*)(lds + (chl - ps * CPV) * ROWV + ml * 2) =
-                  pack_bf16x4(fmaf(a[0], rs.x, bv), fmaf(a[1], rs.y, bv), fmaf(a[2], rs.z, bv), fmaf(a[3], rs.w, bv));
-            }
-        }
-      }
-      __syncthreads();
-      for (int r = tid / LPRV; r < CPV; r += RPS) {
-        const int n = n0 + ps * CPV + r;
-        if (n >= g.N || m >= g.M) continue;
-        const uint4 p = *(const uint4*)(lds + r * ROWV + tl * 2);
-        uint16_t* vrow = vt + (size_t)(n - g.qk_cols) * g.vt_stride;
-        if (fast) {
-          *(uint4*)(vrow + vc0.x) = p;
-        } else {
-          const uint32_t w[4] = {p.x, p.y, p.z, p.w};
-          for (int t = 0; t < 8 && m + t < g.M; ++t) vrow[g.vcol[m + t]] = (uint16_t)(w[t >> 1] >> ((t & 1) * 16));
-        }
-      }
+    for (int w = 0; w < TN16; ++w) {
+      const int n = n0 + wn * WN + w * 16 + l16;
+      bv[w] = bias && n < g.N ? bf16_bits_to_float(bias[n]) : 0.f;
     }
-  } else if constexpr ((EPI == EPI_STORE || EPI == EPI_GELU) && OUT == OUT_BF16) {
-    // bf16 output with a per-element epilogue that needs nothing but the element and its
-    // column: scale, bias and activation are applied in the MFMA layout (a lane holds 4
-    // consecutive columns of one token) and the finished bf16 values are staged through LDS to
-    // leave as 16-byte pieces of whole rows.  The passes split the tile by rows: pass i takes
-    // row block i of every wave (32 rows per wave row, all BN columns), so every wave -- every
-    // SIMD -- does a share of the activation arithmetic in every pass, and a row leaves as
-    // BN * 2 contiguous bytes.  Two staging buffers alternate, which leaves one barrier per
-    // pass: a buffer is rewritten two passes later, behind the barrier of the pass between.
-    constexpr int SR = T::WAVES_M * 32;                // rows per pass
-    constexpr int ROWO = BN * 2 + 16;                  // padded: 16 consecutive rows hit 16 different bank groups
-    constexpr int BUF = SR * ROWO;
-    constexpr int CPRO = BN / 8, RPSO = NT / CPRO;     // 16-byte chunks per row, rows per sweep
-    static_assert(2 * BUF <= T::LDS_BYTES && SR % RPSO == 0 && NT % CPRO == 0, "bf16 staging area");
-    uint16_t* const outp = (uint16_t*)g.out;
-    const int c8 = (tid % CPRO) * 8;
-    const int n = n0 + c8;
-    const bool vec = (g.ldo % 8 == 0) && (((size_t)outp & 15) == 0) && n + 8 <= g.N;
-    if constexpr (!BIAS_PRE) load_bias();
-    __syncthreads();                                   // the operand stages are dead from here on
+    static_assert(T::WAVES_M * T::WAVES_N * 16 * 256 <= T::LDS_BYTES, "transposed staging area");
+    char* const stg = lds + wave * 16 * 256;
+    __builtin_amdgcn_s_barrier();                        // the operand stages are dead from here on (all reads of them were waited for)
+    auto part = [&](auto FIRST, auto COUNT) {            // 16-token blocks FIRST .. FIRST + COUNT - 1 of the wave's rows
+      constexpr int b0 = decltype(FIRST)::value, nb = decltype(COUNT)::value;
+      constexpr int CHV = 2 * nb, RPV = 64 / CHV;        // 8-token chunks per channel row, rows per read
+      auto chunk = [](int row, int c) { return row * (nb * 32) + ((nb == 8 ? c ^ row : nb == 4 ? c ^ T::swz(row) : c ^ ((row >> 2) & 3)) * 16); };
+      const int m = m0 + wm * WM + b0 * 16 + (lane % CHV) * 8;
+      int4 vc0 = make_int4(0, 0, 0, 0), vc1 = make_int4(0, 0, 0, 0);
+      const bool full = m + 7 < g.M;
+      if (full) { vc0 = *(const int4*)(g.vcol + m); vc1 = *(const int4*)(g.vcol + m + 4); }
+      // eight tokens side by side, or twice four: items whose first token is a multiple of four and not of eight
+      const bool eight = full && (vc1.w - vc0.x == 7) && ((vc0.x & 7) == 0);
+      const bool fours = full && vc0.w - vc0.x == 3 && vc1.w - vc1.x == 3 && ((vc0.x | vc1.x) & 3) == 0;
 #pragma unroll
-    for (int i = 0; i < TM; ++i) {
-      char* const buf = lds + (i & 1) * BUF;
+      for (int w = 0; w < TN16; ++w) {
 #pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        const float rs = scaled ? row_scale[wm * WM + i * 32 + t * 16 + l16] : 1.0f;
+        for (int b = 0; b < nb; ++b) {
+          const f32x4 a = acc[(b0 + b) >> 1][w >> 1][((b0 + b) & 1) * 2 + (w & 1)];
+          const float4 rs = *(const float4*)(row_scale + wm * WM + (b0 + b) * 16 + g4 * 4);
+          *(uint2*)(stg + chunk(l16, b * 2 + (g4 >> 1)) + (g4 & 1) * 8) =
+              pack_bf16x4(fmaf(a[0], rs.x, bv[w]), fmaf(a[1], rs.y, bv[w]), fmaf(a[2], rs.z, bv[w]), fmaf(a[3], rs.w, bv[w]));
+        }
+        asm volatile("" ::: "memory");                   // other lanes' pieces are read below: LDS takes a wave's accesses in order
+        uint4 p[16 / RPV];
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
+        for (int k = 0; k < 16 / RPV; ++k) p[k] = *(const uint4*)(stg + chunk(k * RPV + lane / CHV, lane % CHV));
+        asm volatile("" ::: "memory");
 #pragma unroll
-          for (int c = 0; c < 2; ++c) {
-            const int nl = wn * WN + j * 32 + c * 16 + g4 * 4;       // column inside the tile
-            const f32x4 a = acc[i][j][2 * t + c];
-            const float b0 = bf16_bits_to_float(bb[j][c].x & 0xffff), b1 = bf16_bits_to_float(bb[j][c].x >> 16);
-            const float b2 = bf16_bits_to_float(bb[j][c].y & 0xffff), b3 = bf16_bits_to_float(bb[j][c].y >> 16);
-            float v0 = fmaf(a[0], rs, b0), v1 = fmaf(a[1], rs, b1), v2 = fmaf(a[2], rs, b2), v3 = fmaf(a[3], rs, b3);
-            if constexpr (EPI == EPI_GELU) {
-              if (g.act == 0) { v0 = gelu_erf_fast(v0); v1 = gelu_erf_fast(v1); v2 = gelu_erf_fast(v2); v3 = gelu_erf_fast(v3); }
-              else { v0 = gelu_tanh_fast(v0); v1 = gelu_tanh_fast(v1); v2 = gelu_tanh_fast(v2); v3 = gelu_tanh_fast(v3); }
-            }
-            *(uint2*)(buf + (wm * 32 + t * 16 + l16) * ROWO + nl * 2) = pack_bf16x4(v0, v1, v2, v3);
-          }
-      }
-      __syncthreads();
-      if (n < g.N) {
-#pragma unroll
-        for (int sw = 0; sw < SR / RPSO; ++sw) {
-          const int r = sw * RPSO + tid / CPRO;
-          const int m = m0 + (r / 32) * WM + i * 32 + (r % 32);
-          if (m >= g.M) continue;
-          const uint4 v = *(const uint4*)(buf + r * ROWO + c8 * 2);
-          uint16_t* dst = outp + (size_t)m * g.ldo + n;
-          if (vec) {
-            *(uint4*)dst = v;
+        for (int k = 0; k < 16 / RPV; ++k) {
+          const int n = n0 + wn * WN + w * 16 + k * RPV + lane / CHV;
+          if (n >= g.N || m >= g.M) continue;
+          uint16_t* vrow = vt + (size_t)(n - g.qk_cols) * g.vt_stride;
+          if (eight) {
+            *(uint4*)(vrow + vc0.x) = p[k];
+          } else if (fours) {
+            *(uint2*)(vrow + vc0.x) = make_uint2(p[k].x, p[k].y);
+            *(uint2*)(vrow + vc1.x) = make_uint2(p[k].z, p[k].w);
           } else {
-            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-            for (int t = 0; t < 8 && n + t < g.N; ++t) dst[t] = (uint16_t)(w[t >> 1] >> ((t & 1) * 16));
+            const uint32_t u[4] = {p[k].x, p[k].y, p[k].z, p[k].w};
+            for (int t = 0; t < 8 && m + t < g.M; ++t) vrow[g.vcol[m + t]] = (uint16_t)(u[t >> 1] >> ((t & 1) * 16));
           }
         }
       }
-    }
-  } else if constexpr (EPI == EPI_QKV) {
-    // Q | K columns with rotary: the passes split the tile by rows, not by columns.  Pass i
-    // stages row block i of every wave (32 rows per wave row, all BN columns, fp32), so all
-    // waves write at once and a wave then reads and stores whole rows (BN * 2 bytes contiguous
-    // in memory).  The cos / sin entries of the tile's tokens are one contiguous slab of the
-    // table; it is copied into LDS behind the staging area by direct-to-LDS loads issued before
-    // the first pass is staged, and every pass reads its entries from there (fetched from
-    // memory per pass, their latency was more than half of this epilogue).  Staging rows are
-    // unpadded and swizzled instead, 16-byte chunk c of row r at chunk c ^ (r % 16): staging
-    // plus a table of up to 256 + QKV_TABLE_EXTRA bytes per token then fill the operand stages
-    // exactly.  Larger tables (head_dim > 72) are read from memory.
-    constexpr int SR = T::WAVES_M * 32;                // rows per pass
-    constexpr int ROWE = BN * 4;
-    constexpr int STG = SR * ROWE;
-    constexpr int LPR4 = BN / 4, RPS = NT / LPR4;      // lanes per row (4 columns each), rows per sweep
-    static_assert(STG <= T::LDS_BYTES && SR % RPS == 0 && NT % LPR4 == 0 && LPR4 >= 16, "row-split staging");
-    const int cl = (tid % LPR4) * 4;
-    const int n = n0 + cl;                             // N is a multiple of 4: all or nothing
-    float b0 = 0.f, b1 = 0.f, b2 = 0.f, b3 = 0.f;
-    if (bias && n < g.N) {
-      const uint2 bb = *(const uint2*)(bias + n);
-      b0 = bf16_bits_to_float(bb.x & 0xffff); b1 = bf16_bits_to_float(bb.x >> 16);
-      b2 = bf16_bits_to_float(bb.y & 0xffff); b3 = bf16_bits_to_float(bb.y >> 16);
-    }
-    const int pr = (n % g.head_dim) >> 1;              // even: two pairs = one 16-byte entry
-    const int trb = g.rot_pairs * 8;                   // table bytes per token
-    const bool tab_lds = g.rot != nullptr && STG + BM * trb <= T::LDS_BYTES + lds_extra<T, EPI>();
-    const char* const tab = lds + STG;
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-      __syncthreads();
-      if (i == 0 && tab_lds) {
-        // BM * trb bytes from row m0 of the table, 16 bytes per lane, a wave fills 1 KB of LDS
-        // per instruction; rows past M are never used: their chunks re-read the last valid one
-        const char* src = (const char*)g.rot + (size_t)m0 * trb;
-        const long last = (long)(g.M - m0) * trb - 16;
-        for (int c0 = wave * 64; c0 < BM * (trb / 16); c0 += NT)
-          __builtin_amdgcn_global_load_lds(EPD_GPTR(src + min((long)(c0 + lane) * 16, last)), EPD_LPTR(tab + c0 * 16), 16, 0, 0);
-      }
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int sr = wm * 32 + (q >> 1) * 16 + l16;
-          const int ch = (wn * WN + j * 32 + (q & 1) * 16) / 4 + g4;
-          const f32x4 a = acc[i][j][q];
-          *(float4*)(lds + sr * ROWE + (ch ^ (sr & 15)) * 16) = make_float4(a[0], a[1], a[2], a[3]);
-        }
-      if (i == 0) wait_vmcnt<0>();
-      __syncthreads();
-      if (n < g.N) {
-        // fully unrolled so that the LDS reads of all sweeps are in flight together
-#pragma unroll
-        for (int sw = 0; sw < SR / RPS; ++sw) {
-          const int r = sw * RPS + tid / LPR4;
-          const int ml = (r / 32) * WM + i * 32 + (r % 32);
-          const int m = m0 + ml;
-          if (m >= g.M) continue;
-          const float4 e = *(const float4*)(lds + r * ROWE + (((tid % LPR4) ^ (r & 15)) * 16));
-          const float rs = scaled ? row_scale[ml] : 1.0f;
-          float v0 = fmaf(e.x, rs, b0), v1 = fmaf(e.y, rs, b1), v2 = fmaf(e.z, rs, b2), v3 = fmaf(e.w, rs, b3);
-          if (g.rot) {
-            const float4 cs = tab_lds ? *(const float4*)(tab + ml * trb + pr * 8)
-                                      : *(const float4*)(g.rot + (size_t)m * g.rot_pairs + pr);
-            const bool sin_last = i == TM - 1 && sw == SR / RPS - 1 && (BM >= 128 || ((m0 & 64) && ml >= 56));
-            rotate_pair(v0, v1, cs.x, cs.y, sin_last);
-            rotate_pair(v2, v3, cs.z, cs.w, sin_last);
-          }
-          // the softmax scale (in log2 units) rides on Q: one rounding of q * scale instead of
-          // a multiply per score in the attention kernel
-          if (n < g.q_cols) { v0 *= g.q_scale; v1 *= g.q_scale; v2 *= g.q_scale; v3 *= g.q_scale; }
-          *(uint2*)((uint16_t*)g.out + (size_t)m * g.ldo + n) = pack_bf16x4(v0, v1, v2, v3);
-        }
-      }
-    }
+    };
+    static_assert(TM16 == 2 || TM16 == 4 || TM16 == 8 || TM16 == 10, "token parts");
+    part(I0{}, std::integral_constant<int, TM16 < 8 ? TM16 : 8>{});
+    if constexpr (TM16 == 10) part(std::integral_constant<int, 8>{}, std::integral_constant<int, 2>{});
   } else {
-    constexpr int ROWE = HALF * 4 + 16;
-    constexpr int LPR4 = HALF / 4, RPS = NT / LPR4;    // lanes per row (4 columns each), rows per sweep
-    static_assert(BM % RPS == 0, "sweeps");
-    const int cl = (tid % LPR4) * 4;                   // first of the lane's 4 columns inside the half
-    static_assert(HALF == T::STAT_COLS || 2 * HALF == T::STAT_COLS, "sum-of-squares segments");
-    [[maybe_unused]] float seg_ss[BM / RPS];
+    // Everything else goes 16 tokens x WN columns at a time through a piece of LDS of the wave's own, from which it
+    // leaves as whole 128- or 256-byte lines: no wave waits for another.  bf16 results are finished where the
+    // accumulators stand -- a lane holds four consecutive columns of one token in each 16-column block; fp32 rows
+    // (residual stream, fp32 outputs) are turned first, then read and written as rows (from where the
+    // accumulators stand an access touches 16 rows of 64 bytes each: residual add of 256 x 256, 35 k clocks).
+    //   It replaced passes of the whole block over row or column slices of the tile in fp32, a barrier or two each,
+    // with the rotary table copied to LDS or (head_dim 128) read where it was used.  Clocks per 256 x 256 tile:
+    // residual add 38.6 k -> 17.8 k (with all units at it, HBM at its limit, 70 k -> 37 k), GELU 19.9 k -> 9.1 k, Q | K with
+    // rotary 22 k -> 16 k (its table: 64-byte pieces of rows, half the address unit's rate), plain store 6.0 k -> 3.9 k.
+    constexpr bool F32_ROWS = EPI == EPI_RESIDUAL || OUT == OUT_F32;
+    constexpr int SROW = WN * (F32_ROWS ? 4 : 2), CH = SROW / 16, RPI = 64 / CH;   // bytes and 16-byte chunks per staged row, rows per read
+    static_assert(T::WAVES_M * T::WAVES_N * 16 * SROW + T::WAVES_N * BM * 4 <= T::LDS_BYTES, "staging area");
+    if constexpr (BIAS_USED && !BIAS_PRE) load_bias();
+    __builtin_amdgcn_s_barrier();                        // the operand stages are dead from here on (all reads of them were waited for)
+    char* const stg = lds + wave * 16 * SROW;
+    // rows of 256 bytes: chunk ^ row; of 128 (64): two (four) rows share the banks' 256 bytes
+    auto schunk = [](int row, int c) { return row * SROW + ((SROW == 256 ? c ^ row : SROW == 128 ? c ^ T::swz(row) : c ^ ((row >> 2) & 3)) * 16); };
+    if constexpr (F32_ROWS) {
+      const int n = n0 + wn * WN + (lane % FC) * 4;      // N is a multiple of 4: all or nothing
+      const bool sums = EPI == EPI_RESIDUAL && g.stats_out != nullptr;
+      const uint32_t out_pitch = EPI == EPI_RESIDUAL ? (uint32_t)g.ldxb * 2u : (uint32_t)g.ldo * 4u;
+      const uint32_t out_off = n < g.N ? (uint32_t)(lane / FC) * out_pitch + (uint32_t)n * (EPI == EPI_RESIDUAL ? 2u : 4u) : OUTSIDE;
+      const char* const out0 = EPI == EPI_RESIDUAL ? (const char*)g.xb : (const char*)g.out;      // no bf16 copy wanted: an empty window
+      const __amdgpu_buffer_rsrc_t out_rows = row_window(out0 + (size_t)(m0 + wm * WM) * out_pitch, out0 ? (size_t)rows_left * out_pitch : 0);
+      float* const part = (float*)(lds + T::WAVES_M * T::WAVES_N * 16 * SROW);   // [WAVES_N][BM] sums of squares per wave
+      uint2 br = make_uint2(0u, 0u);
+      if (g.bias && n < g.N) br = *(const uint2*)((const uint16_t*)g.bias + n);
+      const float b0 = bf16_bits_to_float(br.x & 0xffff), b1 = bf16_bits_to_float(br.x >> 16);
+      const float b2 = bf16_bits_to_float(br.y & 0xffff), b3 = bf16_bits_to_float(br.y >> 16);
+      [[maybe_unused]] float ss = 0.f;
+      if constexpr (HAS_AUX && !PREF) {
 #pragma unroll
-    for (int h = 0; h < NPASS; ++h) {
-      __syncthreads();
-      if (wn / WPH == h) {
+        for (int b = 0; b < AUX; ++b) load_aux(b);
+      }
 #pragma unroll
-        for (int i = 0; i < TM; ++i) {
+      for (int b = 0; b < TM16; ++b) {
 #pragma unroll
-          for (int j = 0; j < TN; ++j)
+        for (int w = 0; w < TN16; ++w) {
+          const f32x4 a = acc[b >> 1][w >> 1][(b & 1) * 2 + (w & 1)];
+          *(float4*)(stg + schunk(l16, w * 4 + g4)) = make_float4(a[0], a[1], a[2], a[3]);
+        }
+        asm volatile("" ::: "memory");                 // other lanes' pieces are read below: LDS takes a wave's accesses in order
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-              const int ml = wm * WM + i * 32 + (q >> 1) * 16 + l16;
-              const int nl = (wn % WPH) * WN + j * 32 + (q & 1) * 16 + g4 * 4;
-              const f32x4 a = acc[i][j][q];
-              *(float4*)(lds + ml * ROWE + nl * 4) = make_float4(a[0], a[1], a[2], a[3]);
+        for (int w = 0; w < TN16; ++w) {
+          const int c = b * TN16 + w;                  // rows c * FR + lane / FC of the wave's tile
+          const float4 e = *(const float4*)(stg + schunk(w * FR + lane / FC, lane % FC));
+          const float v0 = e.x + b0, v1 = e.y + b1, v2 = e.z + b2, v3 = e.w + b3;
+          if constexpr (EPI == EPI_RESIDUAL) {
+            float4 x = aux[b % AUX][w];
+            x.x += v0; x.y += v1; x.z += v2; x.w += v3;
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x), aux_rows, aux_off[0] + (uint32_t)(c * FR) * aux_pitch, 0, 0);
+            // folded RMSNorm (producer side): the raw rows in bf16 for the next GEMM, and their sums of squares per
+            // STAT_COLS columns, which are two waves' shares; lane c % FC of a row's lanes keeps the sum of its row c
+            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, pack_bf16x4(x.x, x.y, x.z, x.w)), out_rows, out_off + (uint32_t)(c * FR) * out_pitch, 0, 0);
+            // (made also where nobody takes them: a branch here would cut the loops into pieces that do not overlap)
+            const float r = group_sum<FC>(fmaf(x.x, x.x, fmaf(x.y, x.y, fmaf(x.z, x.z, x.w * x.w))));
+            ss = lane % FC == c % FC ? r : ss;
+            if (c % FC == FC - 1 || c == TM16 * TN16 - 1) {
+              const int row = (c / FC * FC + lane % FC) * FR + lane / FC;
+              if (c % FC == FC - 1 || row < WM) part[wn * BM + wm * WM + row] = ss;
             }
+          } else {
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, make_float4(v0, v1, v2, v3)), out_rows, out_off + (uint32_t)(c * FR) * out_pitch, 0, 0);
+          }
+        }
+        if constexpr (HAS_AUX && !PREF) { if (b + AUX < TM16) load_aux(b + AUX); }
+        asm volatile("" ::: "memory");
+      }
+      if (sums) {
+        __syncthreads();
+        constexpr int SEGS = T::WAVES_N / 2;
+        for (int r = tid; r < BM * SEGS; r += NT) {
+          const int seg = r / BM, ml = r % BM, m = m0 + ml;
+          if (m < g.M && n0 + seg * T::STAT_COLS < g.N)
+            g.stats_out[(size_t)m * g.stats_n + n0 / T::STAT_COLS + seg] = part[2 * seg * BM + ml] + part[(2 * seg + 1) * BM + ml];
         }
       }
-      __syncthreads();
-      const int n = n0 + h * HALF + cl;
-      if (n >= g.N) continue;                          // N is a multiple of 4: all or nothing
-      float b0 = 0.f, b1 = 0.f, b2 = 0.f, b3 = 0.f;
-      if (bias) {
-        const uint2 bb = *(const uint2*)(bias + n);
-        b0 = bf16_bits_to_float(bb.x & 0xffff); b1 = bf16_bits_to_float(bb.x >> 16);
-        b2 = bf16_bits_to_float(bb.y & 0xffff); b3 = bf16_bits_to_float(bb.y >> 16);
-      }
-      // fully unrolled so that the residual loads / LDS reads of all sweeps are in flight together
+    } else {
+      uint16_t* const outp = (uint16_t*)g.out;
+      const int ns = n0 + wn * WN + (lane % CH) * 8;     // first column of the lane's 16-byte piece of a staged row
+      const uint32_t out_pitch = (uint32_t)g.ldo * 2u, out_off = ns < g.N ? (uint32_t)(lane / CH) * out_pitch + (uint32_t)ns * 2u : OUTSIDE;
+      const __amdgpu_buffer_rsrc_t out_rows = row_window(outp + (size_t)(m0 + wm * WM) * g.ldo, (size_t)rows_left * out_pitch);
+      float bias[TN16][4], qs[TN16];
 #pragma unroll
-      for (int sw = 0; sw < BM / RPS; ++sw) {
-        const int r = sw * RPS + tid / LPR4;
-        const int m = m0 + r;
-        if (m >= g.M) continue;
-        const float4 e = *(const float4*)(lds + r * ROWE + cl * 4);
-        const float rs = scaled ? row_scale[r] : 1.0f;
-        float v0 = fmaf(e.x, rs, b0), v1 = fmaf(e.y, rs, b1), v2 = fmaf(e.z, rs, b2), v3 = fmaf(e.w, rs, b3);
-        if constexpr (EPI == EPI_GELU) {
-          if (g.act == 0) { v0 = gelu_erf_fast(v0); v1 = gelu_erf_fast(v1); v2 = gelu_erf_fast(v2); v3 = gelu_erf_fast(v3); }
-          else { v0 = gelu_tanh_fast(v0); v1 = gelu_tanh_fast(v1); v2 = gelu_tanh_fast(v2); v3 = gelu_tanh_fast(v3); }
+      for (int w = 0; w < TN16; ++w) {
+        bias[w][0] = bf16_bits_to_float(bb[w].x & 0xffff); bias[w][1] = bf16_bits_to_float(bb[w].x >> 16);
+        bias[w][2] = bf16_bits_to_float(bb[w].y & 0xffff); bias[w][3] = bf16_bits_to_float(bb[w].y >> 16);
+        // the softmax scale (in log2 units) rides on Q: one rounding of q * scale instead of
+        // a multiply per score in the attention kernel
+        qs[w] = n0 + wn * WN + w * 16 + g4 * 4 < g.q_cols ? g.q_scale : 1.0f;
+      }
+      // VARIANT: tanh instead of erf (GELU), rotary embedding (QKV), rows that do not start on 16 bytes (STORE; N and ldo
+      // are multiples of 8) -- outside of the loops, so that these are one
+      // block of code in which loads, arithmetic and stores of different tokens overlap
+      auto rows = [&](auto VARIANT) {
+        constexpr bool variant = decltype(VARIANT)::value;
+        if constexpr (variant && HAS_AUX && !PREF) {
+#pragma unroll
+          for (int b = 0; b < AUX; ++b) load_aux(b);
         }
-        if constexpr (EPI == EPI_RESIDUAL) {
-          float4* xp = (float4*)(g.resid + (size_t)m * g.ldr + n);
-          float4 x;
-          if constexpr (PREF) x = xpre[h * E_SW + sw];
-          else x = *xp;
-          x.x += v0; x.y += v1; x.z += v2; x.w += v3;
-          *xp = x;
-          // folded RMSNorm (producer side): the raw rows in bf16 for the next GEMM, and their
-          // sums of squares per segment of T::STAT_COLS columns (64 in the 64 x 64 tile, else 128;
-          // where a pass has half as many, two passes make one segment)
-          if (g.xb) *(uint2*)((uint16_t*)g.xb + (size_t)m * g.ldxb + n) = pack_bf16x4(x.x, x.y, x.z, x.w);
-          if (g.stats_out) {
-            const float ss = group_sum<LPR4>(fmaf(x.x, x.x, fmaf(x.y, x.y, fmaf(x.z, x.z, x.w * x.w))));
-            if constexpr (HALF == T::STAT_COLS) {
-              if ((tid % LPR4) == 0) g.stats_out[(size_t)m * g.stats_n + (n0 + h * HALF) / HALF] = ss;
+#pragma unroll
+        for (int b = 0; b < TM16; ++b) {
+          const int ml = wm * WM + b * 16 + l16;
+          const float rs = CONSUMER ? row_scale[ml] : 1.0f;
+#pragma unroll
+          for (int w = 0; w < TN16; ++w) {
+            const f32x4 a = acc[b >> 1][w >> 1][(b & 1) * 2 + (w & 1)];
+            float v0 = fmaf(a[0], rs, bias[w][0]), v1 = fmaf(a[1], rs, bias[w][1]), v2 = fmaf(a[2], rs, bias[w][2]), v3 = fmaf(a[3], rs, bias[w][3]);
+            if constexpr (EPI == EPI_GELU) {
+              if constexpr (!variant) { v0 = gelu_erf_fast(v0); v1 = gelu_erf_fast(v1); v2 = gelu_erf_fast(v2); v3 = gelu_erf_fast(v3); }
+              else { v0 = gelu_tanh_fast(v0); v1 = gelu_tanh_fast(v1); v2 = gelu_tanh_fast(v2); v3 = gelu_tanh_fast(v3); }
+            } else if constexpr (EPI == EPI_QKV) {
+              if constexpr (variant) {
+                const float4 cs = aux[b % AUX][w];
+                const bool sin_last = b == TM16 - 1 && (BM >= 128 ? ml >= BM - 8 : (m0 & 64) && ml >= 56);
+                rotate_pair(v0, v1, cs.x, cs.y, sin_last);
+                rotate_pair(v2, v3, cs.z, cs.w, sin_last);
+              }
+              v0 *= qs[w]; v1 *= qs[w]; v2 *= qs[w]; v3 *= qs[w];
+            }
+            *(uint2*)(stg + schunk(l16, w * 2 + (g4 >> 1)) + (g4 & 1) * 8) = pack_bf16x4(v0, v1, v2, v3);
+          }
+          if constexpr (variant && HAS_AUX && !PREF) { if (b + AUX < TM16) load_aux(b + AUX); }
+          asm volatile("" ::: "memory");                 // other lanes' pieces are read below: LDS takes a wave's accesses in order
+#pragma unroll
+          for (int k = 0; k < 16 / RPI; ++k) {
+            const int r = k * RPI + lane / CH;
+            const uint4 v = *(const uint4*)(stg + schunk(r, lane % CH));
+            if constexpr (EPI == EPI_STORE && variant) {
+              const int m = m0 + wm * WM + b * 16 + r;
+              const uint32_t u[4] = {v.x, v.y, v.z, v.w};
+              if (m < g.M && ns < g.N)
+                for (int t = 0; t < 8; ++t) outp[(size_t)m * g.ldo + ns + t] = (uint16_t)(u[t >> 1] >> ((t & 1) * 16));
             } else {
-              seg_ss[sw] = (h % 2 == 0) ? ss : seg_ss[sw] + ss;
-              if (h % 2 == 1 && (tid % LPR4) == 0) g.stats_out[(size_t)m * g.stats_n + (n0 + (h / 2) * 128) / 128] = seg_ss[sw];
+              __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), out_rows, out_off + (uint32_t)(b * 16 + k * RPI) * out_pitch, 0, 0);
             }
           }
-        } else if constexpr (OUT == OUT_F32) {
-          *(float4*)((float*)g.out + (size_t)m * g.ldo + n) = make_float4(v0, v1, v2, v3);
-        } else {
-          *(uint2*)((uint16_t*)g.out + (size_t)m * g.ldo + n) = pack_bf16x4(v0, v1, v2, v3);
+          asm volatile("" ::: "memory");
+          if constexpr (BM > 256) __builtin_amdgcn_sched_barrier(0);
         }
-      }
+      };
+      if ((EPI == EPI_GELU && g.act != 0) || (EPI == EPI_QKV && g.rot) || (EPI == EPI_STORE && ((size_t)outp & 15))) rows(std::true_type{});
+      else rows(std::false_type{});
     }
   }
 }
@@ -1047,7 +991,7 @@ template <class T, int EPI, int OUT, bool GATHER, bool FAST, int TAG>
 __global__ __launch_bounds__(T::NT, T::MINBLK) void gemm_bf16_kernel(GemmArgs g) {
   // + room for a wider rotary table (QKV epilogue) + per-row scales of the epilogue
   // + the row numbers of a gathered operand (ping-pong loop)
-  __shared__ __attribute__((aligned(1024))) char lds[T::LDS_BYTES + lds_extra<T, EPI>() + T::BM * 4 + (GATHER && FAST ? T::BM * MAX_PIECES * 4 : 0)];
+  __shared__ __attribute__((aligned(1024))) char lds[T::LDS_BYTES + T::BM * 4 + (GATHER && FAST ? T::BM * MAX_PIECES * 4 : 0)];
   const int tiles_n = (g.N + T::BN - 1) / T::BN, tiles_m = (g.M + T::BM - 1) / T::BM;
   int tm, tn;
   tile_coords(xcd_remap(blockIdx.x, gridDim.x), tiles_m, tiles_n, g.group_m, tm, tn);
