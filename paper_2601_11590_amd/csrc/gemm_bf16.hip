@@ -238,13 +238,21 @@ template <int N, int OFF> __device__ __forceinline__ void read_frags(bf16x8* f, 
   }
 }
 template <int NA, int NW> __device__ __forceinline__ void read_frags_both(bf16x8* f, uint32_t a0, uint32_t a1, bf16x8* w, uint32_t w0, uint32_t w1) {
-  static_assert(NA == 4 && NW == 4, "blocks");
-  asm volatile(EPD_DSR(8, 18, 20) EPD_DSR(10, 18, 21) EPD_DSR(12, 18, 22) EPD_DSR(14, 18, 23)
-               EPD_DSR(0, 16, 20) EPD_DSR(2, 16, 21) EPD_DSR(4, 16, 22) EPD_DSR(6, 16, 23)
-               EPD_DSR(9, 19, 20) EPD_DSR(11, 19, 21) EPD_DSR(13, 19, 22) EPD_DSR(15, 19, 23)
-               EPD_DSR(1, 17, 20) EPD_DSR(3, 17, 21) EPD_DSR(5, 17, 22) EPD_DSR(7, 17, 23) "s_waitcnt lgkmcnt(0)"
-               : "=&v"(f[0]), "=&v"(f[1]), "=&v"(f[2]), "=&v"(f[3]), "=&v"(f[4]), "=&v"(f[5]), "=&v"(f[6]), "=&v"(f[7]), "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[2]), "=&v"(w[3]), "=&v"(w[4]), "=&v"(w[5]), "=&v"(w[6]), "=&v"(w[7])
-               : "v"(a0), "v"(a1), "v"(w0), "v"(w1), "n"(0), "n"(2048), "n"(4096), "n"(6144) : "memory");
+  static_assert(NA == 4 && (NW == 2 || NW == 4), "blocks");
+  if constexpr (NW == 2) {
+    asm volatile(EPD_DSR(8, 14, 16) EPD_DSR(10, 14, 17) EPD_DSR(0, 12, 16) EPD_DSR(2, 12, 17)
+                 EPD_DSR(4, 12, 18) EPD_DSR(6, 12, 19) EPD_DSR(9, 15, 16) EPD_DSR(11, 15, 17)
+                 EPD_DSR(1, 13, 16) EPD_DSR(3, 13, 17) EPD_DSR(5, 13, 18) EPD_DSR(7, 13, 19) "s_waitcnt lgkmcnt(0)"
+                 : "=&v"(f[0]), "=&v"(f[1]), "=&v"(f[2]), "=&v"(f[3]), "=&v"(f[4]), "=&v"(f[5]), "=&v"(f[6]), "=&v"(f[7]), "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[2]), "=&v"(w[3])
+                 : "v"(a0), "v"(a1), "v"(w0), "v"(w1), "n"(0), "n"(2048), "n"(4096), "n"(6144) : "memory");
+  } else {
+    asm volatile(EPD_DSR(8, 18, 20) EPD_DSR(10, 18, 21) EPD_DSR(12, 18, 22) EPD_DSR(14, 18, 23)
+                 EPD_DSR(0, 16, 20) EPD_DSR(2, 16, 21) EPD_DSR(4, 16, 22) EPD_DSR(6, 16, 23)
+                 EPD_DSR(9, 19, 20) EPD_DSR(11, 19, 21) EPD_DSR(13, 19, 22) EPD_DSR(15, 19, 23)
+                 EPD_DSR(1, 17, 20) EPD_DSR(3, 17, 21) EPD_DSR(5, 17, 22) EPD_DSR(7, 17, 23) "s_waitcnt lgkmcnt(0)"
+                 : "=&v"(f[0]), "=&v"(f[1]), "=&v"(f[2]), "=&v"(f[3]), "=&v"(f[4]), "=&v"(f[5]), "=&v"(f[6]), "=&v"(f[7]), "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[2]), "=&v"(w[3]), "=&v"(w[4]), "=&v"(w[5]), "=&v"(w[6]), "=&v"(w[7])
+                 : "v"(a0), "v"(a1), "v"(w0), "v"(w1), "n"(0), "n"(2048), "n"(4096), "n"(6144) : "memory");
+  }
 }
 #undef EPD_DSR
 
@@ -559,11 +567,13 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int m0, const
   // MFMAs of the last slice, which cover the barrier and the LDS latency.  The freed stage is
   // refilled at once, or (SPREAD tiles) between the MFMAs of the next step.
   auto wait_later = [&](int later) {      // loads of at most min(later, S - 2) stages stay in flight
-    if constexpr (S >= 4) { if (later >= 2) { wait_vmcnt<2 * GL>(); return; } }
-    if constexpr (S >= 3) { if (later == 1 || (S == 3 && later > 1)) { wait_vmcnt<GL>(); return; } }
-    wait_vmcnt<0>();
+    bool done = false;
+    static_for<S - 1>([&](auto I) {
+      constexpr int k = S - 2 - decltype(I)::value;
+      if (!done && later >= k) { wait_vmcnt<k * GL>(); done = true; }
+    });
   };
-  static_assert(S >= 2 && S <= 4, "ring");
+  static_assert(S >= 2 && (S - 2) * GL < 64, "ring, load counter");
   // the sums of squares held since before the first operand load
   auto store_row_scale = [&]() {
     if (scaled_v && tid < BM) {
@@ -655,6 +665,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int m0, const
       else read_frags<PP::NA1, PP::NA0 * 2048>(pa, a0, a0 ^ 64u);
       constexpr int keep = PP::in_flight(rem, p);
       if constexpr (keep >= 0) wait_vmcnt<keep>();
+      if constexpr (rem == 0 && p == 0) prefetch_aux();
       __builtin_amdgcn_sched_barrier(0);
       __builtin_amdgcn_s_barrier();
       __builtin_amdgcn_sched_barrier(0);
@@ -698,9 +709,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int m0, const
     });
     if (wm == 0) __builtin_amdgcn_s_barrier();
   } else {
-  issue_step(0, 0);
-  if constexpr (S >= 3) { if (nk > 1) issue_step(1, 1); }
-  if constexpr (S >= 4) { if (nk > 2) issue_step(2, 2); }
+  static_for<S - 1>([&](auto ST) { if (nk > decltype(ST)::value) issue_step(decltype(ST)::value, decltype(ST)::value); });
   wait_later(nk - 1);
   __builtin_amdgcn_s_barrier();
   store_row_scale();
@@ -752,8 +761,8 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int m0, const
     static_for<S>([&](auto ST) {
       if (kt + decltype(ST)::value < nk) step(ST, std::false_type{}, kt + decltype(ST)::value);
     });
-  }
   if (nk == 1) prefetch_aux();
+  }
 
   // ------------------------------------------------------------------ epilogue
   if constexpr (VMODE) {
@@ -1055,12 +1064,11 @@ static void launch_cfg(const GemmArgs& g, hipStream_t s) {
   hipLaunchKernelGGL((gemm_bf16_kernel<T, EPI, OUT, GATHER, false, 0>), dim3(tiles_m * tiles_n), dim3(T::NT), 0, s, a);
 }
 
-// 256 x 128 serves QKV where 2 * hidden is not a multiple of 256.  With three stages, spread loads and two
-// parts instead of two, at once and four: 25088 x 3 D x D in 305 -> 270 us (D = 1088), 590 -> 494 (1600),
-// 64 -> 62 (320); 128 x 128 tiles forced on the same products take 224, 424 and 44.
+// 256 x 128 serves QKV where 2 * hidden is not a multiple of 256, and narrow outputs (plan_tiles).  Ping-pong loop: 1385
+// clocks a K step of 1024; 25 088 x 3264 x 1088 270 -> 204 us (128 x 128 tiles: 198).
 //            BM   BN  BK  WM WN MINBLK PARTS STAGES
 using T0 = Tile<256, 256, 64, 2, 4, 1, 4, 2, false, 2>;   // 8 waves, 128x64 wave tiles, 128 KB LDS, one block per CU
-using T2 = Tile<256, 128, 64, 2, 2, 1, 2, 3, true>;   // 4 waves, 128x64 wave tiles, 144 KB LDS, one block per CU
+using T2 = Tile<256, 128, 64, 2, 4, 1, 4, 3, false, 2>;   // 8 waves, 128x32 wave tiles, 144 KB LDS, one block per CU
 using T4 = Tile<128, 128, 64, 2, 2, 2, 4, 2>;   // 4 waves, 64x64 wave tiles, 64 KB LDS, two blocks per CU
 using T5 = Tile<320, 256, 64, 2, 4, 1, 5, 2, false, 2>;   // 8 waves, 160x64 wave tiles, 144 KB LDS, one block per CU
 
@@ -1102,10 +1110,19 @@ constexpr TileShape kShape64 = {64, 64, 2, 7, 39.0, {41.0, 41.0, 59.0, 41.0}};
 constexpr TileShape kShape64x128 = {64, 128, 2, 8, 33.3, {22.5, 22.5, 36.7, 22.7}};
 constexpr double kSecondLaunch = 4.0;      // what a second launch of the same GEMM adds (gap + ramp), same unit
 
+constexpr TileShape kShape256x128 = {256, 128, 1, 2, 19.3, {30.0, 30.0, 30.0, 30.0}};
+// Against a long K the large tiles' residual add costs less: the tiles of a launch drift apart, and not all of them
+// are at HBM together (73 896 x 1024 x 4096: 558 us in 256 x 256 tiles, 543 in 320 x 256; 20 676 x 1152 x 4352: 218 in 256 x
+// 256, 240 in 128 x 128; 28 224 x 1152 x 4352: 277 in 320 x 256, 326 in 128 x 128).
+constexpr int kLongK = 2048;
+constexpr double kLongEps256 = 25.0, kLongEps320 = 24.5;
+
 static double tile_cost(int M, int N, int K, int epi, const TileShape& t, long cus) {
   const long tiles = (long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
   const long slots = cus * t.blocks;
-  const double per_round = (double)t.blocks * t.bm * t.bn / 65536.0 * (t.alpha * K / 1024.0 + t.eps[epi & 3]);
+  double eps = t.eps[epi & 3];
+  if (epi == EPI_RESIDUAL && K >= kLongK) eps = t.bm == 320 ? kLongEps320 : t.bm == 256 && t.bn == 256 ? kLongEps256 : eps;
+  const double per_round = (double)t.blocks * t.bm * t.bn / 65536.0 * (t.alpha * K / 1024.0 + eps);
   return (double)((tiles + slots - 1) / slots) * per_round;
 }
 
@@ -1128,6 +1145,12 @@ static TilePlan plan_tiles(int M, int N, int K, int epi, bool may_split, long cu
     const long tiles = (long)((M + t->bm - 1) / t->bm) * ((N + t->bn - 1) / t->bn);
     if (tiles <= 2 * cus * t->blocks) offer(t->cfg, 0, tile_cost(M, N, K, epi, *t, cus));
   }
+  // Narrow outputs against a long K in one round of 256 x 128 tiles: 6272 x 1024 x 4096 56 us against 61 in 128 x 128
+  // tiles and 78 in 256 x 256.  (Against a short one 128 x 128 tiles take as long: K = 1024 25.2 and 25.4 us.  In several
+  // rounds the larger tiles, which move fewer operand bytes, are faster: 20 676 x 1152 x 4352 227 us against
+  // 218, 73 896 x 1024 x 4096 668 against 543.)
+  if (epi == EPI_RESIDUAL && K >= kLongK && (long)((M + 255) / 256) * ((N + 127) / 128) <= cus)
+    offer(kShape256x128.cfg, 0, tile_cost(M, N, K, epi, kShape256x128, cus));
   if (may_split) {
     for (const TileShape* t : {&kShape256, &kShape320}) {
       const long tm = (M + t->bm - 1) / t->bm, tn = (N + t->bn - 1) / t->bn;
@@ -1183,7 +1206,7 @@ void plan_gemm_bf16(const GemmArgs& g, int compute_units, int* tile_rows, int* t
 int gemm_bf16_stat_cols(const GemmArgs& g) {
   int rows, cols, body;
   plan_gemm_bf16(g, 0, &rows, &cols, &body);
-  return cols < 128 ? cols : 128;
+  return cols < 128 || (rows == 256 && cols == 128) ? 64 : 128;      // two waves' columns (Tile::STAT_COLS)
 }
 
 void launch_gemm_bf16(const GemmArgs& g, hipStream_t s) {
