@@ -330,7 +330,7 @@ epd_status epd_probe_mfma_rate(int32_t shape, int32_t zero_operands, int32_t ite
  * output (tokens x output columns) with inner dimension K on a chip of `compute_units` units
  * (<= 0: the current device's, 256 where there is none).  The layer GEMMs of V_m = E(I_m)
  * (section 3.1, Eq. 1) run as one launch of tile_rows x tile_cols tiles, or -- body_rows > 0 --
- * as that launch over the first body_rows tokens plus a second launch of 128 x 128 tiles over the
+ * as that launch over the first body_rows tokens plus a second launch of smaller tiles over the
  * rest, which turns a partial last round of large tiles into a round of small ones.
  *   epilogue  0 = store, 1 = GELU (first MLP GEMM), 2 = residual add (attention output projection,
  *             second MLP GEMM), 3 = the QKV projection (Q | K columns [0, qk_cols), then V)

@@ -140,7 +140,7 @@ bool launch_attn_f32(const AttnArgs& a, hipStream_t s);   // false: head_dim not
 void launch_gemm_bf16(const GemmArgs& g, hipStream_t s);
 // How launch_gemm_bf16 would tile g on a chip of compute_units units (<= 0: the current device's;
 // host only, launches nothing): the tile of the first or only launch, and the rows that launch
-// covers when the rest is left to a second launch of 128 x 128 tiles (0 = one launch covers all).
+// covers when the rest is left to a second launch of smaller tiles (0 = one launch covers all).
 // Reads M, N, epilogue, qk_cols, gather and tile_cfg of g.
 void plan_gemm_bf16(const GemmArgs& g, int compute_units, int* tile_rows, int* tile_cols, int* body_rows);
 bool gemm_bf16_tile_known(int tile);          // tile variants: 0, 2, 4, 5, 7, 8

@@ -162,7 +162,7 @@ struct Tile {
   static constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N, TM = WM / 32, TN = WN / 32;
   static constexpr int TM16 = WM / 16, TN16 = WN / 16;   // 16 x 16 MFMA blocks per wave tile
   static constexpr int PARTS = PARTS_;                   // parts the A blocks of a k step are multiplied in
-  static constexpr int STAT_COLS = 2 * WN;               // columns per sum of squares that the residual epilogue leaves
+  static constexpr int STAT_COLS = BN < 128 ? BN : 128;  // columns per sum of squares that the residual epilogue leaves
   static constexpr int CPR = BK / 8;                     // 16-byte chunks per tile row
   static constexpr int LA = BM * CPR / NT, LW = BN * CPR / NT;   // load instructions per thread and stage
   static constexpr int STAGE_BYTES = (BM + BN) * BK * 2;
@@ -879,7 +879,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int m0, const
             x.x += v0; x.y += v1; x.z += v2; x.w += v3;
             __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x), aux_rows, aux_off[0] + (uint32_t)(c * FR) * aux_pitch, 0, 0);
             // folded RMSNorm (producer side): the raw rows in bf16 for the next GEMM, and their sums of squares per
-            // STAT_COLS columns, which are two waves' shares; lane c % FC of a row's lanes keeps the sum of its row c
+            // STAT_COLS columns, which are two or four waves' shares; lane c % FC of a row's lanes keeps the sum of its row c
             __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, pack_bf16x4(x.x, x.y, x.z, x.w)), out_rows, out_off + (uint32_t)(c * FR) * out_pitch, 0, 0);
             // (made also where nobody takes them: a branch here would cut the loops into pieces that do not overlap)
             const float r = group_sum<FC>(fmaf(x.x, x.x, fmaf(x.y, x.y, fmaf(x.z, x.z, x.w * x.w))));
@@ -897,11 +897,14 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int m0, const
       }
       if (sums) {
         __syncthreads();
-        constexpr int SEGS = T::WAVES_N / 2;
+        constexpr int SEGS = BN / T::STAT_COLS, WPS = T::WAVES_N / SEGS;
+        static_assert(WPS == 2 || WPS == 4, "waves per sum");
         for (int r = tid; r < BM * SEGS; r += NT) {
           const int seg = r / BM, ml = r % BM, m = m0 + ml;
-          if (m < g.M && n0 + seg * T::STAT_COLS < g.N)
-            g.stats_out[(size_t)m * g.stats_n + n0 / T::STAT_COLS + seg] = part[2 * seg * BM + ml] + part[(2 * seg + 1) * BM + ml];
+          const float* const p = part + seg * WPS * BM + ml;
+          float sum = p[0] + p[BM];
+          if constexpr (WPS == 4) sum += p[2 * BM] + p[3 * BM];
+          if (m < g.M && n0 + seg * T::STAT_COLS < g.N) g.stats_out[(size_t)m * g.stats_n + n0 / T::STAT_COLS + seg] = sum;
         }
       }
     } else {
@@ -1127,17 +1130,17 @@ static double tile_cost(int M, int N, int K, int epi, const TileShape& t, long c
 }
 
 // How to cover an M x N output: one launch of `tile`, or (body_rows > 0) the first body_rows rows
-// with `tile` and the rest with 128 x 128 tiles.  The second form cuts the output behind the last
+// with `tile` and the rest with smaller ones (`tail_tile`).  The second form cuts the output behind the last
 // full round of the large tile, so that what would have been a partial round of whole-tile
 // times becomes a round of small tiles: 32768 x 3200 in 256 x 256 tiles is 1664 tiles = 6.5
 // rounds, priced 7; cut after 30208 rows it is 6 rounds plus 500 small tiles.
-struct TilePlan { int tile, body_rows; double cost; };
+struct TilePlan { int tile, body_rows; double cost; int tail_tile; };
 
 static TilePlan plan_tiles(int M, int N, int K, int epi, bool may_split, long cus) {
-  TilePlan best = {0, 0, tile_cost(M, N, K, epi, kShape256, cus)};
+  TilePlan best = {0, 0, tile_cost(M, N, K, epi, kShape256, cus), 0};
   const double keep = 0.98 * best.cost;          // the plain 256 x 256 launch stays unless clearly beaten
-  auto offer = [&](int tile, int body_rows, double cost) {
-    if (cost < keep && cost < best.cost) best = {tile, body_rows, cost};
+  auto offer = [&](int tile, int body_rows, double cost, int tail_tile = 0) {
+    if (cost < keep && cost < best.cost) best = {tile, body_rows, cost, tail_tile};
   };
   offer(kShape128.cfg, 0, tile_cost(M, N, K, epi, kShape128, cus));
   offer(kShape320.cfg, 0, tile_cost(M, N, K, epi, kShape320, cus));
@@ -1145,11 +1148,12 @@ static TilePlan plan_tiles(int M, int N, int K, int epi, bool may_split, long cu
     const long tiles = (long)((M + t->bm - 1) / t->bm) * ((N + t->bn - 1) / t->bn);
     if (tiles <= 2 * cus * t->blocks) offer(t->cfg, 0, tile_cost(M, N, K, epi, *t, cus));
   }
+  auto one_round_256x128 = [&](int rows) { return epi == EPI_RESIDUAL && K >= kLongK && (long)((rows + 255) / 256) * ((N + 127) / 128) <= cus; };
   // Narrow outputs against a long K in one round of 256 x 128 tiles: 6272 x 1024 x 4096 56 us against 61 in 128 x 128
   // tiles and 78 in 256 x 256.  (Against a short one 128 x 128 tiles take as long: K = 1024 25.2 and 25.4 us.  In several
   // rounds the larger tiles, which move fewer operand bytes, are faster: 20 676 x 1152 x 4352 227 us against
   // 218, 73 896 x 1024 x 4096 668 against 543.)
-  if (epi == EPI_RESIDUAL && K >= kLongK && (long)((M + 255) / 256) * ((N + 127) / 128) <= cus)
+  if (one_round_256x128(M))
     offer(kShape256x128.cfg, 0, tile_cost(M, N, K, epi, kShape256x128, cus));
   if (may_split) {
     for (const TileShape* t : {&kShape256, &kShape320}) {
@@ -1159,7 +1163,15 @@ static TilePlan plan_tiles(int M, int N, int K, int epi, bool may_split, long cu
       const long body_tm = std::min(full * cus / tn, (long)(M / t->bm));   // whole row tiles within them
       if (body_tm < 1 || body_tm * t->bm >= M) continue;
       const int body_rows = (int)body_tm * t->bm;
-      offer(t->cfg, body_rows, tile_cost(body_rows, N, K, epi, *t, cus) + tile_cost(M - body_rows, N, K, epi, kShape128, cus) + kSecondLaunch);
+      // the tail in 128 x 128 tiles, or in one round of 256 x 128 against a long K (2112 x 3200 x 12800: 202 us in the former)
+      const int rest = M - body_rows;
+      double tail = tile_cost(rest, N, K, epi, kShape128, cus);
+      int tail_tile = kShape128.cfg;
+      if (one_round_256x128(rest)) {
+        const double c = tile_cost(rest, N, K, epi, kShape256x128, cus);
+        if (c < tail) { tail = c; tail_tile = kShape256x128.cfg; }
+      }
+      offer(t->cfg, body_rows, tile_cost(body_rows, N, K, epi, *t, cus) + tail + kSecondLaunch, tail_tile);
     }
   }
   return best;
@@ -1206,17 +1218,17 @@ void plan_gemm_bf16(const GemmArgs& g, int compute_units, int* tile_rows, int* t
 int gemm_bf16_stat_cols(const GemmArgs& g) {
   int rows, cols, body;
   plan_gemm_bf16(g, 0, &rows, &cols, &body);
-  return cols < 128 || (rows == 256 && cols == 128) ? 64 : 128;      // two waves' columns (Tile::STAT_COLS)
+  return cols < 128 ? cols : 128;
 }
 
 void launch_gemm_bf16(const GemmArgs& g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0) return;
-  const TilePlan plan = may_split_rows(g) ? plan_tiles(g.M, g.N, g.K, g.epilogue, true, g.compute_units > 0 ? g.compute_units : num_cus()) : TilePlan{0, 0, 0.0};
+  const TilePlan plan = may_split_rows(g) ? plan_tiles(g.M, g.N, g.K, g.epilogue, true, g.compute_units > 0 ? g.compute_units : num_cus()) : TilePlan{0, 0, 0.0, 0};
   if (plan.body_rows <= 0) { launch_gemm_bf16_whole(g, s); return; }
   const int mb = plan.body_rows;
   GemmArgs body = g, tail = g;
   body.M = mb; body.tile_cfg = plan.tile + 1;
-  tail.M = g.M - mb; tail.tile_cfg = kShape128.cfg + 1;
+  tail.M = g.M - mb; tail.tile_cfg = plan.tail_tile + 1;
   // everything indexed by the output row moves down by mb rows (vt is indexed through vcol)
   tail.A = (const __bf16*)g.A + (size_t)mb * g.lda;
   if (g.out) tail.out = g.out_f32 ? (void*)((float*)g.out + (size_t)mb * g.ldo) : (void*)((__bf16*)g.out + (size_t)mb * g.ldo);
