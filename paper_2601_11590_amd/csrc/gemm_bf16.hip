@@ -97,6 +97,7 @@ template <int G> __device__ __forceinline__ float group_sum(float x) {
   return x;
 }
 
+constexpr unsigned ROT_TABLE_TILES = 512;   // tiles of a QKV launch up to which its rotary table goes through LDS: two rounds of 256 units
 constexpr int MAX_PIECES = 4;       // pieces per gathered row that the ping-pong loop takes
 
 // Rows of a matrix from `base` on, `bytes` of them in all: accesses beyond are dropped (loads give zero), which spares
@@ -838,7 +839,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int m0, const
     // rotary 22 k -> 16 k (its table: 64-byte pieces of rows, half the address unit's rate), plain store 6.0 k -> 3.9 k.
     constexpr bool F32_ROWS = EPI == EPI_RESIDUAL || OUT == OUT_F32;
     constexpr int SROW = WN * (F32_ROWS ? 4 : 2), CH = SROW / 16, RPI = 64 / CH;   // bytes and 16-byte chunks per staged row, rows per read
-    static_assert(T::WAVES_M * T::WAVES_N * 16 * SROW + T::WAVES_N * BM * 4 <= T::LDS_BYTES, "staging area");
+    constexpr int STG_BYTES = T::WAVES_M * T::WAVES_N * 16 * SROW;
+    [[maybe_unused]] constexpr bool ROT_TABLE = EPI == EPI_QKV && T::PINGPONG;
+    [[maybe_unused]] constexpr int TAB_BYTES = T::LDS_BYTES - STG_BYTES;
+    static_assert(STG_BYTES + T::WAVES_N * BM * 4 <= T::LDS_BYTES, "staging area");
     if constexpr (BIAS_USED && !BIAS_PRE) load_bias();
     __builtin_amdgcn_s_barrier();                        // the operand stages are dead from here on (all reads of them were waited for)
     char* const stg = lds + wave * 16 * SROW;
@@ -921,12 +925,39 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int m0, const
         // a multiply per score in the attention kernel
         qs[w] = n0 + wn * WN + w * 16 + g4 * 4 < g.q_cols ? g.q_scale : 1.0f;
       }
-      // VARIANT: tanh instead of erf (GELU), rotary embedding (QKV), rows that do not start on 16 bytes (STORE; N and ldo
-      // are multiples of 8) -- outside of the loops, so that these are one
+      // Large tiles: the rotary table's rows for the tile's tokens are one slab of memory, which comes to LDS in whole
+      // lines behind the staging pieces (its 16-byte chunks swizzled, so that 16 tokens' entries lie in different
+      // banks); fetched from memory where they are used, entries are 64-byte pieces of 16 rows per access, at half the
+      // address unit's rate and once per wave: 6272 x 3072 x 1024 44.2 -> 40.2 us in
+      // 320 x 256 tiles, the call of eight images 5570 -> 5434 us.  Only in launches of up to two rounds: longer ones gain as
+      // much alone (73 896 x 3072 x 1024 482 -> 458) and lose it again to the chip's clock, attention beside them with it
+      // (32 ragged images 71.5 -> 71.9 ms, five resolutions 41.0 -> 41.3, four clips 423.0 -> 421.8).
+      const uint32_t trb = (uint32_t)g.rot_pairs * 8u, cpr = trb / 16;          // bytes and 16-byte chunks per token
+      const bool table = ROT_TABLE && g.rot && (int)(BM * trb) <= TAB_BYTES && gridDim.x <= ROT_TABLE_TILES;
+      auto swr = [&](int row) { return cpr == 16 || cpr == 32 ? row & 15 : cpr == 8 ? (row >> 1) & 7 : 0; };
+      char* const tab = lds + STG_BYTES;
+      [[maybe_unused]] uint32_t tab_off[TN16];
+      if constexpr (ROT_TABLE) {
+        if (table) {
+          const float inv = 1.0f / (float)cpr;
+          for (int c0 = wave * 64; c0 < BM * (int)cpr; c0 += NT) {
+            const int c = c0 + lane, row = (int)(((float)c + 0.5f) * inv), pos = c - row * (int)cpr;
+            const char* from = (const char*)g.rot + (size_t)min(m0 + row, g.M - 1) * trb + (pos ^ swr(row)) * 16;
+            __builtin_amdgcn_global_load_lds(EPD_GPTR(from), EPD_LPTR(tab + c0 * 16), 16, 0, 0);
+          }
+#pragma unroll
+          for (int w = 0; w < TN16; ++w)
+            tab_off[w] = (uint32_t)(wm * WM + l16) * trb + (uint32_t)((((n0 + wn * WN + w * 16 + g4 * 4) % g.head_dim) >> 2) ^ swr(l16)) * 16u;
+          wait_vmcnt<0>();
+          __builtin_amdgcn_s_barrier();
+        }
+      }
+      // VARIANT 1: tanh instead of erf (GELU), rotary embedding (QKV; 2: from the table in LDS), rows that do not start on
+      // 16 bytes (STORE; N and ldo are multiples of 8) -- outside of the loops, so that these are one
       // block of code in which loads, arithmetic and stores of different tokens overlap
       auto rows = [&](auto VARIANT) {
-        constexpr bool variant = decltype(VARIANT)::value;
-        if constexpr (variant && HAS_AUX && !PREF) {
+        constexpr int variant = decltype(VARIANT)::value;
+        if constexpr (variant == 1 && HAS_AUX && !PREF) {
 #pragma unroll
           for (int b = 0; b < AUX; ++b) load_aux(b);
         }
@@ -939,11 +970,11 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int m0, const
             const f32x4 a = acc[b >> 1][w >> 1][(b & 1) * 2 + (w & 1)];
             float v0 = fmaf(a[0], rs, bias[w][0]), v1 = fmaf(a[1], rs, bias[w][1]), v2 = fmaf(a[2], rs, bias[w][2]), v3 = fmaf(a[3], rs, bias[w][3]);
             if constexpr (EPI == EPI_GELU) {
-              if constexpr (!variant) { v0 = gelu_erf_fast(v0); v1 = gelu_erf_fast(v1); v2 = gelu_erf_fast(v2); v3 = gelu_erf_fast(v3); }
+              if constexpr (variant == 0) { v0 = gelu_erf_fast(v0); v1 = gelu_erf_fast(v1); v2 = gelu_erf_fast(v2); v3 = gelu_erf_fast(v3); }
               else { v0 = gelu_tanh_fast(v0); v1 = gelu_tanh_fast(v1); v2 = gelu_tanh_fast(v2); v3 = gelu_tanh_fast(v3); }
             } else if constexpr (EPI == EPI_QKV) {
-              if constexpr (variant) {
-                const float4 cs = aux[b % AUX][w];
+              if constexpr (variant != 0) {
+                const float4 cs = variant == 2 ? *(const float4*)(tab + tab_off[w] + (uint32_t)(b * 16) * trb) : aux[b % AUX][w];
                 const bool sin_last = b == TM16 - 1 && (BM >= 128 ? ml >= BM - 8 : (m0 & 64) && ml >= 56);
                 rotate_pair(v0, v1, cs.x, cs.y, sin_last);
                 rotate_pair(v2, v3, cs.z, cs.w, sin_last);
@@ -952,13 +983,13 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int m0, const
             }
             *(uint2*)(stg + schunk(l16, w * 2 + (g4 >> 1)) + (g4 & 1) * 8) = pack_bf16x4(v0, v1, v2, v3);
           }
-          if constexpr (variant && HAS_AUX && !PREF) { if (b + AUX < TM16) load_aux(b + AUX); }
+          if constexpr (variant == 1 && HAS_AUX && !PREF) { if (b + AUX < TM16) load_aux(b + AUX); }
           asm volatile("" ::: "memory");                 // other lanes' pieces are read below: LDS takes a wave's accesses in order
 #pragma unroll
           for (int k = 0; k < 16 / RPI; ++k) {
             const int r = k * RPI + lane / CH;
             const uint4 v = *(const uint4*)(stg + schunk(r, lane % CH));
-            if constexpr (EPI == EPI_STORE && variant) {
+            if constexpr (EPI == EPI_STORE && variant == 1) {
               const int m = m0 + wm * WM + b * 16 + r;
               const uint32_t u[4] = {v.x, v.y, v.z, v.w};
               if (m < g.M && ns < g.N)
@@ -971,8 +1002,12 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int m0, const
           if constexpr (BM > 256) __builtin_amdgcn_sched_barrier(0);
         }
       };
-      if ((EPI == EPI_GELU && g.act != 0) || (EPI == EPI_QKV && g.rot) || (EPI == EPI_STORE && ((size_t)outp & 15))) rows(std::true_type{});
-      else rows(std::false_type{});
+      if ((EPI == EPI_GELU && g.act != 0) || (EPI == EPI_QKV && g.rot) || (EPI == EPI_STORE && ((size_t)outp & 15))) {
+        if constexpr (ROT_TABLE) { if (table) { rows(std::integral_constant<int, 2>{}); return; } }
+        rows(std::integral_constant<int, 1>{});
+      } else {
+        rows(std::integral_constant<int, 0>{});
+      }
     }
   }
 }

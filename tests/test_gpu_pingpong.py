@@ -10,7 +10,7 @@ import torch
 from oracle import vit_encode as O
 from paper_2601_11590_amd import binding as B, workloads as W
 from parity_util import check
-from test_gpu_parity import case, small
+from test_gpu_parity import case, parity, small
 
 pytestmark = pytest.mark.gpu
 
@@ -33,3 +33,12 @@ def test_large_tiles_give_the_bits_of_the_128_tile(hidden, heads, merge):
     check(cfg, out[0].float().cpu().numpy(), ref, "256 x 256")
     assert all(torch.equal(out[t], out[4]) for t in (0, 5, 2))
     enc.close()
+
+
+@pytest.mark.parametrize("d,pairs", [(32, (0, 8, 8)), (64, (0, 16, 16)), (72, (0, 18, 18)), (80, (8, 16, 16)), (96, (16, 16, 16)), (128, (16, 24, 24))])
+@pytest.mark.parametrize("tile", [0, 5, 2])
+def test_rotary_table_of_every_head_dim(d, pairs, tile):
+    """Tables of 8 to 32 chunks a token in LDS, swizzled and not, and those that do not fit (head_dim 128 on 256 and 320 rows);
+    a last tile with fewer tokens than the table has rows, tokens that start on a multiple of four."""
+    cfg = small("bf16", hidden=4 * d, num_heads=4, head_dim=d, rope="3d", rope_pairs=pairs, mlp_dim=256, num_layers=1)
+    parity(cfg, [(1, 2, 2), (1, 20, 14), (2, 6, 10), (1, 12, 8)], gemm_tile=tile)
