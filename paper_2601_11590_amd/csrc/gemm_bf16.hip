@@ -13,7 +13,8 @@
 // the 64 lanes' 16-byte chunks to consecutive LDS addresses, so rows cannot be padded;
 // instead the chunk a lane fetches is chosen so that chunk c of row r lands in slot
 // c ^ swz(r) of that row, which spreads the 16 rows read by one MFMA operand fetch over all
-// bank groups.  The next stages are in flight while stage s is multiplied; one barrier per K step.
+// bank groups.  The next stages are in flight while stage s is multiplied.  The main loop is the ping-pong loop
+// (eight-wave tiles, see PingPong) or a plain ring with one barrier per K step.
 //
 // Accumulator orientation.  For a 16x16 MFMA result lane l holds column (l % 16) and rows
 // 4*(l/16) + v, v = 0..3.  By default the W fragment is fed as the first operand, so "rows"
