@@ -496,8 +496,9 @@ epd_status epd_encode(epd_handle h, const void* packed_patches, const int32_t* c
   auto gemm = [&](int step, GemmArgs& g, int k_counted = 0) {   // k_counted: K without padding
     StepTimer tm(h, step, 2.0 * g.M * (double)g.N * (k_counted ? k_counted : g.K), st);
     g.zeros = h->ws + L.zeros;
-    // operands that live in the workspace may be read past their last row (see make_layout)
-    g.overread_ok = (g.A != packed_patches && !g.gather) ? 1 : 0;
+    // operands that live in the workspace -- all but the caller's patches -- may be read past their last row (see make_layout)
+    g.overread_a = g.A != packed_patches;
+    g.overread_w = 1;
     g.tile_cfg = h->tile_cfg;
     g.compute_units = h->compute_units;
     if (bf) launch_gemm_bf16(g, st); else launch_gemm_f32(g, st);

@@ -46,9 +46,10 @@ struct GemmArgs {
   int vt_stride;
   const int32_t* vcol;  // [M] column of token m in vt
   const void* zeros;    // bf16 path: >= 16 readable zero bytes (source of out-of-range tile chunks)
-  int overread_ok;      // bf16 path: 1 = rows [M, round_up(M, 320)) of A and [N, round_up(N, 256)) of
-                        //   W are readable memory (contents irrelevant): enables the load path
-                        //   without per-lane row clamping
+  int overread_a;       // bf16 path: 1 = rows [M, round_up(M, 320)) of A are readable memory (contents
+                        //   irrelevant; gathered rows are never past M)
+  int overread_w;       // bf16 path: 1 = rows [N, round_up(N, 256)) of W are.  Loads of whole tiles, without
+                        //   per-lane row clamping, need both; with gathered rows of A this one only
   // bf16 path, RMSNorm folded into the GEMMs around it (see launch_fold_gamma):
   //   producer (EPI_RESIDUAL): also store the updated residual rows as bf16 to xb and the sum
   //   of their squares per segment of c columns to stats_out[m][n / c], c = gemm_bf16_stat_cols(g)

@@ -279,9 +279,9 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int m0, const
   // it*NT + wave*64 + lane; chunk c is row c / CPR, slot c % CPR, and holds k-chunk
   // slot ^ swz(row) of that row.  One instruction covers RPP = NT / CPR rows (a multiple of
   // 16, so the swizzle of a lane's row is the same for every `it`).
-  //   FAST (the caller guarantees that whole tiles of A and W may be read, also where they
-  //   run past M or N, and K is a multiple of BK): the address is a wave-uniform row base,
-  //   advanced with scalar arithmetic, plus ONE per-lane offset for all loads of an operand.
+  //   FAST (the caller guarantees that whole tiles of W, and of A unless its rows are gathered, may
+  //   be read, also where they run past N or M, and K is a multiple of BK): the address is a wave-
+  //   uniform row base, advanced with scalar arithmetic, plus ONE per-lane offset for all loads of an operand.
   //   Otherwise rows beyond M (or N) are clamped to the last valid row -- they only feed
   //   accumulators that are never stored -- and every load keeps its own per-lane offset.
   constexpr int RPP = NT / CPR;
@@ -1086,7 +1086,7 @@ static void launch_cfg(const GemmArgs& g, hipStream_t s) {
   }
   a.group_m = std::min(a.group_m, tiles_m);
   if constexpr (!GATHER) {
-    if (g.overread_ok && g.K % T::BK == 0) {
+    if (g.overread_a && g.overread_w && g.K % T::BK == 0) {
       if (EPI == EPI_RESIDUAL && g.name_tag == 1)
         hipLaunchKernelGGL((gemm_bf16_kernel<T, EPI, OUT, false, true, (EPI == EPI_RESIDUAL ? 1 : 0)>), dim3(tiles_m * tiles_n), dim3(T::NT), 0, s, a);
       else
@@ -1095,7 +1095,7 @@ static void launch_cfg(const GemmArgs& g, hipStream_t s) {
     }
   }
   if constexpr (GATHER && T::PINGPONG) {
-    if (g.gather_n <= MAX_PIECES && g.K % (g.gather_n * T::BK) == 0) {
+    if (g.overread_w && g.gather_n <= MAX_PIECES && g.K % (g.gather_n * T::BK) == 0) {
       hipLaunchKernelGGL((gemm_bf16_kernel<T, EPI, OUT, true, true, 0>), dim3(tiles_m * tiles_n), dim3(T::NT), 0, s, a);
       return;
     }

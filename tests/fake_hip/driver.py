@@ -1,8 +1,9 @@
 """The built library on the stand-in runtime of fake_hip.cpp, in a process of its own that never loads
-torch:  python driver.py <stand-in .so> <libepd_encode.so> <function of this file>."""
+torch:  python driver.py <stand-in .so> <libepd_encode.so> <function of this file> [<gemm_shim .so>]."""
 
 import ctypes as C
 import os
+import re
 import sys
 import types
 
@@ -244,6 +245,41 @@ def launches_stay_within_the_thread_limit(fake, lib):
     fake.fake_forget()
     B.epd_preprocess(h, POOL, [(50, 60), (64, 64)], [(1, 3, 5), (1, 2, 2)], [0.5], [0.25], POOL, None)
     assert [l[1:] for l in launches(fake)] == [((19, 1, 1), (512, 1, 1))]
+
+
+# ------------------------------------------------------------------ launches of the bf16 GEMMs
+
+def gemm_shim():
+    C.CDLL(sys.argv[2], mode=C.RTLD_GLOBAL)                              # its names are for the shim
+    shim = C.CDLL(sys.argv[4])
+    shim.shim_gemm.argtypes = [C.c_int] * 8
+    return shim
+
+
+def gemm_launches(fake):
+    """(tile rows, tile columns, gathered, whole tiles without clamping, blocks) of every bf16 GEMM launch."""
+    out = []
+    for name, grid, _ in launches(fake):
+        m = re.search(r"gemm_bf16_kernelINS_4TileILi(\d+)ELi(\d+)E.*?EELi\d+ELi\d+ELb([01])ELb([01])E", name)
+        if m:
+            out.append((int(m[1]), int(m[2]), m[3] == "1", m[4] == "1", grid[0]))
+    return out
+
+
+def gathered_gemm_reads_past_its_weights_only_where_allowed(fake, lib):
+    """Loads that take whole tiles read W past its last row, and A past its last row where its rows are not gathered."""
+    shim = gemm_shim()
+    for tile in (0, 2, 4, 5, 7, 8):
+        for gather_n in (0, 4):
+            for may_read in range(4):
+                fake.fake_forget()
+                shim.shim_gemm(300, 200, 512, 0, gather_n, may_read, tile, 256)
+                (l,) = gemm_launches(fake)
+                assert l[2] == (gather_n > 0)
+                needs = 2 if gather_n else 3
+                assert not l[3] or may_read & needs == needs, (tile, gather_n, may_read, l)
+                # ... and where they are allowed they are taken (gathered rows: the large tiles)
+                assert l[3] or may_read & needs != needs or (gather_n and tile in (4, 7, 8)), (tile, gather_n, may_read, l)
 
 
 if __name__ == "__main__":
