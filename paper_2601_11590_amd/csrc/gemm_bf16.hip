@@ -526,9 +526,16 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int m0, const
   // of the residual rows (EPI_RESIDUAL, lanes along rows), or cos and sin of the lane's rotary pairs (EPI_QKV).
   // Where all of it is at most 16 loads they are issued behind the last stage hand-over, so that they
   // overlap the last K step; otherwise AUX blocks are kept in flight through the epilogue.
+  //   A rotary table that comes through LDS (`table`) needs none of these loads: issued all the same, and waited for
+  // ahead of the table, they took the 256 x 128 tile's QKV launch of 12 544 x 960 x 320 from 25.8 to 30.0 us (28.0 without a
+  // table).  On its plain loop (K in parts of steps) the entries are not fetched ahead at all: 6272 x 3240 x 1080 80.7 us, 83
+  // with the prefetch.
   constexpr int FC = WN / 4, FR = 64 / FC;              // lanes per row of fp32 values, rows per access of a wave
   constexpr bool HAS_AUX = !VMODE && (EPI == EPI_RESIDUAL || EPI == EPI_QKV);
-  constexpr bool PREF = HAS_AUX && TM16 * TN16 <= 16;
+  constexpr bool PREF = HAS_AUX && TM16 * TN16 <= 16 && !(EPI == EPI_QKV && T::PINGPONG && !FAST);
+  [[maybe_unused]] constexpr bool ROT_TABLE = HAS_AUX && EPI == EPI_QKV && T::PINGPONG;
+  [[maybe_unused]] constexpr int TAB_BYTES = T::LDS_BYTES - T::WAVES_M * T::WAVES_N * 16 * WN * 2;   // what the bf16 staging pieces leave
+  const bool table = ROT_TABLE && g.rot && gridDim.x <= ROT_TABLE_TILES && BM * g.rot_pairs * 8 <= TAB_BYTES;
   constexpr int AUX = PREF ? TM16 : BM > 256 ? (EPI == EPI_QKV ? 2 : 3) : 4;
   [[maybe_unused]] float4 aux[HAS_AUX ? AUX : 1][TN16];
   const int rows_left = max(0, min(WM, g.M - m0 - wm * WM));       // rows of the wave's tile that exist
@@ -556,7 +563,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int m0, const
   };
   auto prefetch_aux = [&]() {
     if constexpr (PREF) {
-      if (EPI == EPI_QKV && !g.rot) return;
+      if (EPI == EPI_QKV && (!g.rot || table)) return;
 #pragma unroll
       for (int b = 0; b < TM16; ++b) load_aux(b);
     }
@@ -841,8 +848,6 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int m0, const
     constexpr bool F32_ROWS = EPI == EPI_RESIDUAL || OUT == OUT_F32;
     constexpr int SROW = WN * (F32_ROWS ? 4 : 2), CH = SROW / 16, RPI = 64 / CH;   // bytes and 16-byte chunks per staged row, rows per read
     constexpr int STG_BYTES = T::WAVES_M * T::WAVES_N * 16 * SROW;
-    [[maybe_unused]] constexpr bool ROT_TABLE = EPI == EPI_QKV && T::PINGPONG;
-    [[maybe_unused]] constexpr int TAB_BYTES = T::LDS_BYTES - STG_BYTES;
     static_assert(STG_BYTES + T::WAVES_N * BM * 4 <= T::LDS_BYTES, "staging area");
     if constexpr (BIAS_USED && !BIAS_PRE) load_bias();
     __builtin_amdgcn_s_barrier();                        // the operand stages are dead from here on (all reads of them were waited for)
@@ -934,7 +939,6 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int m0, const
       // much alone (73 896 x 3072 x 1024 482 -> 458) and lose it again to the chip's clock, attention beside them with it
       // (32 ragged images 71.5 -> 71.9 ms, five resolutions 41.0 -> 41.3, four clips 423.0 -> 421.8).
       const uint32_t trb = (uint32_t)g.rot_pairs * 8u, cpr = trb / 16;          // bytes and 16-byte chunks per token
-      const bool table = ROT_TABLE && g.rot && (int)(BM * trb) <= TAB_BYTES && gridDim.x <= ROT_TABLE_TILES;
       auto swr = [&](int row) { return cpr == 16 || cpr == 32 ? row & 15 : cpr == 8 ? (row >> 1) & 7 : 0; };
       char* const tab = lds + STG_BYTES;
       [[maybe_unused]] uint32_t tab_off[TN16];

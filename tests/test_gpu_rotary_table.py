@@ -1,0 +1,67 @@
+"""GPU tests of the two ways in which the QKV epilogue of the large tiles gets its rotary entries: from a table in LDS
+(launches of up to two rounds of tiles) or from memory."""
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import vit_encode as O
+from paper_2601_11590_amd import binding as B, workloads as W
+from parity_util import check
+from test_gpu_parity import case, small
+
+pytestmark = pytest.mark.gpu
+
+@pytest.mark.parametrize("tile", [0, 5, 2])
+def test_more_than_two_rounds_of_the_whole_chip(tile):
+    """A first item's rows are the same bits alone (table) and ahead of so many others that the launch has more than two
+    rounds of tiles."""
+    cfg = small("bf16", hidden=256, num_heads=4, mlp_dim=256, num_layers=1)
+    one, rows, cols = (1, 20, 32), 320 if tile == 5 else 256, 128 if tile == 2 else 256
+    tiles_n = 3 * 256 // cols
+    n = (512 // tiles_n + 1) * rows // 640 + 1
+    gw, layers, _, _, _ = case(cfg, [one])
+    grids = [one] * n
+    T = W.num_tokens(grids)
+    assert -(-T // rows) * tiles_n > 2 * 256
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(3)
+    p = torch.rand((T, cfg.patch_dim), generator=gen, device="cuda:0").to(torch.bfloat16)
+    enc = B.EpdEncoder(cfg, gw, layers, max_tokens=T, max_segments=n, max_items=n)
+    enc.set_tuning(tile, 0)
+    many = enc.encode(p, *W.metadata(grids)).clone()
+    alone = enc.encode(p[:640].contiguous(), *W.metadata([one])).clone()
+    torch.cuda.synchronize()
+    assert torch.equal(many[:160], alone)
+    ref = O.encode(cfg, gw, layers, p[:640].float().cpu().numpy().astype(np.float64), *W.metadata([one]))
+    check(cfg, alone.float().cpu().numpy(), ref, "alone")
+    enc.close()
+
+
+def test_table_spares_the_loads_from_memory():
+    """QKV of 16 images at hidden 320 in 256 x 128 tiles, two rounds: 24.8 us with rotary embedding from the table in LDS,
+    22.2 without any.  A version that fetched the entries from memory as well, and then left them, took 29.2 us.  The bound
+    on the ratio (1.12, then 1.31) stands between the two."""
+    times = {"2d": [], "none": []}
+    encs = {}
+    grids = [(1, 28, 28)] * 16
+    T = W.num_tokens(grids)
+    cu, grid = W.metadata(grids)
+    for rope, pairs in (("2d", (0, 16, 16)), ("none", (0, 0, 0))):
+        cfg = W.C2.replace(num_layers=3, hidden=320, num_heads=5, mlp_dim=320, out_dim=64, rope=rope, rope_pairs=pairs)
+        encs[rope] = B.EpdEncoder(cfg, *W.all_weights(cfg), max_tokens=T, max_segments=16, max_items=16)
+        encs[rope].set_tuning(2, 0)
+    rows = torch.rand((T, cfg.patch_dim), device="cuda:0").to(torch.bfloat16)
+    for _ in range(15):
+        for rope, enc in encs.items():
+            enc.set_timing(B.EPD_STEP_QKV)
+            for _ in range(4):
+                enc.encode(rows, cu, grid)
+            torch.cuda.synchronize()
+            ms, launches = enc.get_timing()[:2]
+            times[rope].append(ms / launches * 1e3)
+    for enc in encs.values():
+        enc.close()
+    table, without = (sorted(times[r])[7] for r in ("2d", "none"))
+    print("table %.1f us, no rotary embedding %.1f us" % (table, without), flush=True)
+    assert table <= 1.21 * without, (table, without)
