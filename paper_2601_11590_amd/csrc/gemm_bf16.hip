@@ -98,7 +98,7 @@ template <int G> __device__ __forceinline__ float group_sum(float x) {
   return x;
 }
 
-constexpr unsigned ROT_TABLE_TILES = 512;   // tiles of a QKV launch up to which its rotary table goes through LDS: two rounds of 256 units
+constexpr int ROT_TABLE_ROUNDS = 2;  // rounds of blocks of a QKV launch up to which its rotary table goes through LDS (see the epilogue)
 constexpr int MAX_PIECES = 4;       // pieces per gathered row that the ping-pong loop takes
 
 // Rows of a matrix from `base` on, `bytes` of them in all: accesses beyond are dropped (loads give zero), which spares
@@ -535,7 +535,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int m0, const
   constexpr bool PREF = HAS_AUX && TM16 * TN16 <= 16 && !(EPI == EPI_QKV && T::PINGPONG && !FAST);
   [[maybe_unused]] constexpr bool ROT_TABLE = HAS_AUX && EPI == EPI_QKV && T::PINGPONG;
   [[maybe_unused]] constexpr int TAB_BYTES = T::LDS_BYTES - T::WAVES_M * T::WAVES_N * 16 * WN * 2;   // what the bf16 staging pieces leave
-  const bool table = ROT_TABLE && g.rot && gridDim.x <= ROT_TABLE_TILES && BM * g.rot_pairs * 8 <= TAB_BYTES;
+  const bool table = ROT_TABLE && g.rot && g.rot_lds && BM * g.rot_pairs * 8 <= TAB_BYTES;
   constexpr int AUX = PREF ? TM16 : BM > 256 ? (EPI == EPI_QKV ? 2 : 3) : 4;
   [[maybe_unused]] float4 aux[HAS_AUX ? AUX : 1][TN16];
   const int rows_left = max(0, min(WM, g.M - m0 - wm * WM));       // rows of the wave's tile that exist
@@ -934,10 +934,13 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int m0, const
       // Large tiles: the rotary table's rows for the tile's tokens are one slab of memory, which comes to LDS in whole
       // lines behind the staging pieces (its 16-byte chunks swizzled, so that 16 tokens' entries lie in different
       // banks); fetched from memory where they are used, entries are 64-byte pieces of 16 rows per access, at half the
-      // address unit's rate and once per wave: 6272 x 3072 x 1024 44.2 -> 40.2 us in
-      // 320 x 256 tiles, the call of eight images 5570 -> 5434 us.  Only in launches of up to two rounds: longer ones gain as
-      // much alone (73 896 x 3072 x 1024 482 -> 458) and lose it again to the chip's clock, attention beside them with it
-      // (32 ragged images 71.5 -> 71.9 ms, five resolutions 41.0 -> 41.3, four clips 423.0 -> 421.8).
+      // address unit's rate and once per wave: 6272 x 3072 x 1024 44.2 -> 40.2 us in 320 x 256 tiles, the call of eight
+      // images 5570 -> 5434 us.  Only in launches of up to two rounds of the units the call runs on.  Longer ones in 256 x 128
+      // tiles lose alone (12 544 x 3264 x 1088 109.8 -> 113.4 us, 18 816 x 3600 x 1200 230 -> 240).  In 256 x 256 and 320 x 256
+      // tiles they gain alone (37 632 x 3072 x 1024 246 -> 232, 25 088 x 3840 x 1280 237 -> 234) and whole calls go
+      // either way, the clock of the attention beside them with it: 20 ... 48 images at hidden 1024 0.9 % less, 32 ragged images
+      // the same, 10 ... 14 k tokens at hidden 1152 the same, 20 k 0.7 % and five resolutions 1.5 % more.  So the line does not
+      // stand where a call of every width would have it; it keeps what was measured to lose out.
       const uint32_t trb = (uint32_t)g.rot_pairs * 8u, cpr = trb / 16;          // bytes and 16-byte chunks per token
       auto swr = [&](int row) { return cpr == 16 || cpr == 32 ? row & 15 : cpr == 8 ? (row >> 1) & 7 : 0; };
       char* const tab = lds + STG_BYTES;
@@ -1070,7 +1073,9 @@ static int num_cus() {
 template <class T, int EPI, int OUT, bool GATHER>
 static void launch_cfg(const GemmArgs& g, hipStream_t s) {
   const int tiles_m = (g.M + T::BM - 1) / T::BM, tiles_n = (g.N + T::BN - 1) / T::BN;
+  const long blocks = (long)T::MINBLK * (g.compute_units > 0 ? g.compute_units : num_cus());     // of one round
   GemmArgs a = g;
+  a.rot_lds = EPI == EPI_QKV && (long)tiles_m * tiles_n <= ROT_TABLE_ROUNDS * blocks;
   if (a.group_m <= 0) {
     // keep the A panels of one group (group_m x BM rows x K) within about 2 MB of the 4 MB L2
     const long panel = (long)T::BM * g.K * 2;
@@ -1085,7 +1090,6 @@ static void launch_cfg(const GemmArgs& g, hipStream_t s) {
     // XCD streams all of W.  When the whole grid runs in at most two rounds, number the tiles
     // column by column instead, so that an XCD owns a block of columns: W is then fetched
     // once in total and the (smaller) A once per XCD.
-    const long blocks = (long)T::MINBLK * (g.compute_units > 0 ? g.compute_units : num_cus());
     if ((long)g.N > 2L * g.M && (long)tiles_m * tiles_n <= 2 * blocks) a.group_m = tiles_m;
   }
   a.group_m = std::min(a.group_m, tiles_m);

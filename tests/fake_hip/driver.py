@@ -25,6 +25,8 @@ def load(fake_path, lib_path):
     fake.fake_get.restype = C.c_longlong
     fake.fake_calls.restype = C.c_longlong
     fake.fake_calls.argtypes = [C.c_char_p]
+    fake.fake_args.restype = C.c_void_p
+    fake.fake_keep_args.argtypes = [C.c_char_p, C.c_size_t]
     fake.fake_launch.restype = C.c_char_p
     fake.fake_launch.argtypes = [C.c_int, C.POINTER(C.c_uint32)]
     # the package's own binding, with a torch that holds names only: the real one would load the real runtime
@@ -253,6 +255,7 @@ def gemm_shim():
     C.CDLL(sys.argv[2], mode=C.RTLD_GLOBAL)                              # its names are for the shim
     shim = C.CDLL(sys.argv[4])
     shim.shim_gemm.argtypes = [C.c_int] * 8
+    shim.shim_rot_lds.argtypes = [C.c_void_p]
     return shim
 
 
@@ -280,6 +283,24 @@ def gathered_gemm_reads_past_its_weights_only_where_allowed(fake, lib):
                 assert not l[3] or may_read & needs == needs, (tile, gather_n, may_read, l)
                 # ... and where they are allowed they are taken (gathered rows: the large tiles)
                 assert l[3] or may_read & needs != needs or (gather_n and tile in (4, 7, 8)), (tile, gather_n, may_read, l)
+
+
+def rotary_table_rule_counts_the_units_of_the_stream(fake, lib):
+    """The rotary table goes through LDS in launches of up to two rounds -- of the units the call runs on, not of a whole chip."""
+    shim = gemm_shim()
+    fake.fake_keep_args(b"gemm_bf16_kernel", shim.shim_args_size())
+    seen = set()
+    for tile, cols in ((0, 256), (5, 256), (2, 128)):
+        for units in (0, 64, 128, 208, 256):
+            for M in (2000, 7000, 12000, 16640, 30000, 60000):
+                fake.fake_forget()
+                shim.shim_gemm(M, 3072, 1024, 3, 0, 3, tile, units)
+                (l,) = gemm_launches(fake)
+                assert l[1] == cols
+                two_rounds = l[4] <= 2 * (units or 256)
+                assert shim.shim_rot_lds(fake.fake_args(0)) == two_rounds, (tile, units, M, l)
+                seen.add((units, two_rounds))
+    assert len(seen) == 10                                              # both answers for every number of units
 
 
 if __name__ == "__main__":

@@ -16,7 +16,7 @@ struct Dim3 { uint32_t x, y, z; };
 struct HashRange { const uint8_t* data; int64_t bytes; uint64_t salt; uint32_t words, groups, first_block; };
 struct HashArgs { int n; uint64_t* partial; uint64_t* result; uint32_t blocks; HashRange r[32]; };
 
-struct Launch { std::string name; Dim3 grid, block; };
+struct Launch { std::string name; Dim3 grid, block; std::string args; };
 std::map<const void*, std::string> g_names;
 std::vector<Launch> g_launches;
 std::vector<std::pair<uint64_t*, uint64_t>> g_late;      // stores of a kernel that still runs
@@ -26,6 +26,8 @@ enum { kLastError, kCapture, kLate, kLaunchStatus, kSyncStatus, kHostFlags };
 
 std::string g_refuse;                                    // see fake_refuse
 int g_refuse_status = 0;
+std::string g_keep;                                      // see fake_keep_args
+size_t g_keep_bytes = 0;
 
 constexpr uint64_t kP = (1ull << 61) - 1;
 uint64_t mul(uint64_t a, uint64_t b) { return (uint64_t)((unsigned __int128)a * b % kP); }
@@ -59,6 +61,9 @@ extern "C" {
 void fake_set(int what, long long value) { g_set[what] = value; }
 // launches of kernels whose name holds `part` fail with `status`
 void fake_refuse(const char* part, int status) { g_refuse = part; g_refuse_status = status; }
+// launches of kernels whose name holds `part` keep the first `bytes` of their argument for fake_args
+void fake_keep_args(const char* part, size_t bytes) { g_keep = part; g_keep_bytes = bytes; }
+const void* fake_args(int i) { return g_launches[i].args.data(); }
 long long fake_get(int what) { return g_set[what]; }
 void fake_drain() { drain(); }
 long long fake_calls(const char* name) { return g_calls[name]; }
@@ -86,7 +91,8 @@ int hipLaunchKernel(const void* f, Dim3 grid, Dim3 block, void** args, size_t, v
   CALL();
   if (g_set[kLaunchStatus]) { g_set[kLastError] = g_set[kLaunchStatus]; return (int)g_set[kLaunchStatus]; }
   if (!g_refuse.empty() && g_names[f].find(g_refuse) != std::string::npos) { g_set[kLastError] = g_refuse_status; return g_refuse_status; }
-  g_launches.push_back({g_names[f], grid, block});
+  g_launches.push_back({g_names[f], grid, block, {}});
+  if (g_keep_bytes && g_names[f].find(g_keep) != std::string::npos) g_launches.back().args.assign((const char*)args[0], g_keep_bytes);
   if (g_names[f].find("hash_partial_kernel") != std::string::npos) {
     HashArgs a;
     std::memcpy(&a, args[0], sizeof a);

@@ -15,7 +15,11 @@ void shim_gemm(int M, int N, int K, int epilogue, int gather_n, int may_read, in
   if (gather_n) { g.gather = (const int32_t*)0x50000; g.gather_n = gather_n; }
   g.overread_a = may_read & 1; g.overread_w = (may_read >> 1) & 1;
   g.tile_cfg = tile + 1; g.compute_units = compute_units;
+  g.qk_cols = N / 3 * 2; g.head_dim = 64; g.rot = (const float2*)0x60000; g.rot_pairs = 32;
   epd::launch_gemm_bf16(g, nullptr);
 }
+
+size_t shim_args_size() { return sizeof(epd::GemmArgs); }
+int shim_rot_lds(const void* args) { return ((const epd::GemmArgs*)args)->rot_lds; }
 
 }  // extern "C"

@@ -1,5 +1,6 @@
 """GPU tests of the two ways in which the QKV epilogue of the large tiles gets its rotary entries: from a table in LDS
-(launches of up to two rounds of tiles) or from memory."""
+(launches of up to two rounds of the units the call runs on) or from memory.  Telling the handle of one unit makes
+every launch of more than two tiles take them from memory."""
 
 import numpy as np
 import pytest
@@ -11,6 +12,29 @@ from parity_util import check
 from test_gpu_parity import case, small
 
 pytestmark = pytest.mark.gpu
+
+@pytest.mark.parametrize("heads,d,pairs", [(4, 32, (0, 8, 8)), (4, 64, (0, 16, 16)), (16, 72, (0, 18, 18)), (8, 80, (8, 16, 16)), (4, 96, (16, 16, 16)),
+                                           (4, 128, (16, 24, 24)), (3, 72, (0, 18, 18))])
+@pytest.mark.parametrize("tile", [0, 5, 2])
+def test_entries_from_memory(heads, d, pairs, tile):
+    """Against the oracle, and the same bits as from the table; last tiles with fewer rows than the tile has.  (3 heads of 72:
+    K = 216 is no whole number of K steps, and Q | K columns are 256 x 128 tiles whatever is forced.)"""
+    cfg = small("bf16", hidden=heads * d, num_heads=heads, head_dim=d, rope="3d", rope_pairs=pairs, mlp_dim=256, num_layers=1)
+    grids = [(1, 2, 2), (1, 20, 14), (2, 6, 10), (1, 12, 8)]
+    gw, layers, patches, cu, grid = case(cfg, grids)
+    ref = O.encode(cfg, gw, layers, patches, cu, grid)
+    enc = B.EpdEncoder(cfg, gw, layers, max_tokens=patches.shape[0], max_segments=len(cu) - 1, max_items=len(grids))
+    p = B.to_device_patches(patches, cfg.dtype)
+    enc.set_tuning(tile, 0)
+    out = []
+    for units in (0, 1):
+        enc.set_compute_units(units)
+        out.append(enc.encode(p, cu, grid).clone())
+    torch.cuda.synchronize()
+    check(cfg, out[1].float().cpu().numpy(), ref, "from memory")
+    assert torch.equal(out[0], out[1])
+    enc.close()
+
 
 @pytest.mark.parametrize("tile", [0, 5, 2])
 def test_more_than_two_rounds_of_the_whole_chip(tile):
