@@ -179,8 +179,8 @@ struct Tile {
 
 // Ping-pong main loop (eight waves, WAVES_M = 2, two waves per SIMD).  The two wave rows run half a phase
 // apart: while one multiplies, the other fetches its next fragments, so the matrix cores never wait for
-// an LDS read, a barrier or the issue of a load.  The rows of a wave tile come in one or two parts and a K
-// step is a phase per part:
+// an LDS read, a barrier or the issue of a load.  The rows of a wave tile come in two parts and a K step
+// is a phase per part:
 //     fragment reads, waited for | barrier | matrix instructions, loads between them | barrier
 // and wave row 1 passes one barrier more ahead of the loop (wave row 0 one behind it).  Operands come in
 // units: part h of the rows of both wave rows, and all of W.  Unit u of a step is read in phase p(u), and
@@ -593,7 +593,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, const int m0, const
   };
   if constexpr (T::PINGPONG && FAST) {
     using PP = PingPong<T>;
-    static_assert(T::WAVES_M == 2 && T::WAVES_N == 4 && PP::NP <= 2, "ping-pong tile");
+    static_assert(T::WAVES_M == 2 && T::WAVES_N == 4 && PP::NP == 2, "ping-pong tile");
     constexpr int NP = PP::NP, NW = PP::NW;
     // a load covers 8 rows that start at a multiple of 8, odd for odd waves: its lanes' offsets are the same for all
     // loads of a wave
@@ -1044,8 +1044,7 @@ __device__ __forceinline__ void tile_coords(int t, int tiles_m, int tiles_n, int
 // projection, second MLP GEMM) kernel names of their own, so that a profile lists them apart.
 template <class T, int EPI, int OUT, bool GATHER, bool FAST, int TAG>
 __global__ __launch_bounds__(T::NT, T::MINBLK) void gemm_bf16_kernel(GemmArgs g) {
-  // + room for a wider rotary table (QKV epilogue) + per-row scales of the epilogue
-  // + the row numbers of a gathered operand (ping-pong loop)
+  // + per-row scales of the epilogue + the row numbers of a gathered operand (ping-pong loop)
   __shared__ __attribute__((aligned(1024))) char lds[T::LDS_BYTES + T::BM * 4 + (GATHER && FAST ? T::BM * MAX_PIECES * 4 : 0)];
   const int tiles_n = (g.N + T::BN - 1) / T::BN, tiles_m = (g.M + T::BM - 1) / T::BM;
   int tm, tn;
@@ -1127,18 +1126,20 @@ using T8 = Tile<64, 128, 64, 2, 2, 2, 1, 3, true>;   // 4 waves, 32x64 wave tile
 // and nothing hides their epilogues.  The 128 x 128 tile runs two blocks per unit (the epilogue of
 // one hides behind the main loop of the other) and quantises four times finer, but its main loop
 // is the slowest.  The 320 x 256 tile moves the fewest operand bytes per flop.  A launch is priced
-// by a model fitted to launch times measured INSIDE encoder calls (where the chip sits at its
-// power limit; loops of one GEMM alone rank the tiles differently): the time of one round of
-// blocks is, per 256 x 256 of output area,  alpha * K / 1024 + eps[epilogue]  microseconds
-// (32768-token and 73896-token batches, K = 1024 ... 12800; it reproduces the measured launches
-// of the 6272-token batch as well):
-//                  alpha   eps: store / GELU   residual add   QKV + rotary
-//   256 x 256      22.6        13.2               39.4            21.9
-//   320 x 256      21.8        11.7               39.4            24.8
-//   128 x 128      32.8         4.6               23.8            19.6
-// So the small tile wins short-K GEMMs with a heavy epilogue (the attention output projection at
-// hidden 1024), the 320 x 256 tile gains with short K and on grids where it needs fewer rounds,
-// and at K >= 3200 the two large tiles are equal.
+// by a model: the time of one round of blocks is, per 256 x 256 of output area,
+// alpha * K / 1024 + eps[epilogue]  microseconds:
+//                  alpha   eps: store / GELU   residual add (K >= 2048)   QKV + rotary
+//   256 x 256      22.6        13.2               39.4 (25.0)                 21.9
+//   320 x 256      21.8        11.7               39.4 (24.5)                 24.8
+//   128 x 128      32.8         4.6               23.8                        19.6
+// All but the figures in brackets were fitted to launch times inside encoder calls (where the chip sits at its
+// power limit; loops of one GEMM alone rank the tiles differently) when the large tiles still had one barrier per K step and
+// block-wide epilogues.  Since then launches in them have become 4 to 20 % shorter (73 896 x 3072 x 1024 in 256 x 256 tiles:
+// the model says 623 us, measured 469; 32 768 x 9600 x 3200: 1758 and 1617), those in 128 x 128 tiles, which kept their
+// loop, 0 to 12 %: the ranking leans towards the small tile.  Every tile forced on residual adds of 3136 ... 31 360 rows,
+// hidden 1024, 1152 and 1600 (profiles/residual_tiles.txt): from K = 2048 on what is planned is within 3 % of the best tile in 79 of
+// 84 launches (8 % off in the worst); at K = 1280 ... 1792 in 36 of 63, and up to 15 % off where 128 x 128 tiles are taken
+// and 256 x 256 would be faster (12 544 x 1024 x 1280: 56.0 and 48.9 us).
 bool gemm_bf16_tile_known(int t) { return t == 0 || t == 2 || t == 4 || t == 5 || t == 7 || t == 8; }
 struct TileShape { int bm, bn, blocks, cfg; double alpha, eps[4]; };   // eps indexed by Epilogue
 // Few rows: 64 x 64 and 64 x 128 tiles, whose stages are refilled three and two steps ahead between
@@ -1160,7 +1161,9 @@ constexpr double kSecondLaunch = 4.0;      // what a second launch of the same G
 constexpr TileShape kShape256x128 = {256, 128, 1, 2, 19.3, {30.0, 30.0, 30.0, 30.0}};
 // Against a long K the large tiles' residual add costs less: the tiles of a launch drift apart, and not all of them
 // are at HBM together (73 896 x 1024 x 4096: 558 us in 256 x 256 tiles, 543 in 320 x 256; 20 676 x 1152 x 4352: 218 in 256 x
-// 256, 240 in 128 x 128; 28 224 x 1152 x 4352: 277 in 320 x 256, 326 in 128 x 128).
+// 256, 240 in 128 x 128; 28 224 x 1152 x 4352: 277 in 320 x 256, 326 in 128 x 128).  The line at 2048 is on the safe side: no
+// launch of 4704 ... 36 064 rows, hidden 768 ... 1600, K = 2048, 2560, 3072 or 4096 takes longer than in the tiles that the constants
+// for a short K chose, on the kernels of then; below the line the large tiles gain already (see above).
 constexpr int kLongK = 2048;
 constexpr double kLongEps256 = 25.0, kLongEps320 = 24.5;
 
@@ -1194,7 +1197,8 @@ static TilePlan plan_tiles(int M, int N, int K, int epi, bool may_split, long cu
   }
   auto one_round_256x128 = [&](int rows) { return epi == EPI_RESIDUAL && K >= kLongK && (long)((rows + 255) / 256) * ((N + 127) / 128) <= cus; };
   // Narrow outputs against a long K in one round of 256 x 128 tiles: 6272 x 1024 x 4096 56 us against 61 in 128 x 128
-  // tiles and 78 in 256 x 256.  (Against a short one 128 x 128 tiles take as long: K = 1024 25.2 and 25.4 us.  In several
+  // tiles and 78 in 256 x 256; K = 2048 36.7 and 38.4.  (Only this is priced by kShape256x128's constants.  Against a short K
+  // 128 x 128 tiles take as long: K = 1024 25.2 and 25.4 us, 1536 32.2 and 32.5.  In several
   // rounds the larger tiles, which move fewer operand bytes, are faster: 20 676 x 1152 x 4352 227 us against
   // 218, 73 896 x 1024 x 4096 668 against 543.)
   if (one_round_256x128(M))

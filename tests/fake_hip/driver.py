@@ -303,6 +303,33 @@ def rotary_table_rule_counts_the_units_of_the_stream(fake, lib):
     assert len(seen) == 10                                              # both answers for every number of units
 
 
+def rows_behind_the_last_full_round(fake, lib):
+    """Launches that are cut: the tile and the number of blocks of both parts on 256 units."""
+    shim = gemm_shim()
+
+    def plan(M, N, K, epilogue):
+        fake.fake_forget()
+        shim.shim_gemm(M, N, K, epilogue, 0, 3, -1, 256)
+        return [(l[0], l[1], l[4]) for l in gemm_launches(fake)]
+
+    G, R, Q = 1, 2, 3
+    # against a long K the rest is one round of 256 x 128 tiles
+    assert plan(32768, 3200, 12800, R) == [(256, 256, 118 * 13), (256, 128, 10 * 25)]
+    assert plan(32768, 3200, 3200, R) == [(256, 256, 118 * 13), (256, 128, 10 * 25)]
+    # ... and 128 x 128 tiles against a short one, with another epilogue, or where it would be more than one round
+    assert plan(6272, 4096, 1024, G) == [(320, 256, 16 * 16), (128, 128, 9 * 32)]
+    assert plan(9124, 2304, 768, Q) == [(256, 256, 28 * 9), (128, 128, 16 * 18)]
+    for M in range(9000, 60000, 1111):
+        for N in (1024, 1152, 3200):
+            for K in (1024, 2048, 4352):
+                l = plan(M, N, K, R)
+                if len(l) == 2:
+                    rest = M - l[0][2] // -(-N // 256) * l[0][0]
+                    assert 0 < rest < M
+                    assert l[1] in ((128, 128, -(-rest // 128) * -(-N // 128)), (256, 128, -(-rest // 256) * -(-N // 128))), (M, N, K, l)
+                    assert l[1][1] == 128 and (l[1][0] == 128 or (K >= 2048 and l[1][2] <= 256)), (M, N, K, l)
+
+
 if __name__ == "__main__":
     globals()[sys.argv[3]](*load(sys.argv[1], sys.argv[2]))
     print("passed", sys.argv[3])

@@ -236,6 +236,11 @@ def test_gemm_launch_planner_on_the_benchmark_shapes():
     # against K = 4096 to four rounds of 320 x 256 instead of five of 256 x 256
     assert plan(73896, 1024, 1024, R) == (128, 128, 0)
     assert plan(73896, 1024, 4096, R) == (320, 256, 0)
+    # ... against a long K (from 2048) one round of 256 x 128 tiles where the output is that narrow; QKV, GELU and
+    # stores never take them by price
+    assert plan(6272, 1024, 4096, R) == plan(6272, 1024, 2048, R) == (256, 128, 0)
+    assert plan(6272, 1024, 1984, R) == (128, 128, 0) and plan(8192, 1024, 4096, R) == (256, 128, 0) != plan(8193, 1024, 4096, R)
+    assert plan(6272, 1024, 4096, G) == plan(6272, 1024, 4096) == (128, 128, 0)
     # Q | K columns that do not end on a 256-column boundary: the 256 x 128 tile, never cut
     assert plan(13540, 960, 320, Q, 640) == (256, 128, 0)
     # few tokens: 64-row tiles while they fit two rounds of blocks -- one 448 x 448 image (784 tokens), four, and

@@ -1,9 +1,10 @@
 """GPU test that gathering the merger's operand does not slow its GEMM down: the projection of 2 x 2 token windows
 against the same M x N x K product of plain rows, both with the same tile forced and timed by the
 library's own events.  The gathered one also reads the window list and cannot use the scalar row
-addresses of plain rows: measured 1.07 (256 x 256), 1.25 (128 x 128) and 1.12 (320 x 256) times as long.  With
-row numbers fetched between the loads of a stage, each waited for together with the loads before it,
-it was 1.37, 1.90 and 1.50 times.  The bounds stand between the two."""
+addresses of plain rows: measured 1.05 (256 x 256), 1.24 (128 x 128) and 1.04 (320 x 256) times as long.  The large tiles run the
+ping-pong loop on both; with the gathered one on the plain loop it was 1.22 and 1.20.  The 128 x 128 tile runs the plain
+loop on both; with row numbers fetched between the loads of a stage, each waited for together with the loads
+before it, it was 1.90.  The bounds stand between."""
 
 import pytest
 import torch
@@ -33,7 +34,7 @@ def merge_step_us(cfg, grids, tile):
     return sorted(times)[4]
 
 
-@pytest.mark.parametrize("tile, most", [(0, 1.2), (4, 1.5), (5, 1.28)])
+@pytest.mark.parametrize("tile, most", [(0, 1.13), (4, 1.5), (5, 1.12)])
 def test_gathered_merger_keeps_up_with_plain_rows(tile, most):
     base = dict(num_layers=0, mlp_dim=64, out_dim=4096)
     gathered = merge_step_us(small("bf16", hidden=1024, num_heads=16, merge=2, **base), [(1, 112, 224)], tile)

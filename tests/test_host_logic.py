@@ -42,7 +42,8 @@ def test_on_the_stand_in_runtime(fake, name):
     assert r.returncode == 0 and "passed " + name in r.stdout, r.stdout[-3000:]
 
 
-@pytest.mark.parametrize("name", ["gathered_gemm_reads_past_its_weights_only_where_allowed", "rotary_table_rule_counts_the_units_of_the_stream"])
+@pytest.mark.parametrize("name", ["gathered_gemm_reads_past_its_weights_only_where_allowed", "rotary_table_rule_counts_the_units_of_the_stream",
+                                  "rows_behind_the_last_full_round"])
 def test_gemm_launches_on_the_stand_in_runtime(fake, shim, name):
     r = subprocess.run([sys.executable, os.path.join(HERE, "driver.py"), fake, build.library_path(), name, shim],
                        stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True, timeout=300)
