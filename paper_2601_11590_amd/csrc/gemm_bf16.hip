@@ -1139,7 +1139,9 @@ using T8 = Tile<64, 128, 64, 2, 2, 2, 1, 3, true>;   // 4 waves, 32x64 wave tile
 // loop, 0 to 12 %: the ranking leans towards the small tile.  Every tile forced on residual adds of 3136 ... 31 360 rows,
 // hidden 1024, 1152 and 1600 (profiles/residual_tiles.txt): from K = 2048 on what is planned is within 3 % of the best tile in 79 of
 // 84 launches (8 % off in the worst); at K = 1280 ... 1792 in 36 of 63, and up to 15 % off where 128 x 128 tiles are taken
-// and 256 x 256 would be faster (12 544 x 1024 x 1280: 56.0 and 48.9 us).
+// and 256 x 256 would be faster (12 544 x 1024 x 1280: 56.0 and 48.9 us).  Whole batches, all products
+// (profiles/gemm_tile_model_fit.txt): 22 of 25 planned launches within 3 % of the best tile; behind it are the output
+// projections of 73 896 and 85 500 rows (275 us in 128 x 128 tiles, 241 in 320 x 256; 316 and 289) and the merger of 1568 (84, 63 in 256 x 128).
 bool gemm_bf16_tile_known(int t) { return t == 0 || t == 2 || t == 4 || t == 5 || t == 7 || t == 8; }
 struct TileShape { int bm, bn, blocks, cfg; double alpha, eps[4]; };   // eps indexed by Epilogue
 // Few rows: 64 x 64 and 64 x 128 tiles, whose stages are refilled three and two steps ahead between
@@ -1148,9 +1150,10 @@ struct TileShape { int bm, bn, blocks, cfg; double alpha, eps[4]; };   // eps in
 // long as on a full one: 784 x 1024 x 4096 is 56 tiles of 128 x 128 in 61 us, 208 of 64 x 64 in 21
 // (784 x 3072 x 1024: 23 us, 64 x 128 tiles 16).  They are offered while they fit two rounds of
 // blocks; beyond, the large tiles fill the chip themselves (3136 x 3072 x 1024: 1 round of 256 x 256
-// tiles 36 us, 64 x 64 in four rounds 44).  Their constants rank, they do not predict: measured in
-// calls with every tile forced, 196 ... 4608 tokens at hidden 1024, 1152 and 3200, the tile chosen is
-// the fastest or within 11 % of it, while the model is off by up to a half on single launches.
+// tiles 32 us, 64 x 64 in four rounds 44).  Their constants rank, they do not predict: measured in
+// calls with every tile forced, 196 ... 4608 tokens at hidden 1024, 1152 and 3200 (profiles/gemm_tile_few_rows.txt), the tile
+// chosen is within 3 % of the fastest in 59 of 70 launches and within 11 % in all but one (merger of 1152 rows: 74 us, 59 in
+// 256 x 128), while the model is off by up to a factor of two on single launches.
 constexpr TileShape kShape256 = {256, 256, 1, 0, 22.6, {13.2, 13.2, 39.4, 21.9}};
 constexpr TileShape kShape320 = {320, 256, 1, 5, 21.8, {11.7, 11.7, 39.4, 24.8}};
 constexpr TileShape kShape128 = {128, 128, 2, 4, 32.8, {4.6, 4.6, 23.8, 19.6}};
